@@ -762,7 +762,8 @@ __device__ void plan_general(const int64_t* __restrict__ size, const int32_t* __
 // LDS byte offsets of the regions of the LDS path (N = tensor slots):
 //   A [8N+8]   first (i32) and live-bytes deltas (u32, from 4N)
 //              -> fill: cursors (u16, at 0), predecessor counts (u16, at
-//                 2N+4), sizes in units (u32, at 4N+8)
+//                 w16: 2N+4 rounded up to a whole word), sizes in units (u32,
+//                 at 4N+8)
 //              -> placement words ofsz[N + 1]
 //   F [2N+4]   band lengths (u16), kept for placement
 //   E [2N+4]   left-list starts (u16, N + 1 of them)
@@ -771,11 +772,15 @@ __device__ void plan_general(const int64_t* __restrict__ size, const int32_t* __
 // The u64 sort keys of an unsorted trace use the space from 0 before the
 // reach pass, and the general path uses all of it (16N + 8 at least).
 struct BatchLds {
-    size_t a, f, e, r, t, total;
+    size_t a, pend, f, e, r, t, total;
 };
 __host__ __device__ inline BatchLds batch_lds(size_t N, size_t cap) {
     BatchLds L{};
     const size_t w16 = (2 * N + 4 + 3) & ~(size_t)3;  // N + 1 u16 entries, 4-byte multiple
+    // the counts take (N >> 1) + 1 words, up to 4N+8 for either parity of N;
+    // they are LDS atomics' targets, so they start on a whole word (2N+4 is
+    // none when N is odd)
+    L.pend = w16;
     L.a = 0;
     L.f = 8 * N + 8;
     L.e = L.f + w16;
@@ -823,7 +828,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     int32_t* fst = reinterpret_cast<int32_t*>(smem + R.a);
     uint32_t* live = reinterpret_cast<uint32_t*>(smem + R.a + 4 * N);
     uint32_t* cursor = reinterpret_cast<uint32_t*>(smem + R.a);
-    uint32_t* pend = reinterpret_cast<uint32_t*>(smem + R.a + 2 * N + 4);
+    uint32_t* pend = reinterpret_cast<uint32_t*>(smem + R.a + R.pend);
     uint32_t* su = reinterpret_cast<uint32_t*>(smem + R.a + 4 * N + 8);
     uint64_t* ofsz = reinterpret_cast<uint64_t*>(smem + R.a);
     uint64_t* keys = reinterpret_cast<uint64_t*>(smem);

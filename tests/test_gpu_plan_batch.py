@@ -146,14 +146,30 @@ def test_empty_batch_and_empty_traces():
     assert off.shape == (0,) and peak.shape == (0,)
 
 
-@pytest.mark.skip(reason="a trace of this shape, passed by mp_plan_trace to the batched planner as a "
-                         "batch of one (a small-trace route since removed), ended in a GPU memory "
-                         "aperture violation in plan_batch_kernel<256, 1, false>; no cause was found "
-                         "by reading, so the case stays off the GPU until one is")
 def test_one_slot_unsorted_full_bound():
     """An unsorted 255-tensor trace with 85 ops and lifetimes of up to 8 ops,
-    alone in a batch whose bound is its own length (one slot a thread)."""
+    alone in a batch whose bound is its own length (one slot a thread).  With an
+    odd bound the predecessor counts -- LDS words that atomics add to -- once
+    started halfway through a word; this case had ended in a memory aperture
+    violation."""
     binding = need_gpu()
     rng = np.random.default_rng(300)
     t = tg.random_trace(rng, 255, 85, max_len=8, sizes=[64, 192, 448])
     _check(binding, tg.concat([t]), max_trace_len=255)
+
+
+@pytest.mark.parametrize("bound", [3, 31, 257, 1023, 2047, 4095])
+def test_odd_bounds(bound):
+    """Odd bounds (the default bound is the longest trace's length): a trace of
+    the bound's length, recorded and in any order, under both fits."""
+    binding = need_gpu()
+    rng = np.random.default_rng(304)
+    traces = [tg.random_trace(rng, bound, bound, max_len=6, sorted_first=s, sizes=[64, 192, 448])
+              for s in (True, False)]
+    batch = tg.concat(traces)
+    for policy in (oracle.LOWEST_FIT, oracle.BEST_FIT):
+        print(f"case odd bound {bound}, policy {policy}", flush=True)
+        off, peak, _ = binding.plan_batch(*batch_to_device(batch), policy=policy)
+        eo, ep = oracle.plan_batch(batch.begin, batch.num_ops, batch.size, batch.first,
+                                   batch.last, policy)
+        assert np.array_equal(host(off), eo) and np.array_equal(host(peak), ep)
