@@ -6,6 +6,16 @@
 // op, once when the two coincide.  Each tensor then goes at the lowest (or the
 // tightest) gap left by the placed tensors whose lifetimes meet its own.
 //
+// Nearly every trace is planned by the batched planner's kernel with the
+// breadth order (plan_batch.hip): Kahn's rounds over the intersecting pairs,
+// 19-33 rounds for a 2000-tensor trace where the kernel here takes 2000 steps
+// (1024 traces of 2000 tensors: 5.88 ms here, 0.23 ms there, of which about
+// 0.08 ms is the rank sort).
+// It stays for the traces that path leaves (a peak of -1): sizes summing to
+// 2^31 units or more, more pairs than the LDS lists hold, more than 32
+// far-reaching tensors, more ops than the LDS holds breadths for, or under
+// BEST_FIT a tensor meeting more than 256 others.
+//
 // One workgroup per trace, the trace in LDS.  A tensor is placed with the op
 // that comes first in the op order among its two ops, so the whole order is a
 // sort of the tensors by (breadth of that op desc, op, size desc, id): op
@@ -72,6 +82,7 @@ __global__ __launch_bounds__(kBBlock) void breadth_kernel(
     __shared__ BreadthShared S;
     __shared__ uint64_t red[kBBlock / kWave];
     const int tid = threadIdx.x;
+    if (peak_out[blockIdx.x] != -1) return;  // planned by the batched planner's kernel
     const int64_t b0 = begin[blockIdx.x], b1 = begin[blockIdx.x + 1];
     if (b0 < 0 || b1 > n_tensors || b1 < b0 || b1 - b0 > kBMax) {
         if (tid == 0) raise_status(status, MP_EINVAL);
@@ -277,6 +288,9 @@ hipError_t launch_breadth(const int64_t* begin, int64_t n_traces, const int32_t*
                           int64_t n_tensors, int32_t policy, int64_t* offset_out,
                           int64_t* peak_out, int32_t* status, hipStream_t st) {
     if (n_traces == 0) return hipSuccess;
+    const hipError_t e = launch_breadth_lds(begin, n_traces, num_ops, size, first, last, n_tensors,
+                                            policy, offset_out, peak_out, status, st);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(breadth_kernel, dim3((unsigned)n_traces), dim3(kBBlock), 0, st, begin,
                        num_ops, size, first, last, n_tensors, policy, offset_out, peak_out,
                        status);

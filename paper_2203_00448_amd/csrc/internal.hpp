@@ -68,6 +68,12 @@ hipError_t launch_breadth(const int64_t* begin, int64_t n_traces, const int32_t*
                           const int64_t* size, const int32_t* first, const int32_t* last,
                           int64_t n_tensors, int32_t policy, int64_t* offset_out,
                           int64_t* peak_out, int32_t* status, hipStream_t st);
+// its traces that fit the batched planner's LDS path (plan_batch.hip); the
+// others get a peak of -1
+hipError_t launch_breadth_lds(const int64_t* begin, int64_t n_traces, const int32_t* num_ops,
+                              const int64_t* size, const int32_t* first, const int32_t* last,
+                              int64_t n_tensors, int32_t policy, int64_t* offset_out,
+                              int64_t* peak_out, int32_t* status, hipStream_t st);
 
 // device-wide prefix sums (scan.hip)
 size_t scan_workspace_bytes(int64_t n);

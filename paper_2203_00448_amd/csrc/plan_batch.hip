@@ -801,7 +801,110 @@ __device__ __forceinline__ int item_index(int k) {
     return t + k * BLOCK;
 }
 
-template <int BLOCK, int ITEMS, bool BEST>
+// The Greedy by Breadth ranks of a trace in LDS (0 <= n <= 4096, its sizes
+// below 2^31 units in all): rk[k] = rank of position tid + k * BLOCK.  An op's
+// breadth (a tensor's size at its first op and, if different, at its last) is
+// summed in `ops` (n_ops words, outside the first 12 bytes a tensor of smem
+// only while the keys are not written yet); a tensor is placed with whichever
+// of its two ops ranks first.  Positions are then sorted by (breadth desc, op)
+// -- a 64-bit key with the position in its low bits, so one bitonic sort --
+// and within the few tensors of one op each counts those before it by size and
+// id.  Bound by the sort's barriers: 66 stages for 2048 tensors.
+template <int BLOCK, int ITEMS>
+__device__ __forceinline__ void breadth_ranks(
+    const int64_t* __restrict__ size, const int32_t* __restrict__ first,
+    const int32_t* __restrict__ last, int64_t lo, int n, int32_t n_ops, int sh,
+    const uint32_t (&su_r)[ITEMS], const uint16_t* perm, unsigned char* smem, uint32_t* ops,
+    uint16_t (&rk)[ITEMS]) {
+    const int tid = threadIdx.x;
+    int m = 1;
+    while (m < n) m <<= 1;
+    uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
+    uint32_t* units = reinterpret_cast<uint32_t*>(smem + 8 * (size_t)m);  // by position
+    uint16_t* ranks = reinterpret_cast<uint16_t*>(smem);                  // over the dead keys
+    for (int o = tid; o < n_ops; o += BLOCK) ops[o] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = item_index<BLOCK>(k);
+        if (i < n) {
+            const int32_t f = first[lo + i], l = last[lo + i];
+            atomicAdd(&ops[f], su_r[k]);
+            if (l != f) atomicAdd(&ops[l], su_r[k]);
+        }
+    }
+    __syncthreads();
+    uint64_t key[ITEMS];
+    uint32_t un[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int q = item_index<BLOCK>(k);
+        key[k] = ~0ull;
+        un[k] = su_r[k];
+        if (q < n) {
+            const int i = perm ? (int)perm[q] : q;
+            const int32_t f = first[lo + i], l = last[lo + i];
+            const uint32_t bf = ops[f], bl = ops[l];
+            const uint32_t br = bf >= bl ? bf : bl, op = (uint32_t)(bf >= bl ? f : l);
+            // breadth below 2^31, op below 2^21 (n_ops words fit the LDS)
+            key[k] = ((uint64_t)(0x7FFFFFFFu - br) << 33) | ((uint64_t)op << 12) | (uint32_t)q;
+            if (perm) un[k] = (uint32_t)((uint64_t)size[lo + i] >> sh);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int q = item_index<BLOCK>(k);
+        if (q < m) keys[q] = key[k];
+        if (q < n) units[q] = un[k];
+    }
+    __syncthreads();
+    bitonic_sort_u64<BLOCK>(keys, m);
+    uint32_t pr[ITEMS];  // position and rank of the tensor in this thread's slots
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = item_index<BLOCK>(k);
+        pr[k] = 0;
+        if (i < n) {
+            const uint64_t me = keys[i], op = me >> 12;
+            const uint32_t p = (uint32_t)me & 0xFFFu, u = units[p];
+            auto before = [&](uint32_t o) {  // does position o rank before p? (one op)
+                const uint32_t v = units[o];
+                if (v != u) return v > u;
+                return perm ? perm[o] < perm[p] : o < p;
+            };
+            int s = i;
+            uint32_t cnt = 0;
+            for (; s > 0 && (keys[s - 1] >> 12) == op; --s)
+                cnt += before((uint32_t)keys[s - 1] & 0xFFFu) ? 1u : 0u;
+            for (int e = i + 1; e < n && (keys[e] >> 12) == op; ++e)
+                cnt += before((uint32_t)keys[e] & 0xFFFu) ? 1u : 0u;
+            pr[k] = p | (((uint32_t)s + cnt) << 16);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = item_index<BLOCK>(k);
+        if (i < n) ranks[pr[k] & 0xFFFFu] = (uint16_t)(pr[k] >> 16);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int q = item_index<BLOCK>(k);
+        rk[k] = q < n ? ranks[q] : (uint16_t)0;
+    }
+    __syncthreads();
+}
+
+// BREADTH: Greedy by Breadth (breadth.hip) on the same schedule.  A greedy in
+// any total order equals Kahn's rounds over the pairs that intersect, so only
+// the order of a pair differs: by the rank of (breadth of the tensor's op
+// desc, op, size desc, id), found once by breadth_ranks below.  The call has
+// no workspace: an unsorted trace's permutation sits in its own offset_out
+// until the outputs are written, and a trace that the LDS path cannot hold is
+// left to breadth_kernel, marked by a peak of -1.
+template <int BLOCK, int ITEMS, bool BEST, bool BREADTH>
 __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_batch_kernel(
     const int64_t* __restrict__ begin, const int32_t* __restrict__ num_ops,
     const int64_t* __restrict__ size, const int32_t* __restrict__ first,
@@ -830,6 +933,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     uint32_t* cursor = reinterpret_cast<uint32_t*>(smem + R.a);
     uint32_t* pend = reinterpret_cast<uint32_t*>(smem + R.a + R.pend);
     uint32_t* su = reinterpret_cast<uint32_t*>(smem + R.a + 4 * N + 8);
+    uint16_t* rank16 = reinterpret_cast<uint16_t*>(su);  // BREADTH: ranks in the sizes' place
     uint64_t* ofsz = reinterpret_cast<uint64_t*>(smem + R.a);
     uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
     uint16_t* rlen = reinterpret_cast<uint16_t*>(smem + R.f);
@@ -852,12 +956,13 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     }
     const int64_t lo = begin[b], hi = begin[b + 1];
     const int32_t n_ops = num_ops[b];
-    if (lo < 0 || hi < lo || hi > n_tensors || n_ops < 0 || hi - lo > cap_n) {
+    if (lo < 0 || hi < lo || hi > n_tensors || (!BREADTH && n_ops < 0) || hi - lo > cap_n) {
         if (tid == 0) raise_status(status, MP_EINVAL);
         return;
     }
     const int n = (int)(hi - lo);
-    unsigned char* tws = trace_ws(ws, lo, b);
+    unsigned char* tws = BREADTH ? reinterpret_cast<unsigned char*>(offset_out + lo)
+                                 : trace_ws(ws, lo, b);
     uint16_t* perm = reinterpret_cast<uint16_t*>(tws);  // ids by position (unsorted traces)
 
     // ---- ingest + checks (ids owned strided: i = tid + k * BLOCK).  The
@@ -923,7 +1028,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     }
     {
         int32_t code = (flags & 1u) ? MP_EINVAL : MP_OK;
-        if (total > (uint64_t)INT64_MAX) code = MP_EOVERFLOW;
+        if (total > (uint64_t)INT64_MAX && !(BREADTH && code != MP_OK)) code = MP_EOVERFLOW;
         if (code != MP_OK) {
             if (tid == 0) raise_status(status, code);
             return;
@@ -947,6 +1052,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     auto id_of = [&](int q) { return unsorted ? (int)perm[q] : q; };  // position -> id
 
     uint32_t live_max = 0, n_pairs = 0;
+    uint16_t rk_r[ITEMS];  // BREADTH: ranks of this thread's positions
     if (!general) {
         // ---- position order (first, id); recorded traces are normally sorted already
         if (unsorted) {
@@ -962,10 +1068,19 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
                 if (q < n) perm[q] = (uint16_t)(keys[q] & 0xFFFFu);
             }
             l2_barrier();  // the keys are dead: first[] goes back in position order
+        }
+        if constexpr (BREADTH) {
+            general = (size_t)n_ops * 4 > R.total - R.e;  // the ops' breadths do not fit
+            if (!general)
+                breadth_ranks<BLOCK, ITEMS>(size, first, last, lo, n, n_ops, sh, su_r,
+                                            unsorted ? perm : nullptr, smem,
+                                            reinterpret_cast<uint32_t*>(smem + R.e), rk_r);
+        }
+        if (unsorted || BREADTH) {
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const int q = item_index<BLOCK>(k);
-                if (q < n) fst[q] = first[lo + perm[q]];
+                if (q < n) fst[q] = first[lo + id_of(q)];
             }
         }
         for (int i = tid; i <= n; i += BLOCK) live[i] = 0;
@@ -1036,8 +1151,10 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
                     }
                 }
                 rlen[q] = (uint16_t)(a - q - 1);
-                atomicAdd(&live[q], sq);
-                atomicAdd(&live[a], 0u - sq);
+                if (!BREADTH) {
+                    atomicAdd(&live[q], sq);
+                    atomicAdd(&live[a], 0u - sq);
+                }
                 packed_add(hist, (uint32_t)a, 1u);
                 if ((uint32_t)(a - q - 1) > kMaxDist) {  // reaches beyond a one-byte distance
                     const uint32_t slot = atomicAdd(&nlong, 1u);
@@ -1047,7 +1164,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
         }
         __syncthreads();
         MP_STAMP(3);
-        general = nlong > kLongSlots;
+        general = general || nlong > kLongSlots;
     }
     if (!general) {
         // ---- one prefix pass over positions j (contiguous chunk per thread):
@@ -1129,6 +1246,10 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
         }
         general = n_pairs > (uint32_t)cap_lists || (best && kmax > kBestMaxK);
     }
+    if (BREADTH && general) {
+        if (tid == 0) peak_out[b] = -1;  // breadth_kernel takes this trace
+        return;
+    }
     if (general) {
         __syncthreads();
         uint64_t pk = 0, bound = 0;
@@ -1148,7 +1269,11 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int q = item_index<BLOCK>(k);
-        if (q < n) su[q] = unsorted ? (uint32_t)((uint64_t)size[lo + perm[q]] >> sh) : su_r[k];
+        if (BREADTH) {
+            if (q < n) rank16[q] = rk_r[k];
+        } else if (q < n) {
+            su[q] = unsorted ? (uint32_t)((uint64_t)size[lo + perm[q]] >> sh) : su_r[k];
+        }
     }
     __syncthreads();
 
@@ -1166,13 +1291,13 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
             }
             int q = a;
             uint32_t base = bstart[q], nxt = bstart[q + 1];
-            uint32_t sq = su[q];
+            uint32_t sq = BREADTH ? rank16[q] : su[q];
             for (uint32_t p = p_lo; p < p_hi; ++p) {
                 while (nxt <= p) {
                     ++q;
                     base = nxt;
                     nxt = bstart[q + 1];
-                    sq = su[q];
+                    sq = BREADTH ? rank16[q] : su[q];
                 }
                 const uint32_t j = (uint32_t)q + 1 + (p - base);
                 const uint32_t d = j - (uint32_t)q;
@@ -1184,7 +1309,8 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
                     ent = kLongBase + s;
                 }
                 lents[packed_add(cursor, j, 1u)] = (uint8_t)ent;
-                packed_add(pend, sq >= su[j] ? j : (uint32_t)q, 1u);  // j ranks after q?
+                const bool after = BREADTH ? sq < rank16[j] : sq >= su[j];  // j ranks after q?
+                packed_add(pend, after ? j : (uint32_t)q, 1u);
             }
         }
     }
@@ -1209,7 +1335,12 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
             const uint32_t K = (uint32_t)lbeg[q + 1] - lbeg[q] + rlen[q];
             const uint32_t c = ready_class(K, best);
             const uint32_t pc = packed_get(pend, (uint32_t)q);
-            w_r[k] = ((uint64_t)(kUnplacedBit | class_bits(c) | pc) << 32) | su[q];
+            uint32_t units;
+            if constexpr (BREADTH)
+                units = unsorted ? (uint32_t)((uint64_t)size[lo + perm[q]] >> sh) : su_r[k];
+            else
+                units = su[q];
+            w_r[k] = ((uint64_t)(kUnplacedBit | class_bits(c) | pc) << 32) | units;
             cls_r[k] = pc == 0 ? c + 8 : c;  // +8: a seed
             const uint32_t f = 1u << (10u * (c < 3u ? c : c - 3u));
             tlo += c < 3u ? f : 0u;
@@ -1437,12 +1568,22 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
 
     // ---- outputs
     uint32_t pk = 0;
+    if constexpr (BREADTH) {
+        // the permutation lies in offset_out: every thread has read its part
+        // before any offset is written
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const int q = item_index<BLOCK>(k);
+            rk_r[k] = (uint16_t)(q < n ? id_of(q) : 0);
+        }
+        __syncthreads();
+    }
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int q = item_index<BLOCK>(k);
         if (q < n) {
             const uint64_t w = ofsz[q];
-            offset_out[lo + id_of(q)] = (int64_t)((uint64_t)word_off(w) << sh);
+            offset_out[lo + (BREADTH ? (int)rk_r[k] : id_of(q))] = (int64_t)((uint64_t)word_off(w) << sh);
             const uint32_t e = word_end(w);
             pk = pk > e ? pk : e;
         }
@@ -1461,9 +1602,9 @@ __global__ void reset_status_kernel(int32_t* status) { *status = MP_OK; }
 // is dynamic).
 constexpr size_t kStaticLds = 512;
 
-template <int BLOCK, int ITEMS, bool BEST>
+template <int BLOCK, int ITEMS, bool BEST, bool BREADTH = false>
 hipError_t launch_items(const BatchArgs& a, const BatchShape& s, hipStream_t st) {
-    auto kern = plan_batch_kernel<BLOCK, ITEMS, BEST>;
+    auto kern = plan_batch_kernel<BLOCK, ITEMS, BEST, BREADTH>;
     hipFuncAttributes fa{};
     hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
     if (e != hipSuccess) return e;
@@ -1563,6 +1704,29 @@ hipError_t launch_plan_batch(const BatchArgs& a, hipStream_t st) {
         case 8: return best ? launch_items<B, 8, true>(a, s, st) : launch_items<B, 8, false>(a, s, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+// Greedy by Breadth of the traces that fit the LDS path (256 threads, up to
+// 2048 tensors); a trace it leaves has a peak of -1.  The call states no bound
+// on its traces: with at most 512 tensors in all the slots are 512 (two a
+// thread), else the longest that is accepted.
+hipError_t launch_breadth_lds(const int64_t* begin, int64_t n_traces, const int32_t* num_ops,
+                              const int64_t* size, const int32_t* first, const int32_t* last,
+                              int64_t n_tensors, int32_t policy, int64_t* offset_out,
+                              int64_t* peak_out, int32_t* status, hipStream_t st) {
+    static_assert(MP_BREADTH_MAX_TRACE_LEN == kBatchBlock * kMaxItems, "slots of the longest trace");
+    constexpr int64_t kFew = 2 * kBatchBlock;
+    const bool few = n_tensors <= kFew, best = policy == MP_BEST_FIT;
+    const BatchShape s = batch_shape(few ? kFew : MP_BREADTH_MAX_TRACE_LEN);
+    if (!s.ok) return hipErrorInvalidValue;
+    const BatchArgs a{begin, n_traces, num_ops, size, first, last, n_tensors, s.cap_n,
+                      offset_out, peak_out, nullptr, status, nullptr, policy};
+    constexpr int B = kBatchBlock;
+    if (few)
+        return best ? launch_items<B, 2, true, true>(a, s, st)
+                    : launch_items<B, 2, false, true>(a, s, st);
+    return best ? launch_items<B, 8, true, true>(a, s, st)
+                : launch_items<B, 8, false, true>(a, s, st);
 }
 
 }  // namespace mp

@@ -249,3 +249,46 @@ def test_breadth_status_codes():
         st = binding.new_status()
         binding.plan_breadth_batch(*batch_to_device(tg.concat([t])), check=False, status=st)
         assert int(st.item()) == binding.MP_EINVAL
+
+
+def _breadth_edges():
+    """Traces on both sides of what the batched planner's LDS path holds."""
+    rng = np.random.default_rng(45)
+    cap = 11728  # its pair lists at 2048 tensors; the exact value only picks a side
+    chain = np.arange(2048, dtype=np.int32)
+    out = {}
+    for order in (True, False):  # one op's tensors tie by size, then id, in any order of the ids
+        out[f"ties, sorted {order}"] = tg.random_trace(rng, 500, 20, max_len=3, sizes=[64, 128],
+                                                       sorted_first=order)
+        out[f"2048, sorted {order}"] = tg.random_trace(rng, 2048, 2048, max_len=6, unit=4,
+                                                       sorted_first=order)
+    out["513 of one size, shuffled"] = tg.random_trace(rng, 513, 300, max_len=4, sizes=[320])
+    # more ops than the breadths fit in LDS, and as many as fit
+    for ops in (4900, 5100, 9000):
+        out[f"{ops} ops"] = tg.random_trace(rng, 700, ops, max_len=30)
+    far = tg.random_trace(rng, 1500, 1500, max_len=3, sorted_first=True)
+    for k in (32, 33):  # far-reaching tensors the lists can name, and one more
+        t = tg.Trace(far.size.copy(), far.first.copy(), far.last.copy(), far.num_ops)
+        t.last[np.arange(k) * 10] = np.minimum(t.first[np.arange(k) * 10] + 600, 1499)
+        out[f"{k} far-reaching"] = t
+    size = 64 * rng.integers(1, 5000, 2048)
+    for last in (np.minimum(chain + 5, 2047), np.minimum(chain + cap // 2000 + 1, 2047)):
+        out[f"pairs, band {int(last[0])}"] = tg.Trace(size, chain, last.astype(np.int32), 2048)
+    wide = tg.random_trace(rng, 300, 200, max_len=5)
+    wide.size[:] = rng.integers(2 ** 28, 2 ** 34, 300) | 1
+    out["64-bit unit counts"] = wide
+    star = tg.random_trace(rng, 300, 300, max_len=1, sizes=[64], sorted_first=True)
+    star.last[0] = 299
+    out["one tensor meeting 299"] = star
+    return out
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("name", list(_breadth_edges()))
+def test_breadth_paths(name, policy):
+    binding = need_gpu()
+    print(f"case breadth {name}, policy {policy}", flush=True)
+    t = _breadth_edges()[name]
+    _check_breadth(binding, [t], policy)
+    # among others of either path, so that the traces left over are found
+    _check_breadth(binding, [tg.resnext_trace(1, 900), t, tg.chain256(), t], policy)
