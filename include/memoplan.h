@@ -286,12 +286,12 @@ int32_t mp_bump_plan(const int64_t* begin, int64_t n_traces, const int64_t* size
                      size_t workspace_bytes, int32_t* status_out, void* stream);
 
 /* The optimum of Eq. 2.1 (the least total_mem under its pairwise
- * constraints; the thesis's mip strategy) for tiny traces, by exhaustive
- * search: the least peak over all placement orders with each tensor at the
- * lowest offset that overlaps no placed tensor whose lifetime meets its own
- * (an optimal plan listed by offset is such an order).  One workgroup per
- * trace; subtrees whose partial peak reaches the best found are cut, and a
- * trace stops once the best equals its live-bytes lower bound.
+ * constraints; the thesis's mip strategy) for tiny traces, by branch and
+ * bound: the least peak over the placement orders in which offsets never
+ * fall, each tensor above its placed neighbours (an optimal plan listed by
+ * offset can be brought to that form).  One wave per trace; subtrees that
+ * cannot end below the best peak found are cut, and a trace stops once the
+ * best equals its live-bytes lower bound.
  *   begin[n_traces + 1] int64, num_ops[n_traces] int32, size/first/last
  *              [n_tensors]: as for mp_plan_batch; each trace at most
  *              MP_OPT_MAX_N tensors.

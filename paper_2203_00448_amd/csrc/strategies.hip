@@ -1,7 +1,7 @@
 // The planning strategies that Section 2.3 sets beside greedy_by_size:
 // bump_allocation, the baseline that never reuses memory, and the optimum of
-// Eq. 2.1, which the thesis reaches through a MIP solver and which here is an
-// exhaustive search over placement orders for tiny traces.
+// Eq. 2.1, which the thesis reaches through a MIP solver and which here is a
+// branch and bound search over placement orders for tiny traces.
 #include "internal.hpp"
 #include "mp_device.hpp"
 
@@ -139,195 +139,339 @@ BumpLayout bump_layout(int64_t n) {
 int bit_width64(uint64_t x) { return x ? 64 - __builtin_clzll(x) : 0; }
 
 // ---------------------------------------------------------------------------
-// The optimum of Eq. 2.1 for a tiny trace: the least peak over all placement
-// orders, each tensor at the lowest offset where it overlaps no placed tensor
-// whose lifetime meets its own (sorting an optimal plan by offset gives an
-// order that reaches the optimum this way).  One workgroup per trace; each
-// thread takes prefixes of the order (unranked from their index) and searches
-// below them depth first.  A subtree is cut as soon as its partial peak
-// reaches the best peak found so far by any thread of the workgroup, and the
-// whole search stops once that best equals the live-bytes lower bound.
+// The optimum of Eq. 2.1 for a tiny trace.  List an optimal plan by (offset,
+// tensor) and put each tensor, in that order, at the lowest offset clear of the
+// ones before it: no tensor moves up, so the peak stays optimal, and repeating
+// it ends (the offsets' sum falls) in a plan whose own order reproduces it.  In
+// that order offsets never fall, so a tensor's place is simply the highest end
+// among its neighbours placed before it (its base), and it is enough to search
+// orders in which
+//   - (base, tensor) does not fall from one tensor to the next, and
+//   - no tensor is put at or above the end that another unplaced tensor would
+//     have at its own base (nothing later could cover that place, so the other
+//     one would not be at its lowest offset).
+// A subtree is cut when an unplaced tensor, or the unplaced tensors alive at
+// one op stacked from the last offset on, cannot end below the best peak; the
+// search stops at the live-bytes lower bound.  The best starts at the greedy by
+// size plan, which reaches the bound for nine in ten of the tiny ResNeXt-like
+// traces.
+//
+// One wave per trace.  Tensors are numbered by size descending, so the masks
+// below are the same for every lane and sit in scalar registers; a lane holds
+// its tensors' ends in registers and searches depth first below prefixes of the
+// order (the first kOptPrefix levels, dealt to the lanes as they become free).
+// Each turn of the loop evaluates the lane's node and either places a tensor or
+// backs up, without memory accesses: bound by instruction issue (about 500
+// vector instructions a turn) and by the longest search of the batch.  All
+// lanes share the best peak through ballots, so the plan found does not depend
+// on timing.  2048 traces of 10 tensors: 6.80 ms for the search over all n!
+// orders in one workgroup a trace, 0.10 ms for this one.
 
-constexpr int kOBlock = 256;
 constexpr int kOptMaxN = MP_OPT_MAX_N;
+static_assert(kOptMaxN <= 15, "tensor numbers in 4 bits");
 
 struct OptShared {
-    int64_t sz[kOptMaxN];
+    int64_t sz[kOptMaxN];      // by rank (size descending, id)
+    int32_t first[kOptMaxN], last[kOptMaxN];
+    int32_t id[kOptMaxN];
     uint32_t meets[kOptMaxN];  // bit j: lifetimes of i and j meet (j != i)
-    // per-thread search state, thread index fastest (no bank conflicts)
-    int64_t off[kOptMaxN][kOBlock];
-    int64_t peak[kOptMaxN + 1][kOBlock];  // peak after k placements
-    uint8_t order[kOptMaxN][kOBlock];     // tensor placed k-th
-    uint8_t cand[kOptMaxN + 1][kOBlock];  // next tensor to try at level k
-    uint8_t best_order[kOptMaxN][kOBlock];
-    unsigned long long best;  // least peak found by the workgroup
-    int64_t lb;
-    int32_t winner;
-    int32_t bad;
+    uint32_t alive[kOptMaxN];  // bit j: j is alive at i's first op
 };
 
-// Lowest offset for tensor c: 0 or the end of a placed tensor whose lifetime
-// meets c's, the least of them where c overlaps none of those tensors.
-__device__ int64_t opt_lowest_fit(const OptShared& S, int c, uint32_t placed, int t) {
-    const uint32_t nb = placed & S.meets[c];
-    const int64_t s = S.sz[c];
-    int64_t best = -1;
-    for (uint32_t cands = nb | (1u << 31); cands; cands &= cands - 1) {
-        const int a = __builtin_ctz(cands);
-        const int64_t x = a == 31 ? 0 : S.off[a][t] + S.sz[a];
-        if (best >= 0 && x >= best) continue;
-        bool free_here = true;
-        for (uint32_t m = nb; m && free_here; m &= m - 1) {
-            const int j = __builtin_ctz(m);
-            const int64_t oj = S.off[j][t];
-            if (x < oj + S.sz[j] && oj < x + s) free_here = false;
-        }
-        if (free_here) best = x;
+__device__ __forceinline__ uint32_t opt_uniform(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ uint64_t opt_uniform(uint64_t v) {
+    return ((uint64_t)opt_uniform((uint32_t)(v >> 32)) << 32) | opt_uniform((uint32_t)v);
+}
+template <typename T>
+__device__ __forceinline__ T opt_wave_min(T v) {
+    return wave_reduce(v, OpMin<T>());
+}
+
+// The search over T counts of the trace's unit.  `ends`: this lane's best plan
+// (the greedy one in every lane to start with), `best` its peak; returns the
+// least peak found, `mine` the peak of the lane's `ends`.
+template <typename T>
+__device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb, T best, T (&ends)[kOptMaxN],
+                        T* mine_out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint64_t below = (1ull << lane) - 1ull;
+    const uint32_t all = (1u << n) - 1u;
+    T sz[kOptMaxN];
+    uint32_t meets[kOptMaxN], alive[kOptMaxN];
+    T left0[kOptMaxN];  // sizes alive at i's first op, all unplaced
+#pragma unroll
+    for (int i = 0; i < kOptMaxN; ++i) {
+        const int c = i < n ? i : 0;
+        sz[i] = i < n ? opt_uniform((T)((uint64_t)S.sz[c] >> sh)) : T(0);
+        meets[i] = i < n ? opt_uniform(S.meets[c]) : 0u;
+        alive[i] = i < n ? opt_uniform(S.alive[c]) : 0u;
     }
+#pragma unroll
+    for (int i = 0; i < kOptMaxN; ++i) {
+        left0[i] = 0;
+#pragma unroll
+        for (int j = 0; j < kOptMaxN; ++j) left0[i] += ((alive[i] >> j) & 1u) ? sz[j] : T(0);
+    }
+    // prefixes of two tensors (at most 132 for 64 lanes), or of three from 11
+    // tensors on, where single subtrees get long enough to idle the others
+    const int d = n < 2 ? n : (n <= 10 ? 2 : 3);
+    uint32_t n_pre = 1;
+    for (int k = 0; k < d; ++k) n_pre *= (uint32_t)(n - k);
+    uint32_t next_pre = 0;  // uniform
+
+    T end[kOptMaxN];   // ends of the placed tensors, 0 while unplaced
+    T left[kOptMaxN];  // sizes of the unplaced tensors alive at i's first op
+    T mine = best;
+    uint64_t order = 0;  // 4 bits a level
+    uint32_t placed = 0, from = 0, forced = 0;
+    int level = 0;
+    bool busy = false, out = false;
+    while (true) {
+        // lanes without a subtree take the next prefixes, in lane order
+        const uint64_t want = __ballot(!busy && !out);
+        if (want) {
+            const uint32_t p = next_pre + (uint32_t)__popcll(want & below);
+            if (!busy && !out) {
+                if (p < n_pre) {
+                    busy = true;
+                    uint32_t q = p, free_ids = all;
+                    forced = 0;
+                    for (int k = 0; k < d; ++k) {  // the p-th prefix, in mixed radix
+                        const uint32_t r = (uint32_t)(n - k), digit = q % r;
+                        q /= r;
+                        uint32_t f = free_ids;
+                        for (uint32_t t = 0; t < digit; ++t) f &= f - 1;
+                        const uint32_t c = (uint32_t)__builtin_ctz(f);
+                        forced |= c << (4 * k);
+                        free_ids &= ~(1u << c);
+                    }
+                    placed = from = 0;
+                    order = 0;
+                    level = 0;
+#pragma unroll
+                    for (int i = 0; i < kOptMaxN; ++i) {
+                        end[i] = 0;
+                        left[i] = left0[i];
+                    }
+                } else {
+                    out = true;
+                }
+            }
+            next_pre += (uint32_t)__popcll(want);
+        }
+        if (!__ballot(busy)) break;
+        // ---- the node: bases, the cuts, and the tensors that may come next
+        const int prev = level ? (int)((order >> (4 * (level - 1))) & 15u) : -1;
+        T last = 0, limit = ~T(0), need = 0;
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i) last = i == prev ? end[i] - sz[i] : last;
+        T base[kOptMaxN];
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i) {
+            T b = 0;
+            // the mask goes through an empty asm each turn: hoisted out of the
+            // loop, its bits became 132 lane masks and were spilled
+            uint32_t mi = meets[i];
+            asm volatile("" : "+s"(mi));
+#pragma unroll
+            for (int j = 0; j < kOptMaxN; ++j) {
+                const T e = end[j] & (T)(int64_t)((int32_t)(mi << (31 - j)) >> 31);
+                b = e > b ? e : b;
+            }
+            base[i] = b;
+            const bool un = i < n && !((placed >> i) & 1u);
+            const T e = b + sz[i], h = (b > last ? b : last) + sz[i];
+            limit = un && e < limit ? e : limit;
+            need = un && h > need ? h : need;
+            const T l = last + left[i];  // the tensors left at i's first op, stacked
+            need = i < n && left[i] && l > need ? l : need;
+        }
+        uint32_t cand = 0;
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i) {
+            const bool ok = base[i] < limit && (base[i] > last || (base[i] == last && i > prev));
+            cand |= ok ? 1u << i : 0u;
+        }
+        cand = need < best ? cand & all & ~placed & ~((1u << from) - 1u) : 0u;
+        const bool pre = level < d;
+        if (pre) cand &= 1u << ((forced >> (4 * level)) & 15u);
+        const bool place = busy && cand != 0;
+        // ---- place the lowest candidate, or take the last tensor back
+        const int c = place ? (int)__builtin_ctz(cand) : prev;
+        // a prefix that cannot be placed, or whose subtree is done, is left
+        const bool drop = busy && !place && (pre || level == d);
+        const bool back = busy && !place && !drop;
+        const bool moves = place || back;
+        uint32_t at = 0;
+        T s = 0;
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i) {
+            s = i == c ? sz[i] : s;
+            const T e = place ? base[i] + sz[i] : T(0);
+            end[i] = moves && i == c ? e : end[i];
+            at |= ((alive[i] >> (c & 31)) & 1u) << i;  // the first ops at which c is alive
+        }
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i) {
+            const T v = moves && ((at >> i) & 1u) ? s : T(0);
+            left[i] = place ? left[i] - v : left[i] + v;
+        }
+        if (place) {
+            order |= (uint64_t)c << (4 * level);
+            placed |= 1u << c;
+            ++level;
+            from = 0;
+        } else if (back) {
+            --level;
+            order &= ~(15ull << (4 * level));
+            placed &= ~(1u << c);
+            from = (uint32_t)c + 1u;
+        }
+        if (drop) busy = false;
+        if (__ballot(busy && level == n)) {  // complete orders
+            T pk = ~T(0);
+            if (busy && level == n) {
+                pk = 0;
+#pragma unroll
+                for (int i = 0; i < kOptMaxN; ++i) pk = end[i] > pk ? end[i] : pk;
+                if (pk < mine) {
+                    mine = pk;
+#pragma unroll
+                    for (int i = 0; i < kOptMaxN; ++i) ends[i] = end[i];
+                }
+                if (n == d) busy = false;  // the prefix was the whole order
+            }
+            const T low = opt_wave_min(pk);
+            best = low < best ? low : best;
+            if (best <= lb) break;
+        }
+    }
+    *mine_out = mine;
     return best;
 }
 
-__global__ __launch_bounds__(kOBlock) void optimal_kernel(
+// Greedy by size over T units (tensors in rank order, each at the lowest
+// offset that fits), by one wave: lane a tries the end of tensor a, lane n
+// offset 0.  Returns the peak; ends[] the same in every lane.
+template <typename T>
+__device__ __forceinline__ T opt_greedy(const OptShared& S, int n, int sh, T (&ends)[kOptMaxN]) {
+    const int lane = threadIdx.x & (kWave - 1);
+    T pk = 0;
+#pragma unroll
+    for (int i = 0; i < kOptMaxN; ++i) ends[i] = 0;
+    T my_end = 0;  // of the tensor this lane holds
+    for (int t = 0; t < n; ++t) {
+        const T s = (T)((uint64_t)S.sz[t] >> sh);
+        const uint32_t nb = S.meets[t] & ((1u << t) - 1u);
+        bool ok = lane == n || ((nb >> (lane & 31)) & 1u && lane < t);
+        const T x = lane == n ? T(0) : my_end;
+        for (uint32_t m = nb; m; m &= m - 1) {
+            const int j = __builtin_ctz(m);
+            const T e = (T)__shfl(my_end, j, kWave), o = e - (T)((uint64_t)S.sz[j] >> sh);
+            if (x < e && o < x + s) ok = false;
+        }
+        const T at = opt_wave_min(ok ? x : ~T(0));
+        if (lane == t) my_end = at + s;
+        pk = at + s > pk ? at + s : pk;
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i) ends[i] = i == t ? at + s : ends[i];
+    }
+    return pk;
+}
+
+template <typename T>
+__device__ __forceinline__ void opt_plan(const OptShared& S, int n, int sh, uint64_t lb_bytes, int64_t b0,
+                         int64_t* __restrict__ offset_out, int64_t* __restrict__ peak) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const T lb = (T)(lb_bytes >> sh);
+    T ends[kOptMaxN], mine;
+    T best = opt_greedy<T>(S, n, sh, ends);
+    mine = best;
+    if (best > lb) best = opt_search<T>(S, n, sh, lb, best, ends, &mine);
+    const uint64_t win = __ballot(mine == best);
+    if (lane == (int)__builtin_ctzll(win)) {
+#pragma unroll
+        for (int i = 0; i < kOptMaxN; ++i)
+            if (i < n) offset_out[b0 + S.id[i]] = (int64_t)((uint64_t)ends[i] << sh) - S.sz[i];
+        *peak = (int64_t)((uint64_t)best << sh);
+    }
+}
+
+__global__ __launch_bounds__(kWave) void optimal_kernel(
     const int64_t* __restrict__ begin, const int32_t* __restrict__ num_ops,
     const int64_t* __restrict__ size, const int32_t* __restrict__ first,
     const int32_t* __restrict__ last, int64_t n_tensors, int64_t* __restrict__ offset_out,
     int64_t* __restrict__ peak_out, int32_t* __restrict__ status) {
     __shared__ OptShared S;
-    const int t = threadIdx.x;
+    const int lane = threadIdx.x;
     const int64_t b0 = begin[blockIdx.x], b1 = begin[blockIdx.x + 1];
     const int64_t nn = b1 - b0;
     if (b0 < 0 || b1 > n_tensors || nn < 0 || nn > kOptMaxN) {
-        if (t == 0) raise_status(status, MP_EINVAL);
+        if (lane == 0) raise_status(status, MP_EINVAL);
         return;
     }
     const int n = (int)nn;
-    if (t == 0) {
-        S.bad = 0;
-        S.winner = kOBlock;
-    }
-    __syncthreads();
+    int64_t s = 0;
     int32_t f = 0, l = 0;
-    if (t < n) {
-        const int64_t s = size[b0 + t];
-        f = first[b0 + t];
-        l = last[b0 + t];
-        if (s <= 0 || f < 0 || f > l || l >= num_ops[blockIdx.x]) atomicOr(&S.bad, 1);
-        S.sz[t] = s;
+    bool bad = false;
+    if (lane < n) {
+        s = size[b0 + lane];
+        f = first[b0 + lane];
+        l = last[b0 + lane];
+        bad = s <= 0 || f < 0 || f > l || l >= num_ops[blockIdx.x];
     }
-    __syncthreads();
-    if (S.bad) {
-        if (t == 0) raise_status(status, MP_EINVAL);
+    if (__ballot(bad)) {
+        if (lane == 0) raise_status(status, MP_EINVAL);
         return;
     }
-    // lifetimes that meet, and the live bytes at each tensor's first op (the
-    // most live bytes are reached at some tensor's first op)
-    __shared__ int32_t sf[kOptMaxN], sl[kOptMaxN];
-    if (t < n) {
-        sf[t] = f;
-        sl[t] = l;
+    const uint64_t total = wave_reduce((uint64_t)s, OpSatAdd());
+    if (total > (uint64_t)INT64_MAX) {
+        if (lane == 0) raise_status(status, MP_EOVERFLOW);
+        return;
     }
-    __syncthreads();
-    if (t == 0) {
-        uint64_t total = 0;
-        int64_t lb = 0;
-        for (int i = 0; i < n; ++i) {
-            total = sat_add(total, (uint64_t)S.sz[i]);
-            uint32_t m = 0;
-            int64_t live = 0;
-            for (int j = 0; j < n; ++j) {
-                if (j != i && sf[i] <= sl[j] && sf[j] <= sl[i]) m |= 1u << j;
-                if (sf[j] <= sf[i] && sf[i] <= sl[j]) live += S.sz[j];
-            }
-            S.meets[i] = m;
-            lb = max(lb, live);
-        }
-        if (total > (uint64_t)INT64_MAX) {
-            S.bad = 1;
-            raise_status(status, MP_EOVERFLOW);
-        }
-        S.best = total + 1;  // above any order's peak (at most the sum of sizes)
-        S.lb = lb;
-    }
-    __syncthreads();
-    if (S.bad) return;
     if (n == 0) {
-        if (t == 0) peak_out[blockIdx.x] = 0;
+        if (lane == 0) peak_out[blockIdx.x] = 0;
         return;
     }
-
-    // prefixes: the first d tensors of the order, at least 4 per thread when
-    // the trace is large enough
-    int d = 0;
-    int64_t n_pre = 1;
-    while (d < n && n_pre < 4 * kOBlock) n_pre *= n - d++;
-    unsigned long long mine = ~0ull;  // this thread's best peak
-    for (int64_t p = t; p < n_pre && (int64_t)S.best > S.lb; p += kOBlock) {
-        uint32_t placed = 0;
-        int64_t q = p, pk = 0;
-        bool cut = false;
-        for (int k = 0; k < d && !cut; ++k) {  // the p-th prefix, in mixed radix
-            const int r = n - k;
-            int digit = (int)(q % r);
-            q /= r;
-            uint32_t free_ids = ((1u << n) - 1u) & ~placed;
-            while (digit--) free_ids &= free_ids - 1;
-            const int c = __builtin_ctz(free_ids);
-            const int64_t x = opt_lowest_fit(S, c, placed, t);
-            S.off[c][t] = x;
-            S.order[k][t] = (uint8_t)c;
-            placed |= 1u << c;
-            pk = max(pk, x + S.sz[c]);
-            S.peak[k + 1][t] = pk;
-            cut = pk >= (int64_t)S.best;
-        }
-        if (cut) continue;
-        int k = d;
-        S.cand[k][t] = 0;
-        while (k >= d) {
-            if (k == n) {  // a complete order
-                const unsigned long long v = (unsigned long long)S.peak[n][t];
-                if (v < mine) {
-                    mine = v;
-                    for (int i = 0; i < n; ++i) S.best_order[i][t] = S.order[i][t];
-                    atomicMin(&S.best, v);
-                }
-                --k;
-                placed &= ~(1u << S.order[k][t]);
-                continue;
-            }
-            const uint32_t avail = ((1u << n) - 1u) & ~placed & ~((1u << S.cand[k][t]) - 1u);
-            if (!avail || (int64_t)S.best <= S.lb) {  // level done: back up
-                --k;
-                if (k >= d) placed &= ~(1u << S.order[k][t]);
-                continue;
-            }
-            const int c = __builtin_ctz(avail);
-            S.cand[k][t] = (uint8_t)(c + 1);
-            const int64_t x = opt_lowest_fit(S, c, placed, t);
-            const int64_t nk = max(S.peak[k][t], x + S.sz[c]);
-            if (nk >= (int64_t)S.best) continue;
-            S.off[c][t] = x;
-            S.order[k][t] = (uint8_t)c;
-            placed |= 1u << c;
-            S.peak[k + 1][t] = nk;
-            ++k;
-            S.cand[k][t] = 0;
-        }
+    // ranks, lifetimes that meet, and the live bytes at each tensor's first op
+    // (the most live bytes are reached at some tensor's first op)
+    int rank = 0;
+    for (int j = 0; j < n; ++j) {
+        const int64_t sj = __shfl(s, j, kWave);
+        rank += (sj > s || (sj == s && j < lane)) ? 1 : 0;
+    }
+    if (lane < n) {
+        S.sz[rank] = s;
+        S.first[rank] = f;
+        S.last[rank] = l;
+        S.id[rank] = lane;
     }
     __syncthreads();
-    if (mine == S.best) atomicMin(&S.winner, t);
-    __syncthreads();
-    if (t == S.winner) {  // one optimal plan: the winner's best order, placed again
-        uint32_t placed = 0;
-        for (int k = 0; k < n; ++k) {
-            const int c = S.best_order[k][t];
-            const int64_t x = opt_lowest_fit(S, c, placed, t);
-            S.off[c][t] = x;
-            placed |= 1u << c;
-            offset_out[b0 + c] = x;
+    uint64_t live = 0;
+    if (lane < n) {
+        uint32_t meets = 0, alive = 0;
+        for (int j = 0; j < n; ++j) {
+            if (j != lane && S.first[lane] <= S.last[j] && S.first[j] <= S.last[lane])
+                meets |= 1u << j;
+            if (S.first[j] <= S.first[lane] && S.first[lane] <= S.last[j]) {
+                alive |= 1u << j;
+                live += (uint64_t)S.sz[j];
+            }
         }
-        peak_out[blockIdx.x] = (int64_t)S.best;
+        S.meets[lane] = meets;
+        S.alive[lane] = alive;
     }
+    const uint64_t lb = wave_reduce(live, OpMax<uint64_t>());
+    const uint64_t orv = wave_reduce((uint64_t)s, OpOr<uint64_t>());
+    __syncthreads();
+    const int sh = __builtin_ctzll(orv);
+    // 32-bit counts of the common unit while two sums of the sizes fit them
+    if ((total >> sh) < (1ull << 31))
+        opt_plan<uint32_t>(S, n, sh, lb, b0, offset_out, peak_out + blockIdx.x);
+    else
+        opt_plan<uint64_t>(S, n, sh, lb, b0, offset_out, peak_out + blockIdx.x);
 }
 
 }  // namespace
@@ -384,7 +528,7 @@ hipError_t launch_optimal(const int64_t* begin, int64_t n_traces, const int32_t*
                           int64_t n_tensors, int64_t* offset_out, int64_t* peak_out,
                           int32_t* status, hipStream_t st) {
     if (n_traces == 0) return hipSuccess;
-    hipLaunchKernelGGL(optimal_kernel, dim3((unsigned)n_traces), dim3(kOBlock), 0, st, begin,
+    hipLaunchKernelGGL(optimal_kernel, dim3((unsigned)n_traces), dim3(kWave), 0, st, begin,
                        num_ops, size, first, last, n_tensors, offset_out, peak_out, status);
     return hipGetLastError();
 }

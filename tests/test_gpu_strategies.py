@@ -186,6 +186,29 @@ def test_optimal_tiny_batch_workload():
     _check_optimal(b, o, p, traces, expected)
 
 
+@pytest.mark.parametrize("kind", ["ties", "wide", "dense", "prefix"])
+def test_optimal_search_forms(kind):
+    """Equal sizes (canonical order by tensor), 64-bit unit counts, many meeting
+    lifetimes, and the lengths around the search's prefix depths (1-3)."""
+    binding = need_gpu()
+    rng = np.random.default_rng(99)
+    print(f"case optimal search: {kind}", flush=True)
+    traces = []
+    for k in range(120):
+        n = int(rng.integers(1, 4)) if kind == "prefix" else int(rng.integers(5, 9))
+        span = 8 if kind == "dense" else 4
+        t = tg.random_trace(rng, n, 8, max_len=span, unit=1, sorted_first=bool(k % 2),
+                            sizes=[64, 128, 192] if kind == "ties" else None)
+        if kind == "wide":
+            t.size[:] = rng.integers(2 ** 30, 2 ** 40, n) | 1
+        traces.append(t)
+    b, o, p = _optimal(binding, traces)
+    expected = [oracle.optimal_plan(t.size, t.first, t.last, t.num_ops)[1] for t in traces]
+    _check_optimal(b, o, p, traces, expected)
+    again = _optimal(binding, traces)[1]
+    assert np.array_equal(o, again)  # one wave a trace: the same plan every time
+
+
 # ---------------------------------------------------------------------------
 # Greedy by Breadth: offsets and peaks bit-exact against the oracle
 
