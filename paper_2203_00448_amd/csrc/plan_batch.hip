@@ -81,7 +81,9 @@ constexpr uint32_t kBestMaxK = (uint32_t)kWave * kBestSlots;  // BEST_FIT on the
 
 // Ready classes by neighbour count K: the lanes a tensor is fitted by.
 // 0: K <= 8, one lane; 1: K <= 16, two; 2: K <= 32, four; 3: K <= 64,
-// eight; 4: more, the whole wave (under BEST_FIT every K > 8).
+// eight; 4: more, the whole wave.  Under BEST_FIT 0: one lane; 1: K <= 16, a
+// row of 16 lanes; 3: K <= 64, the whole wave, a neighbour a lane; 4: more,
+// the whole wave, four a lane.
 constexpr int kClasses = 5;
 constexpr int kWideClass = 4;
 
@@ -110,7 +112,7 @@ constexpr uint32_t kMaxDist = kLongBase - 1;
 
 __device__ __forceinline__ uint32_t ready_class(uint32_t K, bool best) {
     if (K <= 8) return 0u;
-    if (best) return (uint32_t)kWideClass;
+    if (best) return K <= 16 ? 1u : (K <= 64 ? 3u : (uint32_t)kWideClass);
     return K <= 16 ? 1u : (K <= 32 ? 2u : (K <= 64 ? 3u : (uint32_t)kWideClass));
 }
 
@@ -415,6 +417,64 @@ __device__ uint32_t best_fit_group(uint32_t (&o)[kBestSlots], uint32_t (&e)[kBes
         best = other < best ? other : best;
     }
     return best != ~0ull ? (uint32_t)best : top;
+}
+
+// BEST_FIT with one neighbour a lane, for a row of 16 lanes (K <= 16) or the
+// whole wave (K <= 64, all lanes): a free gap starts at 0 or at the end of a
+// range that no range covers, so lane l takes the end of its own range as a
+// gap start and looks at every range in turn -- the row's by DPP rotation, the
+// wave's by readlane -- for one that covers it and for the nearest start at or
+// above it.  About six instructions a neighbour against the 36 exchange stages
+// of the 256-range sort that every tensor with more than 8 neighbours took
+// (600 ragged traces of up to 4096 tensors: 1.54 -> 0.42 ms).
+// Differences are taken modulo 2^32: offsets and ends stay below 2^31 units,
+// so a difference at or above 2^31 is negative.  An unplaced neighbour or an
+// empty slot has size 0 (covers nothing) and no start.
+struct BestScan {
+    uint32_t c;        // this lane's gap start
+    uint32_t nxt;      // distance to the nearest start at or above it
+    uint32_t covered;  // nonzero: inside some range
+};
+__device__ __forceinline__ void best_scan(BestScan& b, uint32_t oj, uint32_t sj) {
+    const uint32_t t = oj - b.c;
+    b.nxt = min(b.nxt, t);
+    // oj <= c < oj + sj, from the same difference.  Not written c - oj < sj:
+    // the compiler folds a DPP rotation of oj into v_subrev_u32_dpp, which on
+    // gfx950 rotates c instead (measured)
+    b.covered |= t + (sj - 1u) < sj ? 1u : 0u;
+}
+template <int I>
+__device__ __forceinline__ void best_scan_row(BestScan& b, uint32_t o, uint32_t sz) {
+    if constexpr (I < 16) {
+        best_scan(b, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)o, 0x120 + I, 0xF, 0xF, false),
+                  (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sz, 0x120 + I, 0xF, 0xF, false));
+        best_scan_row<I + 1>(b, o, sz);
+    }
+}
+// o: offset or a value at or above 2^31; e: end of a placed range; s: units.
+// K: neighbours (whole wave only, uniform).  All 64 lanes must be active.
+template <bool ROW>
+__device__ __forceinline__ uint32_t best_fit_lanes(uint32_t o, uint32_t e, uint32_t s, uint32_t K) {
+    auto lanes_max = [](uint32_t v) { return ROW ? group_max_u32(v, 16u) : wave_max_u32(v); };
+    auto lanes_min = [&](uint32_t v) { return ~lanes_max(~v); };
+    const bool placed = o < kUnplacedBit;
+    const uint32_t oo = placed ? o : 0xFFFFFFFFu, sz = placed ? e - o : 0u;
+    BestScan b{placed ? e : 0u, oo - (placed ? e : 0u), 0u};
+    if constexpr (ROW) {
+        best_scan_row<1>(b, oo, sz);
+    } else {
+        for (uint32_t j = 0; j < K; ++j)
+            best_scan(b, (uint32_t)__builtin_amdgcn_readlane((int)oo, (int)j),
+                      (uint32_t)__builtin_amdgcn_readlane((int)sz, (int)j));
+    }
+    const bool fits = placed && !b.covered && b.nxt < kUnplacedBit && b.nxt >= s;
+    const uint32_t gap = fits ? b.nxt : 0xFFFFFFFFu;
+    const uint32_t g = lanes_min(gap);
+    const uint32_t low = lanes_min(oo);  // the gap [0, low)
+    const uint32_t x = lanes_min(gap == g ? b.c : 0xFFFFFFFFu);
+    const uint32_t top = lanes_max(placed ? e : 0u);
+    if (low < kUnplacedBit && low >= s && low <= g) return 0u;
+    return g != 0xFFFFFFFFu ? x : top;
 }
 
 // A tensor being fitted by a lane group: its position, size, left-list start,
@@ -912,7 +972,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     unsigned char* __restrict__ ws, int64_t* __restrict__ offset_out,
     int64_t* __restrict__ peak_out, int64_t* __restrict__ lb_out, int32_t* __restrict__ status) {
     const uint64_t t_start = wall_clock64();
-    constexpr bool best = BEST;  // BEST_FIT: one lane up to 8 neighbours, else the whole wave
+    constexpr bool best = BEST;
     extern __shared__ __align__(16) unsigned char smem[];
     // static LDS: at most kStaticLds bytes (checked at launch), or four
     // workgroups of a 2000-tensor trace no longer fit a CU
@@ -1430,7 +1490,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     // maximum over its lanes until no lane moves.  Then the word is published and the successors'
     // pending counts decremented; those reaching zero are appended for the
     // next round.  Tensors with more than 64 neighbours (under BEST_FIT, more
-    // than 8) take a whole wave each, dealt over the waves.  Waves with no
+    // than 16) take a whole wave each, dealt over the waves.  Waves with no
     // lane in the round go straight to its barrier.  Per-round append
     // counters rotate over three slots so that one barrier per round
     // suffices.
@@ -1486,7 +1546,9 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
             auto run = [&](auto slots_tag) {
                 constexpr int S = decltype(slots_tag)::value;
                 constexpr uint32_t M = 8u / S;
-                const uint32_t a3 = 8u * M * n3, a2 = a3 + 4u * M * n2, a1 = a2 + 2u * M * n1;
+                // (BEST_FIT: class 0 only, the others below)
+                const uint32_t a3 = best ? 0u : 8u * M * n3, a2 = best ? 0u : a3 + 4u * M * n2;
+                const uint32_t a1 = best ? 0u : a2 + 2u * M * n1;
                 const uint32_t tot = a1 + M * n0;
                 for (uint32_t pass = 0; pass < tot; pass += BLOCK) {
                     if (pass + wbase >= tot) break;  // wave-uniform: nothing for this wave
@@ -1539,6 +1601,31 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
             const uint32_t t8 = n0 + 2u * n1 + 4u * n2 + 8u * n3;  // lanes at eight slots
             if (best || 2u * t8 > (uint32_t)BLOCK) run(std::integral_constant<int, 8>{});
             else run(std::integral_constant<int, 4>{});
+            if constexpr (best) {
+                // a row of 16 lanes each, then the whole wave each
+                constexpr uint32_t kRows = kWave / 16;
+                for (uint32_t i0 = bgn[1] + kRows * (wbase / kWave); i0 < end[1];
+                     i0 += kRows * (BLOCK / kWave)) {
+                    const uint32_t i = i0 + ((uint32_t)lane >> 4);
+                    const bool has = i < end[1];
+                    const Item it = load_item(has ? readyq[region[1] + i] : 0u, has, spare, ofsz,
+                                              lbeg, rlen);
+                    uint32_t o[1], e[1];
+                    gather<1, LONG>(it, (uint32_t)lane & 15u, ofsz, ll, o, e);
+                    const uint32_t x = best_fit_lanes<true>(o[0], e[0], it.s, 0u);
+                    if (has && (lane & 15) == 0) ofsz[it.q] = ((uint64_t)x << 32) | it.s;
+                    release<1>(o, ofsz, rl, lane);
+                }
+                for (uint32_t i0 = bgn[3] + (wbase / kWave); i0 < end[3]; i0 += BLOCK / kWave) {
+                    const Item it = load_item(readyq[region[3] + i0], true, spare, ofsz, lbeg, rlen);
+                    uint32_t o[1], e[1];
+                    gather<1, LONG>(it, (uint32_t)lane, ofsz, ll, o, e);
+                    const uint32_t x = best_fit_lanes<false>(
+                        o[0], e[0], it.s, (uint32_t)__builtin_amdgcn_readfirstlane((int)it.K));
+                    if (lane == 0) ofsz[it.q] = ((uint64_t)x << 32) | it.s;
+                    release<1>(o, ofsz, rl, lane);
+                }
+            }
             // more neighbours than eight lanes hold: the whole wave each, dealt
             // over the waves
             for (uint32_t i0 = bgn[4] + (wbase / kWave); i0 < end[4]; i0 += BLOCK / kWave) {

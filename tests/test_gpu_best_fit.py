@@ -141,3 +141,29 @@ def test_decode100k_single_trace():
     bad = np.nonzero(host(o) != eo)[0]
     assert bad.size == 0, f"{bad.size} offsets differ, first at {bad[:5]}"
     assert int(p.item()) == ep
+
+
+@pytest.mark.parametrize("K", [7, 8, 9, 15, 16, 17, 31, 32, 63, 64, 65, 255, 256])
+def test_batch_neighbour_counts(K):
+    """Traces whose tensors meet K others (and, at the ends, fewer), around the
+    counts at which the batched planner changes the lanes a tensor is fitted
+    by; sizes of few values (equal gaps and equal ends) and of many, in order
+    and shuffled."""
+    binding = need_gpu()
+    rng = np.random.default_rng(700 + K)
+    traces = []
+    for sizes in ([64, 128, 192, 320], None):
+        for shuffle in (False, True):
+            n = 2 * K + 40
+            first = np.arange(n, dtype=np.int32)
+            left = K // 2  # a constant lifetime: K // 2 or so before, the rest after
+            last = np.minimum(first + left + (first % 2) * (K % 2), n - 1).astype(np.int32)
+            size = (np.asarray(sizes, np.int64)[rng.integers(0, 4, n)] if sizes
+                    else 64 * rng.integers(1, 400, n))
+            if K > 32:  # one tensor meeting exactly K others, among a few short ones
+                last = first.copy()
+                last[0] = K
+            p = rng.permutation(n) if shuffle else np.arange(n)
+            traces.append(tg.Trace(size[p], first[p], last[p], n))
+    print(f"case BEST_FIT, {K} neighbours", flush=True)
+    _check_batch(binding, tg.concat(traces), max_trace_len=600)
