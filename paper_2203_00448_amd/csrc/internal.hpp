@@ -75,6 +75,14 @@ hipError_t launch_breadth_lds(const int64_t* begin, int64_t n_traces, const int3
                               int64_t n_tensors, int32_t policy, int64_t* offset_out,
                               int64_t* peak_out, int32_t* status, hipStream_t st);
 
+// one trace of up to MP_BATCH_MAX_TRACE_LEN tensors on the batched planner's LDS
+// path (plan_batch.hip); *planned (device) is 0 when the path cannot hold it.
+// `ws`: 24 n + 128 bytes.
+hipError_t launch_plan_one(const int64_t* size, const int32_t* first, const int32_t* last,
+                           int64_t n, int32_t num_ops, int32_t policy, int64_t* offset_out,
+                           int64_t* peak_out, void* ws, uint32_t* planned, int32_t* status,
+                           hipStream_t st);
+
 // device-wide prefix sums (scan.hip)
 size_t scan_workspace_bytes(int64_t n);
 hipError_t device_scan_i64(int64_t* data, int64_t n, bool inclusive, int64_t* partial,

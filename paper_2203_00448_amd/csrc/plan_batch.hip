@@ -31,6 +31,7 @@
 // planned by the same workgroup on the general path (plan_general): the
 // greedy taken literally, one tensor at a time in rank order, 64-bit offsets,
 // its working lists in the workspace.  No valid trace is refused.
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -964,13 +965,23 @@ __device__ __forceinline__ void breadth_ranks(
 // no workspace: an unsorted trace's permutation sits in its own offset_out
 // until the outputs are written, and a trace that the LDS path cannot hold is
 // left to breadth_kernel, marked by a peak of -1.
-template <int BLOCK, int ITEMS, bool BEST, bool BREADTH>
+// ONE: a single trace of n_tensors tensors and one_ops ops (begin and num_ops
+// are null); *planned is 0 when the LDS path cannot hold it, else 1.
+// A trace of more than kOnePairs pairs a tensor is left too: its rounds are many
+// and hold a few tensors with long neighbour lists each, where the single-trace
+// planner's waits are shorter (500 decode-like tensors, 40 pairs each: 2.5 ms
+// here, 0.31 ms there; ResNeXt-like ones have 5).
+constexpr uint32_t kOnePairs = 12;
+enum BatchMode { kBatch, kBreadthBatch, kOneTrace };
+template <int BLOCK, int ITEMS, bool BEST, BatchMode MODE>
 __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_batch_kernel(
     const int64_t* __restrict__ begin, const int32_t* __restrict__ num_ops,
     const int64_t* __restrict__ size, const int32_t* __restrict__ first,
     const int32_t* __restrict__ last, int64_t n_tensors, int32_t cap_n, int32_t cap_lists,
     unsigned char* __restrict__ ws, int64_t* __restrict__ offset_out,
-    int64_t* __restrict__ peak_out, int64_t* __restrict__ lb_out, int32_t* __restrict__ status) {
+    int64_t* __restrict__ peak_out, int64_t* __restrict__ lb_out, int32_t* __restrict__ status,
+    int32_t one_ops, uint32_t* __restrict__ planned) {
+    constexpr bool BREADTH = MODE == kBreadthBatch, ONE = MODE == kOneTrace;
     const uint64_t t_start = wall_clock64();
     constexpr bool best = BEST;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1014,8 +1025,9 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
         ncls64 = seeds64 = 0;
         nlong = 0;
     }
-    const int64_t lo = begin[b], hi = begin[b + 1];
-    const int32_t n_ops = num_ops[b];
+    const int64_t lo = ONE ? 0 : begin[b], hi = ONE ? n_tensors : begin[b + 1];
+    const int32_t n_ops = ONE ? one_ops : num_ops[b];
+    if (ONE && tid == 0) *planned = 1u;  // done, or rejected: taken back below if left
     if (lo < 0 || hi < lo || hi > n_tensors || (!BREADTH && n_ops < 0) || hi - lo > cap_n) {
         if (tid == 0) raise_status(status, MP_EINVAL);
         return;
@@ -1304,10 +1316,15 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
                 kmax = max(kmax, red32[2][w]);
             }
         }
-        general = n_pairs > (uint32_t)cap_lists || (best && kmax > kBestMaxK);
+        general = n_pairs > (uint32_t)cap_lists || (best && kmax > kBestMaxK) ||
+                  (ONE && n_pairs > kOnePairs * (uint32_t)n);
     }
     if (BREADTH && general) {
         if (tid == 0) peak_out[b] = -1;  // breadth_kernel takes this trace
+        return;
+    }
+    if (ONE && general) {
+        if (tid == 0) *planned = 0u;
         return;
     }
     if (general) {
@@ -1689,9 +1706,10 @@ __global__ void reset_status_kernel(int32_t* status) { *status = MP_OK; }
 // is dynamic).
 constexpr size_t kStaticLds = 512;
 
-template <int BLOCK, int ITEMS, bool BEST, bool BREADTH = false>
-hipError_t launch_items(const BatchArgs& a, const BatchShape& s, hipStream_t st) {
-    auto kern = plan_batch_kernel<BLOCK, ITEMS, BEST, BREADTH>;
+template <int BLOCK, int ITEMS, bool BEST, BatchMode MODE = kBatch>
+hipError_t launch_items(const BatchArgs& a, const BatchShape& s, hipStream_t st,
+                        int32_t one_ops = 0, uint32_t* planned = nullptr) {
+    auto kern = plan_batch_kernel<BLOCK, ITEMS, BEST, MODE>;
     hipFuncAttributes fa{};
     hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
     if (e != hipSuccess) return e;
@@ -1702,7 +1720,7 @@ hipError_t launch_items(const BatchArgs& a, const BatchShape& s, hipStream_t st)
     hipLaunchKernelGGL(kern, dim3((unsigned)a.n_traces), dim3(BLOCK), s.lds_bytes, st,
                        a.begin, a.num_ops, a.size, a.first, a.last, a.n_tensors, s.cap_n,
                        s.cap_pairs, static_cast<unsigned char*>(a.workspace), a.offset_out,
-                       a.peak_out, a.lb_out, a.status);
+                       a.peak_out, a.lb_out, a.status, one_ops, planned);
     return hipGetLastError();
 }
 
@@ -1810,10 +1828,37 @@ hipError_t launch_breadth_lds(const int64_t* begin, int64_t n_traces, const int3
                       offset_out, peak_out, nullptr, status, nullptr, policy};
     constexpr int B = kBatchBlock;
     if (few)
-        return best ? launch_items<B, 2, true, true>(a, s, st)
-                    : launch_items<B, 2, false, true>(a, s, st);
-    return best ? launch_items<B, 8, true, true>(a, s, st)
-                : launch_items<B, 8, false, true>(a, s, st);
+        return best ? launch_items<B, 2, true, kBreadthBatch>(a, s, st)
+                    : launch_items<B, 2, false, kBreadthBatch>(a, s, st);
+    return best ? launch_items<B, 8, true, kBreadthBatch>(a, s, st)
+                : launch_items<B, 8, false, kBreadthBatch>(a, s, st);
+}
+
+// A single trace: alone on its CU, so with all of its LDS for the pairs (up to
+// 65,520 of them) and, beyond 512 tensors, 512 threads (2000 tensors: 68 us,
+// with the batch's 256 86 us).
+hipError_t launch_plan_one(const int64_t* size, const int32_t* first, const int32_t* last,
+                           int64_t n, int32_t num_ops, int32_t policy, int64_t* offset_out,
+                           int64_t* peak_out, void* ws, uint32_t* planned, int32_t* status,
+                           hipStream_t st) {
+    if (n < 1 || n > MP_BATCH_MAX_TRACE_LEN) return hipErrorInvalidValue;
+    constexpr int B = kBatchBlock, BL = kBatchBlockLong;
+    BatchShape s{};
+    s.cap_n = n <= 2 * B ? 2 * B : (n <= 4 * BL ? 4 * BL : 8 * BL);
+    const size_t base = batch_lds((size_t)s.cap_n, 0).total + kStaticLds;
+    s.cap_pairs = (int32_t)std::min<size_t>((163840 - base) & ~(size_t)15, 65520);
+    s.lds_bytes = batch_lds((size_t)s.cap_n, (size_t)s.cap_pairs).total;
+    const BatchArgs a{nullptr, 1, nullptr, size, first, last, n, s.cap_n,
+                      offset_out, peak_out, nullptr, status, ws, policy};
+    const bool best = policy == MP_BEST_FIT;
+    if (s.cap_n == 2 * B)
+        return best ? launch_items<B, 2, true, kOneTrace>(a, s, st, num_ops, planned)
+                    : launch_items<B, 2, false, kOneTrace>(a, s, st, num_ops, planned);
+    if (s.cap_n == 4 * BL)
+        return best ? launch_items<BL, 4, true, kOneTrace>(a, s, st, num_ops, planned)
+                    : launch_items<BL, 4, false, kOneTrace>(a, s, st, num_ops, planned);
+    return best ? launch_items<BL, 8, true, kOneTrace>(a, s, st, num_ops, planned)
+                : launch_items<BL, 8, false, kOneTrace>(a, s, st, num_ops, planned);
 }
 
 }  // namespace mp

@@ -14,19 +14,24 @@
 //              chosen from a histogram of band lengths, so that the other
 //              tensors meeting t from behind lie in a short window before t
 //   rank       stable radix sort by size descending over positions
-//   place      persistent kernel: workgroups take ranks in blocks of 32
-//              consecutive ranks claimed per XCD, so that most dependency
-//              links (usually rank r - 1 to rank r) stay inside one L2.  For
-//              tensor t the workgroup walks t's candidates (forward band,
-//              backward window, long list), keeps those ranked before t,
-//              turns the already placed ones into one run of ranges by
+//   place      persistent kernel.  Lowest fit: one workgroup places every
+//              tensor, the others prepare them in rank order ahead of it.  To
+//              prepare tensor t a workgroup walks t's candidates (forward
+//              band, backward window, long list), keeps those ranked before
+//              t, turns the already placed ones into one run of ranges by
 //              offset (their union through a coverage bitmap, or an LDS
-//              bitonic sort with prefix maxima of the ends), marks the run's
-//              gaps that hold t, then waits for the rest while keeping the
-//              lowest fit up to date as they arrive.  A tensor only waits on
-//              lower ranks; each is held by a running workgroup or sits in a
-//              block whose XCD takes it once a running workgroup there
-//              finishes, so the schedule cannot deadlock.
+//              bitonic sort with prefix maxima of the ends) and hands over the
+//              run's gaps that hold t and the ranks still to be placed.  The
+//              placing workgroup's waves take the tensors in rank order and
+//              keep each one's lowest fit up to date while the late ranks
+//              arrive, in its own LDS.  A preparation waits for nothing but
+//              the placement to come within a window of ranks.
+//              BEST_FIT: every workgroup takes a rank, waits for its
+//              predecessors and fits it; ranks are taken in blocks of 32 per
+//              XCD, so that most links (usually rank r - 1 to rank r) stay
+//              inside one L2.  Either way a tensor only waits on lower ranks,
+//              each held by a running workgroup or taken once one finishes,
+//              so the schedule cannot deadlock.
 //   output     offsets (scaled back to bytes) and the peak.
 #include <type_traits>
 #ifdef MP_DEBUG_WAIT
@@ -41,15 +46,33 @@ namespace mp {
 
 namespace {
 
-constexpr int kTBlock = 512;
+constexpr int kTBlock = 512;      // BEST_FIT and the 64-bit path
+constexpr int kChainBlock = 1024; // lowest fit: 16 placing waves
 constexpr int kRunCap = 16384;    // ranges sorted at once in LDS
-// Predecessors still unplaced when t is examined.  Each is held by another
-// running workgroup (one rank at a time per workgroup) or is still untaken in
-// another XCD's current block (see kTicketBlock), so there are fewer than the
-// grid + kXcdGroups * (kTicketBlock - 1); the host keeps the grid at most
-// kDynCap + 1 - kXcdGroups * (kTicketBlock - 1).
+// Predecessors still unplaced when t is examined (late).  Lowest fit: a
+// preparation starts at most kAhead ranks ahead of the front (every rank below
+// the front is placed), so there are fewer than kAhead.  BEST_FIT: each is held
+// by another running workgroup (one rank at a time per workgroup) or is still
+// untaken in another XCD's current block (see kTicketBlock), so there are fewer
+// than the grid + kXcdGroups * (kTicketBlock - 1); the host keeps the grid at
+// most 513 - kXcdGroups * (kTicketBlock - 1).
 constexpr int kDynCap = 512;
-static_assert(kDynCap <= 8 * kWave, "wave 0 holds every late predecessor, 8 a lane at most");
+// (kAhead 64 / 128 / 256 / 512 with the decode-like and the ranking-like trace:
+// 62.9 / 42.1 / 33.9 / 33.3 and 664 / 535 / 605 / 765 ms: too near a front
+// leaves the long preparations late, too far makes the lists of late ranks long.)
+constexpr uint32_t kAhead = 256;
+static_assert(kAhead <= (uint32_t)kDynCap && kDynCap <= 8 * kWave,
+              "a wave holds every late predecessor, 8 a lane at most");
+// The placing workgroup's LDS ring of placed ranks: a wave starts rank v only
+// while every rank in hand is above v - (kRing - kAhead), so a late rank (less
+// than kAhead below its tensor's) is never overwritten while it is waited for.
+constexpr uint32_t kRing = 2048;
+constexpr uint32_t kHands = kAhead;  // hand-overs in flight, slot rank % kHands
+constexpr uint32_t kGapCap = 4096;   // gaps a hand-over holds (512: 28,000 of the 10^6 ranking-like
+                                     // tensors had more and were left to their preparers, 905 ms)
+constexpr uint32_t kByPreparer = 0x80000000u;  // hand-over: the preparer placed the tensor
+static_assert((kRing & (kRing - 1)) == 0 && (kHands & (kHands - 1)) == 0 && kRing >= 2 * kAhead,
+              "rings indexed by the rank's low bits");
 // Ranks are handed out in blocks of kTicketBlock consecutive ranks: a
 // workgroup takes the next slot of its XCD's current block, and the one that
 // opens a block claims the next block of the whole trace.  A rank below t's
@@ -67,6 +90,8 @@ constexpr uint64_t kUnplaced64 = ~0ull;
 
 struct TFlags {
     uint32_t unsorted, sorted, abort, wide;
+    uint32_t planned;  // a short trace is done (the batched planner's kernel took it)
+    uint32_t pad;
     uint64_t or_all, sum;
     uint32_t shift, lthr, n_long, ticket;
     uint32_t xtick[kXcdGroups];  // slots taken per XCD (blocks of kTicketBlock ranks)
@@ -76,6 +101,11 @@ struct TFlags {
     uint32_t done_ingest, done_reach, done_output;
     uint32_t skip_narrow, skip_wide;  // nonzero: the 32-bit (64-bit) unit path does not run
     uint32_t pool[kPoolSlots];        // 1 while a workgroup holds the slot
+    uint32_t roles;                   // lowest fit: workgroups started (the first one places)
+    uint32_t stop;                    // lowest fit: a wait found no end (reported, never expected)
+    uint32_t chain;                   // lowest fit: one workgroup places (else each its own ranks)
+    uint32_t depth, meets, done_depth;  // its measures, summed over the sampled windows
+    alignas(64) uint32_t front;       // lowest fit: every rank below is placed and visible
     uint32_t hist[64];      // band lengths by bit width
     uint64_t peak;
     int64_t long_prefix_tiles;
@@ -89,7 +119,7 @@ struct TView {  // position-ordered arrays
 
 // ---------------------------------------------------------------- ingest
 
-__global__ void t_init_kernel(TFlags* fl) {
+__device__ __forceinline__ void init_flags(TFlags* fl) {
     const int i = threadIdx.x;
     if (i < 64) fl->hist[i] = 0;
     if (i < kPoolSlots) fl->pool[i] = 0;
@@ -111,8 +141,23 @@ __global__ void t_init_kernel(TFlags* fl) {
         fl->done_ingest = 0;
         fl->done_reach = 0;
         fl->done_output = 0;
+        fl->roles = 0;
+        fl->stop = 0;
+        fl->chain = 0;
+        fl->depth = 0;
+        fl->meets = 0;
+        fl->done_depth = 0;
+        fl->front = 0;
         fl->peak = 0;
+        fl->planned = 0;
     }
+}
+__global__ void t_init_kernel(TFlags* fl) { init_flags(fl); }
+
+// A value that is the same in every lane, moved to a scalar register (branches
+// on it are scalar branches).
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 __device__ __forceinline__ uint32_t flag_load(const uint32_t* p) {
@@ -147,7 +192,8 @@ __global__ __launch_bounds__(256) void t_ingest_kernel(const int64_t* __restrict
                                                        int32_t* __restrict__ status,
                                                        uint64_t* __restrict__ keys,
                                                        uint32_t* __restrict__ vals,
-                                                       uint32_t* __restrict__ xbase, int64_t nx) {
+                                                       uint32_t* __restrict__ xbase, int64_t nx,
+                                                       uint64_t* __restrict__ heads) {
     __shared__ uint64_t red[256 / kWave];
     __shared__ uint32_t s_last;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -167,6 +213,8 @@ __global__ __launch_bounds__(256) void t_ingest_kernel(const int64_t* __restrict
     }
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nx; i += stride)
         xbase[i] = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < kHands; i += stride)
+        heads[i] = 0;
     bad = block_reduce<256>(bad, OpOr<uint32_t>(), reinterpret_cast<uint32_t*>(red));
     unsorted = block_reduce<256>(unsorted, OpOr<uint32_t>(), reinterpret_cast<uint32_t*>(red));
     orv = block_reduce<256>(orv, OpOr<uint64_t>(), red);
@@ -322,6 +370,132 @@ __global__ void t_long_list_kernel(const int32_t* __restrict__ reach,
     }
 }
 
+// ---- traces of up to MP_BATCH_MAX_TRACE_LEN tensors that the batched
+// planner's kernel could not hold (dense ones, or 64-bit unit counts): every
+// step above in one workgroup, one launch for eleven.  Sorted in LDS.
+constexpr int kSmallN = MP_BATCH_MAX_TRACE_LEN;
+constexpr int kSmallBlock = 1024;
+
+// Ascending by (key, idx), P a power of two (bitonic); PACKED: by the key alone,
+// which holds the index in its low 12 bits (25 against 41 us for 4096).
+template <bool PACKED>
+__device__ __forceinline__ void small_sort(uint64_t* key, uint16_t* idx, int P) {
+    for (int k = 2; k <= P; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = threadIdx.x; t < P / 2; t += kSmallBlock) {
+                const int a = 2 * t - (t & (j - 1)), b = a + j;
+                const uint64_t ka = key[a], kb = key[b];
+                const uint16_t ia = PACKED ? 0 : idx[a], ib = PACKED ? 0 : idx[b];
+                const bool gt = ka > kb || (!PACKED && ka == kb && ia > ib);
+                if (gt == ((a & k) == 0)) {
+                    key[a] = kb;
+                    key[b] = ka;
+                    if (!PACKED) {
+                        idx[a] = ib;
+                        idx[b] = ia;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSmallBlock) void t_small_kernel(
+    const int64_t* __restrict__ size, const int32_t* __restrict__ first,
+    const int32_t* __restrict__ last, int n, int32_t num_ops, TFlags* fl,
+    int32_t* __restrict__ status, uint32_t* __restrict__ su, uint64_t* __restrict__ su64,
+    uint32_t* __restrict__ off, uint64_t* __restrict__ off64, uint32_t* __restrict__ pid,
+    int32_t* __restrict__ reach, uint32_t* __restrict__ order, int32_t* __restrict__ long_list,
+    uint32_t* __restrict__ xbase, int64_t nx) {
+    __shared__ uint64_t key[kSmallN];
+    __shared__ uint16_t idx[kSmallN];
+    __shared__ int32_t fst[kSmallN];
+    __shared__ uint64_t red[kSmallBlock / kWave];
+    __shared__ uint32_t n_long;
+    if (fl->planned) return;
+    const int tid = threadIdx.x;
+    __syncthreads();
+    init_flags(fl);
+    if (tid == 0) n_long = 0;
+    for (int64_t i = tid; i < nx; i += kSmallBlock) xbase[i] = 0;
+    uint64_t bits = 0, orv = 0, acc = 0;  // bits: 1 invalid, 2 not sorted by first
+    for (int i = tid; i < n; i += kSmallBlock) {
+        const int64_t s = size[i];
+        const int32_t f = first[i], l = last[i];
+        if (s <= 0 || f < 0 || f > l || l >= num_ops) bits |= 1;
+        if (i + 1 < n && first[i + 1] < f) bits |= 2;
+        if (s > 0) {
+            orv |= (uint64_t)s;
+            acc = sat_add(acc, (uint64_t)s);
+        }
+        fst[i] = f;
+    }
+    bits = block_reduce<kSmallBlock>(bits, OpOr<uint64_t>(), red);
+    orv = block_reduce<kSmallBlock>(orv, OpOr<uint64_t>(), red);
+    acc = block_reduce<kSmallBlock>(acc, OpSatAdd(), red);
+    const bool over = acc > (uint64_t)INT64_MAX;
+    if ((bits & 1) || over) {
+        if (tid == 0) {
+            if (bits & 1) raise_status(status, MP_EINVAL);
+            if (over) raise_status(status, MP_EOVERFLOW);
+            fl->abort = 1;
+        }
+        return;
+    }
+    const int sh = __builtin_ctzll(orv);
+    const bool wide = (acc >> sh) > 0xFFFFFFFEull;
+    int P = 2;
+    while (P < n) P <<= 1;
+    // positions: (first, id)
+    if (bits & 2) {
+        for (int i = tid; i < P; i += kSmallBlock)
+            key[i] = i < n ? ((uint64_t)(uint32_t)fst[i] << 12) | (uint32_t)i : ~0ull;
+        __syncthreads();
+        small_sort<true>(key, idx, P);
+        for (int q = tid; q < n; q += kSmallBlock) {
+            fst[q] = (int32_t)(key[q] >> 12);
+            idx[q] = (uint16_t)(key[q] & 0xFFFu);
+        }
+        __syncthreads();
+    }
+    // sizes, reaches and long tensors by position, and the rank keys
+    uint64_t un[kSmallN / kSmallBlock];
+    for (int k = 0, q = tid; q < n; ++k, q += kSmallBlock) {
+        const int i = (bits & 2) ? idx[q] : q;
+        un[k] = (uint64_t)size[i] >> sh;
+        if (wide) {
+            su64[q] = un[k];
+            off64[q] = kUnplaced64;
+        } else {
+            su[q] = (uint32_t)un[k];
+            off[q] = kUnplacedT;
+        }
+        pid[q] = (uint32_t)i;
+        const int32_t r = gallop_reach(fst, q, n, last[i]);
+        reach[q] = r;
+        if (r - q > 1) long_list[atomicAdd(&n_long, 1u)] = q;  // every band is kept as a long one
+    }
+    __syncthreads();
+    for (int k = 0, q = tid; q < P; ++k, q += kSmallBlock) {
+        // pads last; a narrow size is below 2^32 units
+        if (wide) key[q] = q < n ? ~un[k] : ~0ull;
+        else key[q] = q < n ? ((uint64_t)(0xFFFFFFFFu - (uint32_t)un[k]) << 12) | (uint32_t)q : ~0ull;
+        idx[q] = (uint16_t)q;
+    }
+    __syncthreads();
+    if (wide) small_sort<false>(key, idx, P);
+    else small_sort<true>(key, idx, P);
+    for (int r = tid; r < n; r += kSmallBlock)
+        order[r] = wide ? (uint32_t)idx[r] : (uint32_t)(key[r] & 0xFFFu);
+    if (tid == 0) {
+        fl->shift = (uint32_t)sh;
+        fl->wide = wide ? 1u : 0u;
+        fl->lthr = 0;
+        fl->n_long = n_long;
+    }
+}
+
 // ---------------------------------------------------------------- placement
 
 // Offsets are published once and carry no other data, so device-coherent
@@ -368,13 +542,25 @@ __device__ __forceinline__ uint32_t take_rank(TFlags* fl, uint32_t* xbase, int64
 // Barrier after which every thread's global stores of the workgroup are
 // complete (the workgroup barrier alone does not wait for them); readers then
 // load through L2 (agent_load64).
+__device__ __forceinline__ void stores_done() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
 __device__ __forceinline__ void l2_barrier() {
-    __builtin_amdgcn_s_waitcnt(0);
+    stores_done();
     __syncthreads();
 }
 
+// Pointers that keep their address space as arguments of functions of their
+// own: a plain pointer argument makes every access a flat one, which in LDS
+// costs several times a direct access.  The kernels' large steps stay
+// functions (inlined together they no longer fit the registers).
+typedef __attribute__((address_space(3))) uint64_t* LdsU64;
+typedef __attribute__((address_space(3))) uint32_t* LdsU32;
+typedef __attribute__((address_space(1))) uint64_t* MemU64;
+typedef __attribute__((address_space(1))) uint32_t* MemU32;
+
 template <int BLOCK>
-__device__ void bitonic_sort_keys(uint64_t* keys, int m) {
+__device__ __forceinline__ void bitonic_sort_keys(uint64_t* keys, int m) {
     for (int k = 2; k <= m; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
             for (int i = threadIdx.x; i < (m >> 1); i += BLOCK) {
@@ -402,7 +588,10 @@ __device__ __forceinline__ uint32_t run_pmax(uint64_t k) { return (uint32_t)k; }
 // Sort keys[0..m0) in LDS (padded to a power of two) and turn the low halves
 // into prefix maxima of the ends.  Contiguous chunk per thread for the scan.
 template <int BLOCK>
-__device__ void make_run(uint64_t* keys, int m0, uint32_t* scratch) {
+__device__ __noinline__ void make_run(LdsU64 keys_l, int m0, LdsU32 scratch_l) {
+    uint64_t* keys = (uint64_t*)keys_l;
+    uint32_t* scratch = (uint32_t*)scratch_l;
+    m0 = (int)uniform((uint32_t)m0);
     int m = 1;
     while (m < m0) m <<= 1;
     for (int i = m0 + threadIdx.x; i < m; i += BLOCK) keys[i] = ~0ull;
@@ -450,17 +639,24 @@ __device__ __forceinline__ bool run_clear(const uint64_t* keys, int m, uint32_t 
 // that holds a run), then its maximal covered intervals, in address order,
 // written back over the keys as start << 32 | end (disjoint, so each end is
 // its own prefix maximum) and loaded into `skeys`.  The lowest and the
-// tightest fit depend on the union only.  Returns false, the keys untouched,
-// when the union reaches past kRunCap * 64 units or has more than kRunCap
+// tightest fit depend on the union only.  Returns the number of intervals, or
+// kNoUnion, the keys untouched, when the union reaches past kRunCap * 64 units or has more than kRunCap
 // intervals.
+constexpr uint32_t kNoUnion = 0xFFFFFFFFu;
+
 template <int BLOCK>
-__device__ bool union_run(uint64_t* gkeys, uint32_t nstat, uint64_t* skeys, uint32_t* scratch,
-                          uint64_t* scratch64, uint32_t* m_out) {
+__device__ __noinline__ uint32_t union_run(MemU64 gkeys_m, uint32_t nstat, LdsU64 skeys_l,
+                                           LdsU32 scratch_l, LdsU64 scratch64_l) {
+    uint64_t* gkeys = (uint64_t*)gkeys_m;
+    uint64_t* skeys = (uint64_t*)skeys_l;
+    uint32_t* scratch = (uint32_t*)scratch_l;
+    uint64_t* scratch64 = (uint64_t*)scratch64_l;
+    nstat = uniform(nstat);
     constexpr uint32_t kBits = (uint32_t)kRunCap * 64u;
     uint32_t top = 0;
     for (uint32_t i = threadIdx.x; i < nstat; i += BLOCK) top = max(top, (uint32_t)gkeys[i]);
-    top = block_reduce<BLOCK>(top, OpMax<uint32_t>(), scratch);
-    if (top > kBits) return false;
+    top = uniform(block_reduce<BLOCK>(top, OpMax<uint32_t>(), scratch));
+    if (top > kBits) return kNoUnion;
     uint32_t* bm = reinterpret_cast<uint32_t*>(skeys);
     const uint32_t nw = (top + 31) >> 5;
     for (uint32_t j = threadIdx.x; j < nw; j += BLOCK) bm[j] = 0u;
@@ -502,8 +698,8 @@ __device__ bool union_run(uint64_t* gkeys, uint32_t nstat, uint64_t* skeys, uint
     uint64_t total;
     const uint64_t base =
         block_exclusive_sum<BLOCK, uint64_t>(((uint64_t)cs << 32) | ce, &total, scratch64);
-    const uint32_t m = (uint32_t)total;
-    if (m > (uint32_t)kRunCap) return false;
+    const uint32_t m = uniform((uint32_t)total);
+    if (m > (uint32_t)kRunCap) return kNoUnion;
     uint32_t* g32 = reinterpret_cast<uint32_t*>(gkeys);  // key k: [2k] end, [2k + 1] start
     uint32_t gs = (uint32_t)(base >> 32), ge = (uint32_t)base;
     for (uint32_t j = j0; j < j1; ++j) {
@@ -515,8 +711,7 @@ __device__ bool union_run(uint64_t* gkeys, uint32_t nstat, uint64_t* skeys, uint
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < m; i += BLOCK) skeys[i] = gkeys[i];
     __syncthreads();
-    *m_out = m;
-    return true;
+    return m;
 }
 
 // Lowest offset clear of every run.  It is 0 or the end of some range; an
@@ -603,8 +798,14 @@ struct PlaceArgs {
     // fit policy: 0 lowest gap, 1 tightest gap (a build with MP_DEBUG_WAIT
     // also reads bits 8 and 9: a late list of 8; the widest wait)
     int32_t best;
-    uint32_t* xbase;  // kXcdGroups x xcap claimed blocks (+1), zero at the launch
+    uint32_t* xbase;  // BEST_FIT: kXcdGroups x xcap claimed blocks (+1), zero at the launch
     int64_t xcap;
+    // lowest fit: rank by position, and the hand-overs (kHands slots)
+    const uint32_t* rank_of;
+    uint64_t* heads;  // (rank + 1) << 32 | kByPreparer | late << 16 | gaps; zero at the launch
+    uint64_t* meta;   // 2 a slot: size << 32 | position; the run's top (or the offset)
+    uint64_t* gaps;   // kGapCap a slot: end << 32 | start, in address order
+    uint64_t* late;   // kDynCap a slot: size << 32 | rank
 };
 
 // Visit the positions ranked before t whose lifetimes meet t's: the forward
@@ -995,13 +1196,11 @@ struct WideArgs {
     int32_t best;
 };
 
+// lks, lke: kGRun words of LDS each; red64: BLOCK / 64; s_words: three words.
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void t_place_wide_kernel(WideArgs a) {
-    __shared__ uint64_t lks[kGRun];
-    __shared__ uint64_t lke[kGRun];
-    __shared__ uint64_t red64[BLOCK / kWave];
-    __shared__ uint32_t s_rank, s_cnt, s_slot;
-    if (a.fl->abort || !a.fl->wide) return;
+__device__ __forceinline__ void place_wide(const WideArgs& a, uint64_t* lks, uint64_t* lke,
+                                           uint64_t* red64, uint32_t* s_words) {
+    uint32_t &s_rank = s_words[0], &s_cnt = s_words[1];
     const uint32_t lthr = a.fl->lthr, n_long = a.fl->n_long;
     uint64_t* pv = a.priv + (int64_t)blockIdx.x * 4 * a.cap;
     const GenRanges own{pv, pv + a.cap, pv + 2 * a.cap, pv + 3 * a.cap};
@@ -1036,7 +1235,7 @@ __global__ __launch_bounds__(BLOCK) void t_place_wide_kernel(WideArgs a) {
         if (m <= a.cap) {
             x = fit_general<BLOCK>(own, m, st, a.best != 0, lks, lke, red64);
         } else {  // every predecessor is placed now: a pool slot, the ranges again
-            const uint32_t slot = pool_acquire(a.fl, &s_slot);
+            const uint32_t slot = pool_acquire(a.fl, s_words + 2);
             const GenRanges gr = pool_ranges(a.pool, slot, a.n);
             __syncthreads();
             if (threadIdx.x == 0) s_cnt = 0;
@@ -1050,75 +1249,472 @@ __global__ __launch_bounds__(BLOCK) void t_place_wide_kernel(WideArgs a) {
     }
 }
 
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a) {
 #ifdef MP_DEBUG_WAIT
-    // test build (MEMOPLAN_DEBUG_WAIT bits of a.best): 0x200 every wait takes
-    // its widest form; 0x100 besides the late list holds 8
+// test build (MEMOPLAN_DEBUG_WAIT bits of a.best): 0x200 every wait takes its
+// widest form; 0x100 besides the late list holds 8
 #define T_DYN_CAP ((a.best & 0x100) ? 8u : (uint32_t)kDynCap)
-#define T_BEST (a.best & 1)
 #define T_WIDEST_WAIT ((a.best & 0x200) != 0)
 #else
 #define T_DYN_CAP ((uint32_t)kDynCap)
-#define T_BEST a.best
 #define T_WIDEST_WAIT false
 #endif
-    __shared__ uint64_t skeys[kRunCap];  // placed predecessors (one run)
+
+// ------------------------------------------------- lowest fit: the placing workgroup
+//
+// The chain of dependencies is what bounds a trace (the decode-like one of
+// 100,000 tensors has 61,000 links, the ranking-like one of 10^6 nearly one a
+// tensor), and a link between two workgroups -- an agent-scope store, a poll
+// that sees it -- takes 0.6-0.8 us.  Here every link stays inside one CU: a wave
+// places the ranks it draws from an LDS counter, a tensor's late predecessors
+// are read from an LDS ring of (rank, offset) words that the other placing
+// waves write, and only the finished offset goes to memory, for the preparers.
+// Decode-like trace 49.4 -> 33.9 ms, ranking-like 712 -> 605 ms; a link is now
+// about 35 dependent instructions of one wave and two LDS round trips (0.4 us).
+
+// A wait that has found nothing for about 30 s (never expected): every
+// workgroup then leaves, and the call reports MP_EDEVICE.
+template <typename Args>
+__device__ __forceinline__ bool wait_over(uint32_t& spins, int64_t& since, const Args& a) {
+    if (++spins & 0xFFFFu) return false;
+    const int64_t now = (int64_t)wall_clock64();
+    if (since == 0) since = now;
+    if (now - since > 3000000000ll) {
+        raise_status(a.status, MP_EDEVICE);
+        agent_store(&a.fl->stop, 1u);
+    }
+    return agent_load(&a.fl->stop) != 0u;
+}
+
+// Its 16 waves: wave 0 commits (stores the offsets of the placed prefix and
+// moves the front), waves 1-7 load hand-overs into LDS, each four ranks at a
+// time, and waves 8-15, two a SIMD and at raised priority (38.5 ms without),
+// place: more polling waves a SIMD made every link wait for their instructions
+// (16 placing waves 50 ms, 10: 35.2, 4: 45).  Only
+// the commit and the loads touch memory, so a placing wave never waits for it.
+constexpr uint32_t kLoaders = 7, kLoadBlock = 4, kPlacers = 8;
+constexpr uint32_t kLdsHands = kLoaders * kLoadBlock;
+constexpr uint32_t kLdsLate = 256;        // late predecessors a slot holds (more: read from memory)
+constexpr uint32_t kSlotFree = 0xFFFFFFFFu;
+
+struct ChainArgs {  // of PlaceArgs, what the placing workgroup reads and writes
+    const uint32_t* order;
+    uint32_t* off;
+    const uint64_t *heads, *meta, *gaps, *late;
+    TFlags* fl;
+    int32_t* status;
+    uint32_t n;
+    int32_t best;
+};
+
+struct LdsHand {  // one hand-over
+    uint64_t gaps[kWave];
+    uint64_t late[kLdsLate];
+    uint32_t counts, st, top;  // the head's low half, size, the run's top (or the offset)
+    uint32_t rank;             // kSlotFree, or the rank once the rest is written
+};
+struct ChainShared {
+    uint64_t ring[kRing];  // rank << 32 | offset of the last rank placed in each slot
+    LdsHand hand[kLdsHands];
+    uint32_t next;   // next rank to draw
+    uint32_t front;  // every rank below is committed
+    uint32_t last;   // the rank placed last (a hint)
+};
+
+__device__ __forceinline__ uint64_t lds_poll64(const uint64_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// Stores the offsets of ranks placed so far, in order, 64 at a time.
+__device__ __forceinline__ void chain_commit(const ChainArgs& a, ChainShared& S) {
+    const uint32_t lane = threadIdx.x & (kWave - 1), n = a.n;
+    uint32_t f = 0, spins = 0;
+    int64_t since = 0;
+    while (f < n) {
+        const uint32_t r = f + lane;
+        const uint32_t qt = r < n ? a.order[r] : 0u;
+        uint32_t c;  // ranks f .. f + c - 1 are placed
+        uint64_t e;
+        while (true) {
+            e = lds_poll64(&S.ring[r & (kRing - 1)]);
+            const uint64_t ok = __ballot(r < n && (uint32_t)(e >> 32) == r);
+            c = ~ok ? (uint32_t)__builtin_ctzll(~ok) : (uint32_t)kWave;
+            if (c) break;
+            __builtin_amdgcn_s_sleep(2);
+            if (wait_over(spins, since, a)) return;
+        }
+        spins = 0;
+        since = 0;
+        if (lane < c) agent_store(a.off + qt, (uint32_t)e);
+        stores_done();
+        f += c;
+        if (lane == 0) {
+            lds_publish(&S.front, f);
+            agent_store(&a.fl->front, f);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Loads the hand-overs of every kLoaders-th block of kLoadBlock ranks.
+__device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, uint32_t loader) {
+    const uint32_t lane = threadIdx.x & (kWave - 1), n = a.n;
+    LdsHand* mine = S.hand + loader * kLoadBlock;
+    for (uint32_t base = loader * kLoadBlock; base < n; base += kLdsHands) {
+        uint32_t todo = (1u << min(kLoadBlock, n - base)) - 1u;
+        uint32_t spins = 0;
+        int64_t since = 0;
+        while (todo) {
+            const uint32_t r = base + lane;
+            const bool want = lane < kLoadBlock && ((todo >> lane) & 1u);
+            const uint64_t h = want ? agent_load64(a.heads + (r & (kHands - 1))) : 0ull;
+            const bool ok = want && (uint32_t)(h >> 32) == r + 1u &&
+                            lds_poll(&mine[lane & (kLoadBlock - 1)].rank) == kSlotFree;
+            const uint32_t m = (uint32_t)__ballot(ok);
+            if (!m) {
+                __builtin_amdgcn_s_sleep(2);
+                if (wait_over(spins, since, a)) return;
+                continue;
+            }
+            uint64_t gap[kLoadBlock], lt[kLoadBlock], me[kLoadBlock];
+            uint32_t hl[kLoadBlock];
+#pragma unroll
+            for (uint32_t j = 0; j < kLoadBlock; ++j) {
+                hl[j] = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)h, (int)j);
+                const uint32_t slot = (base + j) & (kHands - 1);
+                const bool on = (m >> j) & 1u, open = on && !(hl[j] & kByPreparer);
+                me[j] = on && lane < 2 ? agent_load64(a.meta + 2 * slot + lane) : 0ull;
+                gap[j] = open && lane < (hl[j] & 0xFFFFu)
+                             ? agent_load64(a.gaps + (size_t)slot * kGapCap + lane)
+                             : 0ull;
+                lt[j] = open && lane < (hl[j] >> 16)
+                            ? agent_load64(a.late + (size_t)slot * kDynCap + lane)
+                            : 0ull;
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < kLoadBlock; ++j) {
+                if (!((m >> j) & 1u)) continue;
+                LdsHand& H = mine[j];
+                H.gaps[lane] = gap[j];
+                H.late[lane] = lt[j];
+                const uint32_t nl = hl[j] >> 16;
+                if (!(hl[j] & kByPreparer) && nl > (uint32_t)kWave && nl <= kLdsLate) {
+                    const uint64_t* late = a.late + (size_t)((base + j) & (kHands - 1)) * kDynCap;
+                    uint64_t v[kLdsLate / kWave];
+#pragma unroll
+                    for (uint32_t k = 1; k < kLdsLate / kWave; ++k)
+                        v[k] = lane + kWave * k < nl ? agent_load64(late + lane + kWave * k) : 0ull;
+#pragma unroll
+                    for (uint32_t k = 1; k < kLdsLate / kWave; ++k) H.late[lane + kWave * k] = v[k];
+                }
+                if (lane == 0) {
+                    H.counts = hl[j];
+                    H.st = (uint32_t)(me[j] >> 32);
+                }
+                if (lane == 1) H.top = (uint32_t)me[j];
+                // one wave's LDS operations are performed in order
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                if (lane == 0) lds_publish(&H.rank, base + j);
+                __builtin_amdgcn_wave_barrier();
+            }
+            todo &= ~m;
+        }
+    }
+}
+
+// Finds the offset of rank r from its hand-over, with up to K late predecessors
+// a lane; false when a wait was given up.
+template <int K>
+__device__ __forceinline__ bool chain_place(const ChainArgs& a, ChainShared& S, LdsHand& H,
+                                            uint32_t r, int ng, int nl, uint32_t* x_out) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const size_t slot = r & (kHands - 1);
+    const uint64_t* gaps = a.gaps + slot * kGapCap;
+    const uint32_t st = uniform(H.st), top = uniform(H.top);
+    uint64_t gap = H.gaps[lane];
+    uint32_t want[K], sz[K];  // late ranks and their sizes (late predecessor lane + 64 k in slot k)
+    uint64_t pend[K];         // lanes still waiting
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int d = lane + kWave * k;
+        uint64_t v = 0;
+        if (K <= (int)kLdsLate / kWave) v = H.late[d];
+        else if (d < nl) v = agent_load64(a.late + slot * kDynCap + d);
+        want[k] = (uint32_t)v;
+        sz[k] = (uint32_t)(v >> 32);
+        pend[k] = __ballot(d < nl);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (lane == 0) lds_publish(&H.rank, kSlotFree);  // everything is in registers
+    // this lane's late ranges, empty until known
+    uint32_t lo_d[K], hi_d[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        lo_d[k] = kUnplacedT;
+        hi_d[k] = 0;
+    }
+    // lowest c' >= c with [c', c' + st) clear of every known late range: jump
+    // to the highest end among the (few) overlapping ones
+    auto past_late = [&](uint32_t c) {
+        while (true) {
+            uint32_t mx = 0;  // highest overlapping end of this lane (ends are > 0)
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                mx = (lo_d[k] < c + st && c < hi_d[k]) ? max(mx, hi_d[k]) : mx;
+            uint64_t ov = __ballot(mx != 0);
+            if (!ov) return c;
+            uint32_t v = c;
+            for (; ov; ov &= ov - 1)
+                v = max(v, (uint32_t)__builtin_amdgcn_readlane((int)mx, (int)__builtin_ctzll(ov)));
+            c = v;
+        }
+    };
+    // lowest fit at or above c in gaps k on, or above every placed range
+    uint32_t x = 0;
+    int xk = 0, batch = 0;
+    auto walk = [&](int k, uint32_t c) {
+        for (; k < ng; ++k) {
+            if ((k >> 6) != batch) {  // the next 64 gaps, one a lane
+                batch = k >> 6;
+                const int i = (batch << 6) + lane;
+                gap = i < ng ? agent_load64(gaps + i) : 0ull;
+            }
+            const uint32_t g0 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)gap, k & 63);
+            const uint32_t g1 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(gap >> 32), k & 63);
+            c = past_late(max(c, g0));
+            if ((uint64_t)c + st <= g1) break;
+        }
+        x = k < ng ? c : past_late(max(c, top));
+        xk = k;
+    };
+    // Known ranges only raise the lowest fit, so the answer is kept up to date
+    // as they arrive: it moves (the walk resumes from it) only when a range
+    // that arrived overlaps it.
+    walk(0, 0u);
+    uint32_t spins = 0;
+    int64_t since = 0;
+    uint64_t left = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) left |= pend[k];
+    while (left) {
+        uint64_t any = 0, hit = 0;
+        left = 0;
+        const uint32_t last = lds_poll(&S.last);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (K > 1 && !pend[k]) continue;
+            const uint64_t e = lds_poll64(&S.ring[want[k] & (kRing - 1)]);
+            const uint64_t in = __builtin_amdgcn_ballot_w64((uint32_t)(e >> 32) == want[k]) & pend[k];
+            if (in) {
+                const bool me = __builtin_amdgcn_inverse_ballot_w64(in);
+                lo_d[k] = me ? (uint32_t)e : lo_d[k];
+                hi_d[k] = me ? (uint32_t)e + sz[k] : hi_d[k];
+                hit |= __builtin_amdgcn_ballot_w64(lo_d[k] < x + st && x < hi_d[k]) & in;
+                any |= in;
+                pend[k] &= ~in;
+            }
+            left |= pend[k];
+        }
+        if (hit) walk(xk, x);
+        if (!any) {
+            // ranks far from the one placed last look again later
+            if ((int32_t)(r - uniform(last)) > 4) __builtin_amdgcn_s_sleep(2);
+            if (wait_over(spins, since, a)) return false;
+        }
+    }
+    *x_out = x;
+    return true;
+}
+
+// Draws ranks and places them.
+__device__ __forceinline__ void chain_solve(const ChainArgs& a, ChainShared& S) {
+    __builtin_amdgcn_s_setprio(3);
+    const uint32_t lane = threadIdx.x & (kWave - 1), n = a.n;
+    while (true) {
+        uint32_t r = 0;
+        if (lane == 0) r = atomicAdd(&S.next, 1u);
+        r = uniform(r);
+        if (r >= n) break;
+        LdsHand& H = S.hand[r % kLdsHands];
+        uint32_t spins = 0;
+        int64_t since = 0;
+        while (uniform(lds_poll(&H.rank)) != r) {
+            __builtin_amdgcn_s_sleep(1);
+            if (wait_over(spins, since, a)) return;
+        }
+        while (r - uniform(lds_poll(&S.front)) >= kRing - kAhead) {
+            __builtin_amdgcn_s_sleep(2);
+            if (wait_over(spins, since, a)) return;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        const uint32_t hl = uniform(H.counts);
+        uint32_t x;
+        if (hl & kByPreparer) {
+            x = uniform(H.top);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            if (lane == 0) lds_publish(&H.rank, kSlotFree);
+        } else {
+            const int ng = (int)(hl & 0xFFFFu), nl = (int)(hl >> 16);
+            bool ok;
+            if (T_WIDEST_WAIT || nl > 4 * kWave) ok = chain_place<8>(a, S, H, r, ng, nl, &x);
+            else if (nl <= kWave) ok = chain_place<1>(a, S, H, r, ng, nl, &x);
+            else ok = chain_place<4>(a, S, H, r, ng, nl, &x);
+            if (!ok) return;
+        }
+        if (lane == 0) {
+            __hip_atomic_store(&S.ring[r & (kRing - 1)], ((uint64_t)r << 32) | x, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+            lds_publish(&S.last, r);
+        }
+        __builtin_amdgcn_wave_barrier();  // lane 0's two steps stay apart (see the hand-over)
+    }
+}
+
+typedef __attribute__((address_space(3))) ChainShared* ChainLds;
+
+__device__ __noinline__ void chain_loop(ChainLds lds, MemU32 order, MemU32 off, MemU64 heads,
+                                        MemU64 meta, MemU64 gaps, MemU64 late, MemU32 fl,
+                                        MemU32 status, uint32_t n, int32_t best) {
+    ChainShared& S = *(ChainShared*)lds;
+    ChainArgs a{(const uint32_t*)order, (uint32_t*)off,  (const uint64_t*)heads,
+                (const uint64_t*)meta,  (const uint64_t*)gaps, (const uint64_t*)late,
+                (TFlags*)(uint32_t*)fl, (int32_t*)(uint32_t*)status, uniform(n),
+                (int32_t)uniform((uint32_t)best)};
+    const uint32_t wid = uniform(threadIdx.x / kWave);
+    for (uint32_t i = threadIdx.x; i < kRing; i += kChainBlock) S.ring[i] = ~0ull;
+    if (threadIdx.x < kLdsHands) S.hand[threadIdx.x].rank = kSlotFree;
+    if (threadIdx.x == 0) S.next = S.front = S.last = 0u;
+    __syncthreads();
+    static_assert(1 + kLoaders + kPlacers == kChainBlock / kWave, "a role for every wave");
+    if (wid == 0) chain_commit(a, S);
+    else if (wid <= kLoaders) chain_load(a, S, wid - 1u);
+    else chain_solve(a, S);
+}
+
+// kPlaceChain: the lowest fit with one placing workgroup (the first to start)
+// and the others preparing; kPlaceSelf and kPlaceBest: every workgroup places
+// its own ranks, at the lowest or the tightest gap.
+enum PlaceMode { kPlaceSelf, kPlaceBest, kPlaceChain };
+
+template <int BLOCK, PlaceMode MODE>
+__global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wide) {
+    constexpr bool BEST = MODE == kPlaceBest, CHAIN = MODE == kPlaceChain;
+    __shared__ uint64_t skeys[kRunCap];  // placed predecessors (one run); the placing workgroup's ring
     __shared__ uint64_t dkeys[kDynCap];  // predecessors placed after t was examined
     __shared__ uint32_t dpos[kDynCap];
     __shared__ uint32_t scratch[BLOCK / kWave];
     __shared__ uint64_t scratch64[BLOCK / kWave];
     __shared__ uint64_t gbits[kRunCap / 64];  // gaps of the placed run that hold t
-    __shared__ uint32_t cidx[kWave];           // the first 64 of them
+    __shared__ uint32_t cidx[kWave];           // kPlaceSelf: the first 64 of them
     __shared__ uint32_t s_rank, s_nstat, s_ndyn, s_slot, s_lcnt;
+    static_assert(sizeof(ChainShared) <= sizeof(skeys), "the placing workgroup's LDS");
     // the run buffer is free while predecessors are collected: the forward
     // band's candidate list
     uint32_t* const band_list = reinterpret_cast<uint32_t*>(skeys);
-    if (a.fl->abort || a.fl->wide) return;
+    if (a.fl->planned || a.fl->abort) return;
+    if constexpr (!CHAIN) {
+        if (a.fl->wide) {  // 64-bit unit counts
+            __shared__ uint32_t s_words[3];
+            place_wide<BLOCK>(wide, skeys, skeys + kGRun, scratch64, s_words);
+            return;
+        }
+    }
+    if (CHAIN && a.fl->wide) return;
+    if (MODE != kPlaceBest && (a.fl->chain != 0) != CHAIN) return;  // the other kernel places
     const uint32_t lthr = a.fl->lthr, n_long = a.fl->n_long;
+    if constexpr (CHAIN) {
+        if (threadIdx.x == 0) s_rank = atomicAdd(&a.fl->roles, 1u);
+        __syncthreads();
+        const uint32_t role = uniform(s_rank);
+        __syncthreads();
+        if (role == 0) {
+            chain_loop((ChainLds)skeys, (MemU32)a.order, (MemU32)a.off, (MemU64)a.heads,
+                       (MemU64)a.meta, (MemU64)a.gaps, (MemU64)a.late, (MemU32)a.fl,
+                       (MemU32)a.status, (uint32_t)a.n, a.best);
+            return;
+        }
+    }
     uint64_t* gkeys = a.run_keys + (int64_t)blockIdx.x * a.stat_cap;
     const int64_t stat_cap = a.stat_cap;
     while (true) {
         if (threadIdx.x == 0) {
-            s_rank = take_rank(a.fl, a.xbase, a.xcap);
+            if constexpr (!CHAIN) {
+                s_rank = take_rank(a.fl, a.xbase, a.xcap);
+            } else {
+                uint32_t r = atomicAdd(&a.fl->ticket, 1u);
+                uint32_t spins = 0;
+                int64_t since = 0;
+                while (r < (uint32_t)a.n && r >= agent_load(&a.fl->front) + kAhead) {
+                    __builtin_amdgcn_s_sleep(4);
+                    if (wait_over(spins, since, a)) r = (uint32_t)a.n;
+                }
+                s_rank = r;
+            }
             s_nstat = 0;
             s_ndyn = 0;
         }
         __syncthreads();
-        const uint32_t r = s_rank;
+        const uint32_t r = uniform(s_rank);
         if (r >= (uint32_t)a.n) break;
-        const int32_t qt = (int32_t)a.order[r];
-        const uint32_t st = a.su[qt];
+        const int32_t qt = (int32_t)uniform(a.order[r]);
+        const uint32_t st = uniform(a.su[qt]);
+        const uint32_t slot = r & (kHands - 1);
+        // The tensor's offset, found here: to its own place, or (lowest fit)
+        // handed to the placing workgroup.
+        auto give = [&](uint32_t x) {
+            if (threadIdx.x == 0) {
+                if constexpr (!CHAIN) {
+                    agent_store(a.off + qt, x);
+                } else {
+                    agent_store64(a.meta + 2 * slot + 1, x);
+                    stores_done();
+                    agent_store64(a.heads + slot, ((uint64_t)(r + 1u) << 32) | kByPreparer);
+                }
+            }
+            __syncthreads();
+        };
+        // the offset of a lower rank, waited for (0 when the call is given up)
+        auto placed = [&](uint32_t p) {
+            uint32_t o, spins = 0;
+            int64_t since = 0;
+            while ((o = agent_load(a.off + p)) == kUnplacedT) {
+                __builtin_amdgcn_s_sleep(1);
+                if (wait_over(spins, since, a)) return 0u;
+            }
+            return o;
+        };
         // 1. collect: placed predecessors as keys, unplaced ones by position
-        //    (beyond kDynCap of those, wait for them right here)
-        for_each_pred<BLOCK>(a, qt, st, lthr, n_long, band_list, &s_lcnt, [&](int32_t p, uint32_t o) {
-            if (o == kUnplacedT) {
-                const uint32_t d = atomicAdd(&s_ndyn, 1u);
-                if (d < T_DYN_CAP) {
-                    dpos[d] = (uint32_t)p;
+        while (true) {
+            for_each_pred<BLOCK>(a, qt, st, lthr, n_long, band_list, &s_lcnt, [&](int32_t p, uint32_t o) {
+                if (o == kUnplacedT) {
+                    const uint32_t d = atomicAdd(&s_ndyn, 1u);
+                    if (d < T_DYN_CAP) dpos[d] = (uint32_t)p;
                     return;
                 }
-                // more late predecessors than other workgroups: the grid
-                // broke its bound.  Report it; waiting here keeps the result
-                // right and every workgroup finishing.
+                const uint32_t k = atomicAdd(&s_nstat, 1u);
+                if (k < (uint32_t)stat_cap) gkeys[k] = ((uint64_t)o << 32) | (uint64_t)(o + a.su[p]);
+            });
+            __syncthreads();
+            if (uniform(s_ndyn) <= T_DYN_CAP) break;
+            // more late predecessors than the schedule leaves: its bound is
+            // broken.  Report it; collecting again until few enough are late
+            // keeps the result right and every workgroup finishing.
+            __syncthreads();
+            if (threadIdx.x == 0) {
                 raise_status(a.status, MP_EDEVICE);
-                while ((o = agent_load(a.off + p)) == kUnplacedT) __builtin_amdgcn_s_sleep(2);
+                s_nstat = 0;
+                s_ndyn = 0;
             }
-            const uint32_t k = atomicAdd(&s_nstat, 1u);
-            if (k < (uint32_t)stat_cap) gkeys[k] = ((uint64_t)o << 32) | (uint64_t)(o + a.su[p]);
-        });
-        __syncthreads();
-        uint32_t nstat = s_nstat;
-        const int ndyn = (int)min(s_ndyn, T_DYN_CAP);
+            __syncthreads();
+        }
+        uint32_t nstat = uniform(s_nstat);
+        const int ndyn = (int)min(uniform(s_ndyn), T_DYN_CAP);
         if (nstat > (uint32_t)stat_cap) {
             // more predecessors than the workgroup's buffer: wait for the late
             // ones, take a pool slot, collect every predecessor's range there
             // and fit over all of them (the general fit)
-            for (int d = threadIdx.x; d < ndyn; d += BLOCK)
-                while (agent_load(a.off + dpos[d]) == kUnplacedT) __builtin_amdgcn_s_sleep(1);
+            for (int d = threadIdx.x; d < ndyn; d += BLOCK) placed(dpos[d]);
             __syncthreads();
-            const uint32_t slot = pool_acquire(a.fl, &s_slot);
-            const GenRanges gr = pool_ranges(a.pool, slot, a.n);
+            const uint32_t ps = pool_acquire(a.fl, &s_slot);
+            const GenRanges gr = pool_ranges(a.pool, ps, a.n);
             if (threadIdx.x == 0) s_nstat = 0;
             __syncthreads();
             for_each_pred<BLOCK>(a, qt, st, lthr, n_long, band_list, &s_lcnt, [&](int32_t p, uint32_t o) {
@@ -1128,207 +1724,244 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a) {
                 gr.ke[k] = (uint64_t)o + a.su[p];
             });
             __syncthreads();
-            const uint64_t x = fit_general<BLOCK>(gr, s_nstat, st, T_BEST != 0, skeys,
-                                                  skeys + kGRun, scratch64);
-            pool_release(a.fl, slot);
-            if (threadIdx.x == 0) agent_store(a.off + qt, (uint32_t)x);
-            __syncthreads();
+            const uint64_t x = fit_general<BLOCK>(gr, s_nstat, st, BEST, skeys, skeys + kGRun,
+                                                  scratch64);
+            pool_release(a.fl, ps);
+            give((uint32_t)x);
             continue;
         }
         // 2. sorted runs of the placed predecessors: one in LDS when it fits,
         //    else runs of kRunCap sorted in LDS and kept in global scratch
         // beyond a few hundred ranges the union is cheaper than a sort
         int nruns = (int)((nstat + kRunCap - 1) / kRunCap);
-        uint32_t m_union = 0;
-        if (nstat > kUnionMin && union_run<BLOCK>(gkeys, nstat, skeys, scratch, scratch64, &m_union)) {
+        const uint32_t m_union =
+            nstat > kUnionMin ? uniform(union_run<BLOCK>((MemU64)gkeys, nstat, (LdsU64)skeys,
+                                                         (LdsU32)scratch, (LdsU64)scratch64))
+                              : kNoUnion;
+        if (m_union != kNoUnion) {
             nstat = m_union;
             nruns = 1;
         } else if (nruns == 1) {
             for (int i = threadIdx.x; i < (int)nstat; i += BLOCK) skeys[i] = gkeys[i];
             __syncthreads();
-            make_run<BLOCK>(skeys, (int)nstat, scratch);
+            make_run<BLOCK>((LdsU64)skeys, (int)nstat, (LdsU32)scratch);
         } else {
             for (int run = 0; run < nruns; ++run) {
                 const int m0 = (int)min((uint32_t)kRunCap, nstat - (uint32_t)run * kRunCap);
                 uint64_t* g = gkeys + (int64_t)run * kRunCap;
                 for (int i = threadIdx.x; i < m0; i += BLOCK) skeys[i] = g[i];
                 __syncthreads();
-                make_run<BLOCK>(skeys, m0, scratch);
+                make_run<BLOCK>((LdsU64)skeys, m0, (LdsU32)scratch);
                 for (int i = threadIdx.x; i < m0; i += BLOCK) g[i] = skeys[i];
                 __syncthreads();
             }
         }
-        // Lowest fit with one run of placed predecessors: before waiting,
-        // mark the run's gaps [prefix maximum below i, start of i) that hold
-        // t.  Then wave 0 alone waits for the late ones (all of them: one to
-        // four a lane, their ranges stay in registers) and walks the
-        // marked gaps in order, then the top: in a gap it moves past the
-        // highest end among the late ranges overlapping [c, c + st) until
-        // none does, and the first gap that still holds t gives the offset.
-        // No workgroup barrier lies between the last wait and the publish.
-        if (!T_BEST && nruns <= 1) {
-            const int m = (int)nstat, words = (m + 63) >> 6;
-            const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-            for (int w = wid; w < words; w += BLOCK / kWave) {
-                const int i = 64 * w + lane;
-                bool ok = false;
-                if (i < m) {
-                    const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
-                    ok = g1 > g0 && g1 - g0 >= st;
-                }
-                const uint64_t mk = __ballot(ok);
-                if (lane == 0) gbits[w] = mk;
-            }
-            __syncthreads();
-            // wave 0; K late predecessors a lane (K = 1, 4 or 8 for up to 64,
-            // 256 or 512 of them)
-            auto wave0 = [&](auto k_late) {
-                constexpr int K = decltype(k_late)::value;
-                // The first 64 marked gaps, in address order, one per lane
-                // (a prefix count over the first 64 words of marks); a gap
-                // beyond them is reached by the walk further down.
-                const uint64_t my_bits = lane < words ? gbits[lane] : 0ull;
-                const uint32_t my_cnt = (uint32_t)__popcll(my_bits);
-                const uint32_t incl = wave_inclusive_sum(my_cnt);
-                const uint32_t n_marked = (uint32_t)__shfl(incl, kWave - 1, kWave);
-                const int ncand = (int)min(n_marked, (uint32_t)kWave);
-                uint32_t slot = incl - my_cnt;
-                for (uint64_t bm = my_bits; bm && slot < (uint32_t)kWave; bm &= bm - 1, ++slot)
-                    cidx[slot] = (uint32_t)(64 * lane + __builtin_ctzll(bm));
-                __builtin_amdgcn_wave_barrier();
-                uint32_t cg0 = 0, cg1 = 0;  // this lane's candidate gap [cg0, cg1)
-                if (lane < ncand) {
-                    const int i = (int)cidx[lane];
-                    cg0 = i ? run_pmax(skeys[i - 1]) : 0u;
-                    cg1 = run_start(skeys[i]);
-                }
-                // marked gaps past the candidates: the walk resumes after the
-                // last candidate (word 64 on when the first 64 words hold no more)
-                const int resume = n_marked > (uint32_t)kWave || words > kWave
-                                       ? (n_marked >= (uint32_t)kWave
-                                              ? (int)(uint32_t)__builtin_amdgcn_readlane(
-                                                    (int)cidx[kWave - 1], 0) + 1
-                                              : 64 * kWave)
-                                       : m;
-                // When every marked gap is a candidate and a lane is left, that
-                // lane holds the top of the run (no end): the walk then never
-                // runs past the candidates.
-                const bool closed = resume == m && ncand < kWave;
-                const int nc = ncand + (closed ? 1 : 0), ktop = closed ? ncand : -1;
-                if (closed && lane == ncand) cg0 = m ? run_pmax(skeys[m - 1]) : 0u;
-                // this lane's late ranges (late predecessor lane + 64 r in
-                // slot r), empty until known
-                uint32_t lo_d[K], hi_d[K];
-#pragma unroll
-                for (int r = 0; r < K; ++r) {
-                    lo_d[r] = kUnplacedT;
-                    hi_d[r] = 0;
-                }
-                // lowest c' >= c with [c', c' + st) clear of every known late
-                // range: jump to the highest end among the (few) overlapping ones
-                auto past_late = [&](uint32_t c) {
-                    while (true) {
-                        uint32_t mx = 0;  // highest overlapping end of this lane (ends are > 0)
-#pragma unroll
-                        for (int r = 0; r < K; ++r)
-                            mx = (lo_d[r] < c + st && c < hi_d[r]) ? max(mx, hi_d[r]) : mx;
-                        uint64_t ov = __ballot(mx != 0);
-                        if (!ov) return c;
-                        uint32_t v = c;
-                        for (; ov; ov &= ov - 1)
-                            v = max(v, (uint32_t)__builtin_amdgcn_readlane((int)mx, (int)__builtin_ctzll(ov)));
-                        c = v;
+        // Lowest fit with one run of placed predecessors: mark the run's gaps
+        // [prefix maximum below i, start of i) that hold t.  CHAIN: they go to
+        // the placing workgroup, in address order, with the late predecessors.
+        // Else wave 0 alone waits for the late ones (all of them: one to eight
+        // a lane, their ranges stay in registers) and walks the marked gaps in
+        // order, then the top: in a gap it moves past the highest end among the
+        // late ranges overlapping [c, c + st) until none does, and the first
+        // gap that still holds t gives the offset.  No workgroup barrier lies
+        // between the last wait and the publish.
+        if constexpr (!BEST) {
+            if (nruns <= 1) {
+                const int m = (int)nstat, words = (m + 63) >> 6;
+                const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+                for (int w = wid; w < words; w += BLOCK / kWave) {
+                    const int i = 64 * w + lane;
+                    bool ok = false;
+                    if (i < m) {
+                        const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
+                        ok = g1 > g0 && g1 - g0 >= st;
                     }
-                };
-                // lowest fit at or above c in candidates k on: x and its
-                // candidate xk; false when it runs past the candidates
-                uint32_t x = 0;
-                int xk = 0;
-                auto walk = [&](int k, uint32_t c) {
-                    for (; k < nc; ++k) {
-                        c = past_late(max(c, (uint32_t)__builtin_amdgcn_readlane((int)cg0, k)));
-                        if (k == ktop ||
-                            (uint64_t)c + st <= (uint32_t)__builtin_amdgcn_readlane((int)cg1, k)) {
-                            x = c;
-                            xk = k;
-                            return true;
+                    const uint64_t mk = __ballot(ok);
+                    if (lane == 0) gbits[w] = mk;
+                }
+                __syncthreads();
+                if constexpr (!CHAIN) {
+                    // wave 0; K late predecessors a lane (K = 1, 4 or 8 for up to 64,
+                    // 256 or 512 of them)
+                    auto wave0 = [&](auto k_late) {
+                        constexpr int K = decltype(k_late)::value;
+                        // The first 64 marked gaps, in address order, one per lane
+                        // (a prefix count over the first 64 words of marks); a gap
+                        // beyond them is reached by the walk further down.
+                        const uint64_t my_bits = lane < words ? gbits[lane] : 0ull;
+                        const uint32_t my_cnt = (uint32_t)__popcll(my_bits);
+                        const uint32_t incl = wave_inclusive_sum(my_cnt);
+                        const uint32_t n_marked = (uint32_t)__shfl(incl, kWave - 1, kWave);
+                        const int ncand = (int)min(n_marked, (uint32_t)kWave);
+                        uint32_t slot = incl - my_cnt;
+                        for (uint64_t bm = my_bits; bm && slot < (uint32_t)kWave; bm &= bm - 1, ++slot)
+                            cidx[slot] = (uint32_t)(64 * lane + __builtin_ctzll(bm));
+                        __builtin_amdgcn_wave_barrier();
+                        uint32_t cg0 = 0, cg1 = 0;  // this lane's candidate gap [cg0, cg1)
+                        if (lane < ncand) {
+                            const int i = (int)cidx[lane];
+                            cg0 = i ? run_pmax(skeys[i - 1]) : 0u;
+                            cg1 = run_start(skeys[i]);
                         }
-                    }
-                    return false;
-                };
-                // The wait, one late predecessor a lane.  Known ranges only
-                // raise the lowest fit, so the answer is kept up to date as
-                // they arrive: it moves (the walk resumes from it) only when
-                // a range that arrived overlaps it.
-                uint32_t pend = 0, p[K], sp[K];  // pend: bit r for slot r
-#pragma unroll
-                for (int r = 0; r < K; ++r) {
-                    const int d = lane + kWave * r;
-                    p[r] = d < ndyn ? dpos[d] : 0u;
-                    sp[r] = d < ndyn ? a.su[p[r]] : 0u;
-                    pend |= d < ndyn ? 1u << r : 0u;
-                }
-                bool ok = walk(0, 0u);
-                while (__ballot(pend != 0)) {
-                    uint32_t o[K];
-#pragma unroll
-                    for (int r = 0; r < K; ++r) o[r] = (pend >> r) & 1u ? agent_load(a.off + p[r]) : kUnplacedT;
-                    bool got = false, hit = false;
-#pragma unroll
-                    for (int r = 0; r < K; ++r) {
-                        if (o[r] != kUnplacedT) {
-                            lo_d[r] = o[r];
-                            hi_d[r] = o[r] + sp[r];
-                            pend &= ~(1u << r);
-                            got = true;
-                            hit = hit || (lo_d[r] < x + st && x < hi_d[r]);
+                        // marked gaps past the candidates: the walk resumes after the
+                        // last candidate (word 64 on when the first 64 words hold no more)
+                        const int resume = n_marked > (uint32_t)kWave || words > kWave
+                                               ? (n_marked >= (uint32_t)kWave
+                                                      ? (int)(uint32_t)__builtin_amdgcn_readlane(
+                                                            (int)cidx[kWave - 1], 0) + 1
+                                                      : 64 * kWave)
+                                               : m;
+                        // When every marked gap is a candidate and a lane is left, that
+                        // lane holds the top of the run (no end): the walk then never
+                        // runs past the candidates.
+                        const bool closed = resume == m && ncand < kWave;
+                        const int nc = ncand + (closed ? 1 : 0), ktop = closed ? ncand : -1;
+                        if (closed && lane == ncand) cg0 = m ? run_pmax(skeys[m - 1]) : 0u;
+                        // this lane's late ranges (late predecessor lane + 64 r in
+                        // slot r), empty until known
+                        uint32_t lo_d[K], hi_d[K];
+        #pragma unroll
+                        for (int r = 0; r < K; ++r) {
+                            lo_d[r] = kUnplacedT;
+                            hi_d[r] = 0;
                         }
-                    }
-                    // no sleep between polls: each takes an agent-scope load's
-                    // round trip, and a sleep only delays the detection
-                    if (!__ballot(got)) continue;
-                    if (ok && __ballot(hit)) ok = walk(xk, x);
-                }
-                // every late range is known
-                if (!ok) {  // past the candidates: the marked gaps after them, then the top
-                    bool found = walk(0, 0u);
-                    for (int w = resume >> 6; w < words && !found; ++w) {
-                        uint64_t bm = gbits[w];
-                        if (w == (resume >> 6)) bm &= ~0ull << (resume & 63);
-                        for (; bm; bm &= bm - 1) {
-                            const int i = 64 * w + __builtin_ctzll(bm);
-                            const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
-                            const uint32_t c = past_late(g0);
-                            if ((uint64_t)c + st <= g1) {
-                                x = c;
-                                found = true;
-                                break;
+                        // lowest c' >= c with [c', c' + st) clear of every known late
+                        // range: jump to the highest end among the (few) overlapping ones
+                        auto past_late = [&](uint32_t c) {
+                            while (true) {
+                                uint32_t mx = 0;  // highest overlapping end of this lane (ends are > 0)
+        #pragma unroll
+                                for (int r = 0; r < K; ++r)
+                                    mx = (lo_d[r] < c + st && c < hi_d[r]) ? max(mx, hi_d[r]) : mx;
+                                uint64_t ov = __ballot(mx != 0);
+                                if (!ov) return c;
+                                uint32_t v = c;
+                                for (; ov; ov &= ov - 1)
+                                    v = max(v, (uint32_t)__builtin_amdgcn_readlane((int)mx, (int)__builtin_ctzll(ov)));
+                                c = v;
                             }
+                        };
+                        // lowest fit at or above c in candidates k on: x and its
+                        // candidate xk; false when it runs past the candidates
+                        uint32_t x = 0;
+                        int xk = 0;
+                        auto walk = [&](int k, uint32_t c) {
+                            for (; k < nc; ++k) {
+                                c = past_late(max(c, (uint32_t)__builtin_amdgcn_readlane((int)cg0, k)));
+                                if (k == ktop ||
+                                    (uint64_t)c + st <= (uint32_t)__builtin_amdgcn_readlane((int)cg1, k)) {
+                                    x = c;
+                                    xk = k;
+                                    return true;
+                                }
+                            }
+                            return false;
+                        };
+                        // The wait, one late predecessor a lane.  Known ranges only
+                        // raise the lowest fit, so the answer is kept up to date as
+                        // they arrive: it moves (the walk resumes from it) only when
+                        // a range that arrived overlaps it.
+                        uint32_t pend = 0, p[K], sp[K];  // pend: bit r for slot r
+        #pragma unroll
+                        for (int r = 0; r < K; ++r) {
+                            const int d = lane + kWave * r;
+                            p[r] = d < ndyn ? dpos[d] : 0u;
+                            sp[r] = d < ndyn ? a.su[p[r]] : 0u;
+                            pend |= d < ndyn ? 1u << r : 0u;
                         }
+                        bool ok = walk(0, 0u);
+                        while (__ballot(pend != 0)) {
+                            uint32_t o[K];
+        #pragma unroll
+                            for (int r = 0; r < K; ++r) o[r] = (pend >> r) & 1u ? agent_load(a.off + p[r]) : kUnplacedT;
+                            bool got = false, hit = false;
+        #pragma unroll
+                            for (int r = 0; r < K; ++r) {
+                                if (o[r] != kUnplacedT) {
+                                    lo_d[r] = o[r];
+                                    hi_d[r] = o[r] + sp[r];
+                                    pend &= ~(1u << r);
+                                    got = true;
+                                    hit = hit || (lo_d[r] < x + st && x < hi_d[r]);
+                                }
+                            }
+                            // no sleep between polls: each takes an agent-scope load's
+                            // round trip, and a sleep only delays the detection
+                            if (!__ballot(got)) continue;
+                            if (ok && __ballot(hit)) ok = walk(xk, x);
+                        }
+                        // every late range is known
+                        if (!ok) {  // past the candidates: the marked gaps after them, then the top
+                            bool found = walk(0, 0u);
+                            for (int w = resume >> 6; w < words && !found; ++w) {
+                                uint64_t bm = gbits[w];
+                                if (w == (resume >> 6)) bm &= ~0ull << (resume & 63);
+                                for (; bm; bm &= bm - 1) {
+                                    const int i = 64 * w + __builtin_ctzll(bm);
+                                    const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
+                                    const uint32_t c = past_late(g0);
+                                    if ((uint64_t)c + st <= g1) {
+                                        x = c;
+                                        found = true;
+                                        break;
+                                    }
+                                }
+                            }
+                            if (!found) x = past_late(m ? run_pmax(skeys[m - 1]) : 0u);
+                        }
+                        if (lane == 0) agent_store(a.off + qt, x);
+                    };
+                    if (wid == 0) {
+                        if (T_WIDEST_WAIT) wave0(std::integral_constant<int, 8>{});
+                        else if (ndyn <= kWave) wave0(std::integral_constant<int, 1>{});
+                        else if (ndyn <= 4 * kWave) wave0(std::integral_constant<int, 4>{});
+                        else wave0(std::integral_constant<int, 8>{});
                     }
-                    if (!found) x = past_late(m ? run_pmax(skeys[m - 1]) : 0u);
+                    __syncthreads();
+                    continue;
                 }
-                if (lane == 0) agent_store(a.off + qt, x);
-            };
-            if (wid == 0) {
-                if (T_WIDEST_WAIT) wave0(std::integral_constant<int, 8>{});
-                else if (ndyn <= kWave) wave0(std::integral_constant<int, 1>{});
-                else if (ndyn <= 4 * kWave) wave0(std::integral_constant<int, 4>{});
-                else wave0(std::integral_constant<int, 8>{});
+                static_assert(kRunCap / 64 <= BLOCK, "a thread per word of marks");
+                uint64_t bits = (int)threadIdx.x < words ? gbits[threadIdx.x] : 0ull;
+                uint32_t ng;
+                uint32_t at = block_exclusive_sum<BLOCK>((uint32_t)__popcll(bits), &ng, scratch);
+                ng = uniform(ng);
+                if (ng <= kGapCap) {
+                    for (; bits; bits &= bits - 1, ++at) {
+                        const int i = 64 * (int)threadIdx.x + __builtin_ctzll(bits);
+                        const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
+                        agent_store64(a.gaps + (size_t)slot * kGapCap + at, ((uint64_t)g1 << 32) | g0);
+                    }
+                    for (int d = threadIdx.x; d < ndyn; d += BLOCK) {
+                        const uint32_t p = dpos[d];
+                        agent_store64(a.late + (size_t)slot * kDynCap + d,
+                                      ((uint64_t)a.su[p] << 32) | a.rank_of[p]);
+                    }
+                    if (threadIdx.x == 0) {
+                        agent_store64(a.meta + 2 * slot, ((uint64_t)st << 32) | (uint32_t)qt);
+                        agent_store64(a.meta + 2 * slot + 1, m ? run_pmax(skeys[m - 1]) : 0u);
+                    }
+                    l2_barrier();  // the hand-over is in memory before its head
+                    if (threadIdx.x == 0)
+                        agent_store64(a.heads + slot, ((uint64_t)(r + 1u) << 32) |
+                                                          ((uint64_t)(uint32_t)ndyn << 16) | ng);
+                    // Without a barrier here the compiler joins this test of
+                    // thread 0 with the one at the loop's top: the first
+                    // wave's other lanes then go round the loop, barriers
+                    // included, before lane 0 has drawn the next rank.
+                    __syncthreads();
+                    continue;
+                }
             }
-            __syncthreads();
-            continue;
         }
         // 3. wait for the predecessors that were not placed yet; their ranges
         //    form one more run
         for (int d = threadIdx.x; d < ndyn; d += BLOCK) {
             const uint32_t p = dpos[d];
-            uint32_t o;
-            while ((o = agent_load(a.off + p)) == kUnplacedT) __builtin_amdgcn_s_sleep(1);
+            const uint32_t o = placed(p);
             dkeys[d] = ((uint64_t)o << 32) | (uint64_t)(o + a.su[p]);
         }
         __syncthreads();
-        if (ndyn) make_run<BLOCK>(dkeys, ndyn, scratch);
+        if (ndyn) make_run<BLOCK>((LdsU64)dkeys, ndyn, (LdsU32)scratch);
         // 4. the fit over every run (one pass)
         RunRef runs[kScratchRuns + 1];
         int nr = 0;
@@ -1341,15 +1974,82 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a) {
         }
         if (ndyn) runs[nr++] = RunRef{dkeys, ndyn};
         uint32_t x;
-        if (T_BEST) x = best_fit_runs<BLOCK, kScratchRuns + 1>(runs, nr, st, scratch64);
+        if constexpr (BEST) x = best_fit_runs<BLOCK, kScratchRuns + 1>(runs, nr, st, scratch64);
         else x = nr ? fit_runs<BLOCK, kScratchRuns + 1>(runs, nr, st, scratch) : 0u;
-        if (threadIdx.x == 0) agent_store(a.off + qt, x);
-        __syncthreads();
+        give(x);
+    }
+}
+
+// Rank by position (the inverse of the rank order), for the hand-overs, and the
+// choice of the lowest fit's kernel from up to kDepthWindows windows of 128
+// consecutive ranks, one a workgroup: their dependency depth (level of a
+// tensor: one more than the highest among the window's earlier ranks it meets)
+// and the share of their pairs that meet.  256 workgroups placing their own
+// ranks take about 0.75 us a level, one workgroup about 0.33 us a rank whatever
+// the depth, and more where a tensor's late predecessors are many (each is held
+// in a lane and walked past).  Measured (depth and pairs met as shares of a
+// window's most), each its own / one workgroup: ResNeXt-like 30,000 tensors (2%,
+// 0%) 1.2 / 10 ms; decode-like 40,000 (63%, 15%) 19.1 / 13.5 ms; ranking-like
+// 300,000 (76%, 41.3%) 209 / 180 ms, 70,000 (73%, 43.7%) 43.2 / 42.6 ms, 40,000
+// (70%, 48%) 24.4 / 29.2 ms, 20,000 (71%, 56%) 15.2 / 23.0 ms.
+constexpr uint32_t kDepthWindow = 128, kDepthWindows = 64;
+constexpr uint64_t kDepthPercent = 45, kMeetPercent = 43;
+__global__ __launch_bounds__(256) void t_rank_of_kernel(const uint32_t* __restrict__ order,
+                                                        const int32_t* __restrict__ reach,
+                                                        int64_t n, uint32_t* __restrict__ rank_of,
+                                                        TFlags* fl) {
+    if (fl->abort || fl->wide) return;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += stride)
+        rank_of[order[r]] = (uint32_t)r;
+    const uint32_t windows = min(gridDim.x, kDepthWindows);
+    if (blockIdx.x >= windows || threadIdx.x >= (unsigned)kWave) return;
+    // wave 0: two ranks a lane (lane, lane + 64), levels kept in registers
+    const int lane = threadIdx.x;
+    const int64_t r0 = n > (int64_t)kDepthWindow
+                           ? (n - (int64_t)kDepthWindow) * blockIdx.x / (windows > 1 ? windows - 1 : 1)
+                           : 0;
+    int32_t q[2], z[2];
+    uint32_t lv[2], met = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int64_t r = r0 + lane + kWave * k;
+        q[k] = r < n ? (int32_t)order[r] : INT32_MAX;
+        z[k] = r < n ? reach[q[k]] : 0;
+        lv[k] = r < n ? 1u : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        for (int i = 0; i < kWave; ++i) {
+            // the rank's level is final; it lifts the later ranks it meets
+            const int32_t qi = __builtin_amdgcn_readlane(q[k], i), zi = __builtin_amdgcn_readlane(z[k], i);
+            const uint32_t li = (uint32_t)__builtin_amdgcn_readlane((int)lv[k], i) + 1u;
+#pragma unroll
+            for (int m = k; m < 2; ++m) {
+                const bool meets = q[m] < qi ? z[m] > qi : zi > q[m];
+                const bool later = lane + kWave * m > i + kWave * k;
+                lv[m] = meets && later && lv[m] < li ? li : lv[m];
+                met += meets && later ? 1u : 0u;
+            }
+        }
+    }
+    const uint32_t d = wave_reduce(max(lv[0], lv[1]), OpMax<uint32_t>());
+    met = wave_reduce(met, OpAdd<uint32_t>());
+    if (lane == 0) {
+        atomicAdd(&fl->depth, d);
+        atomicAdd(&fl->meets, met);
+        __threadfence();
+        if (atomicAdd(&fl->done_depth, 1u) == windows - 1) {
+            const uint64_t w = (uint64_t)min(n, (int64_t)kDepthWindow);
+            const bool deep = 100ull * flag_load(&fl->depth) > kDepthPercent * (windows * w);
+            const bool sparse =
+                100ull * flag_load(&fl->meets) < kMeetPercent * (windows * (w * (w - 1) / 2));
+            fl->chain = deep && sparse ? 1u : 0u;
+        }
     }
 }
 
 #undef T_DYN_CAP
-#undef T_BEST
 #undef T_WIDEST_WAIT
 
 __global__ __launch_bounds__(256) void t_output_kernel(const uint32_t* __restrict__ off,
@@ -1361,6 +2061,7 @@ __global__ __launch_bounds__(256) void t_output_kernel(const uint32_t* __restric
                                                        TFlags* fl, int64_t* __restrict__ peak_out) {
     __shared__ uint64_t red[256 / kWave];
     __shared__ uint32_t s_last;
+    if (fl->planned) return;
     if (fl->abort) {
         if (blockIdx.x == 0 && threadIdx.x == 0) *peak_out = (int64_t)fl->peak;
         return;
@@ -1393,7 +2094,7 @@ __global__ void t_peak_kernel(const TFlags* fl, int64_t* peak_out) { *peak_out =
 
 struct TLayout {
     size_t flags, su, pf, pl, pid, off, su64, off64, reach, keys0, vals0, keys1, vals1, radix,
-        lflag, lpartial, llist, run_keys, pool, xbase, total;
+        lflag, lpartial, llist, run_keys, pool, xbase, rank_of, heads, meta, gaps, late, total;
     int64_t xcap;  // rank blocks an XCD can claim
     unsigned grid;
 };
@@ -1411,8 +2112,8 @@ unsigned place_grid() {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus < 1)
         cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, t_place_kernel<kTBlock>, kTBlock, 0) !=
-            hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, t_place_kernel<kTBlock, kPlaceBest>, kTBlock,
+                                                     0) != hipSuccess ||
         per < 1)
         per = 1;
     const int64_t g = (int64_t)cus * per;
@@ -1460,6 +2161,11 @@ TLayout t_layout(int64_t n, unsigned grid) {
     // that ends it): blocks 0 .. (n + grid) / kTicketBlock
     L.xcap = (nn + (int64_t)grid) / kTicketBlock + 2;
     L.xbase = take((size_t)kXcdGroups * (size_t)L.xcap * 4);
+    L.rank_of = take(nn * 4);
+    L.heads = take((size_t)kHands * 8);
+    L.meta = take((size_t)kHands * 16);
+    L.gaps = take((size_t)kHands * kGapCap * 8);
+    L.late = take((size_t)kHands * kDynCap * 8);
     L.total = o;
     L.grid = grid;
     return L;
@@ -1497,7 +2203,13 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
     int64_t* lpartial = reinterpret_cast<int64_t*>(w + L.lpartial);
     int32_t* llist = reinterpret_cast<int32_t*>(w + L.llist);
 
-    hipLaunchKernelGGL(t_init_kernel, dim3(1), dim3(64), 0, st, fl);
+    // Up to the batched planner's longest trace, its kernel takes the trace as a
+    // batch of one in one launch; what it cannot hold (told by fl->planned) goes
+    // on below, with one workgroup's preparation.  256 recorded tensors: 58.9
+    // -> 26 us (14 launches before, 4 now), 2000: 149 -> 68 us, 3001 in any order,
+    // tightest fit: 315 -> 245 us.
+    const bool small = n > 0 && n <= kSmallN;
+    if (!small) hipLaunchKernelGGL(t_init_kernel, dim3(1), dim3(64), 0, st, fl);
     if (n == 0) {
         hipLaunchKernelGGL(t_peak_kernel, dim3(1), dim3(1), 0, st, (const TFlags*)fl, peak_out);
         return hipGetLastError();
@@ -1505,12 +2217,20 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
     const unsigned g = grid_n(n, 256);
     uint32_t* xbase = reinterpret_cast<uint32_t*>(w + L.xbase);
     const int64_t nx = (int64_t)kXcdGroups * L.xcap;
-    hipLaunchKernelGGL(t_ingest_kernel, dim3(g), dim3(256), 0, st, size, first, last, n, num_ops,
-                       fl, status, keys0, vals0, xbase, nx);
-    // position order (unsorted inputs only)
     bool alt = false;
-    hipError_t e = radix_sort_pairs(keys0, vals0, keys1, vals1, n, 0, 32, rws, &alt, st,
-                                    &fl->sorted);
+    hipError_t e = hipSuccess;
+    if (small) {
+        e = launch_plan_one(size, first, last, n, num_ops, policy, offset_out, peak_out,
+                            w + L.run_keys, &fl->planned, status, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(t_small_kernel, dim3(1), dim3(kSmallBlock), 0, st, size, first, last,
+                           (int)n, num_ops, fl, status, su, su64, off, off64, pid, reach, vals0,
+                           llist, xbase, nx);
+    } else {
+    hipLaunchKernelGGL(t_ingest_kernel, dim3(g), dim3(256), 0, st, size, first, last, n, num_ops,
+                       fl, status, keys0, vals0, xbase, nx, reinterpret_cast<uint64_t*>(w + L.heads));
+    // position order (unsorted inputs only)
+    e = radix_sort_pairs(keys0, vals0, keys1, vals1, n, 0, 32, rws, &alt, st, &fl->sorted);
     if (e != hipSuccess) return e;
     // positions, and the rank-sort pairs in (keys0, vals0)
     hipLaunchKernelGGL(t_positions_kernel, dim3(g), dim3(256), 0, st,
@@ -1533,6 +2253,7 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
     e = radix_sort_pairs(keys0, vals0, keys1, vals1, n, 0, 64, rws, &alt64, st, &fl->skip_wide);
     if (e != hipSuccess) return e;
     if (alt != alt64) return hipErrorInvalidValue;  // both sorts end in the same buffer
+    }
     uint64_t* pool = reinterpret_cast<uint64_t*>(w + L.pool);
     PlaceArgs pa{su,
                  reach,
@@ -1547,7 +2268,12 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
                  status,
                  policy == MP_BEST_FIT ? 1 : 0,
                  xbase,
-                 L.xcap};
+                 L.xcap,
+                 reinterpret_cast<const uint32_t*>(w + L.rank_of),
+                 reinterpret_cast<uint64_t*>(w + L.heads),
+                 reinterpret_cast<uint64_t*>(w + L.meta),
+                 reinterpret_cast<uint64_t*>(w + L.gaps),
+                 reinterpret_cast<uint64_t*>(w + L.late)};
 #ifdef MP_DEBUG_WAIT
     // test build: MEMOPLAN_DEBUG_WAIT=wide makes every wait hold eight late
     // predecessors a lane; =tight besides caps the late list at 8, so tensors
@@ -1558,11 +2284,23 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
         if (!strcmp(dbg, "tight")) pa.best |= 0x300;
     }
 #endif
-    hipLaunchKernelGGL(t_place_kernel<kTBlock>, dim3(L.grid), dim3(kTBlock), 0, st, pa);
-    WideArgs wa{su64, reach, alt ? vals1 : vals0, llist, off64,
-                reinterpret_cast<uint64_t*>(w + L.run_keys), stat_cap_of(n) / 4, pool, n, fl,
-                policy == MP_BEST_FIT ? 1 : 0};
-    hipLaunchKernelGGL(t_place_wide_kernel<kTBlock>, dim3(L.grid), dim3(kTBlock), 0, st, wa);
+    const WideArgs wa{su64, reach, pa.order, llist, off64,
+                      reinterpret_cast<uint64_t*>(w + L.run_keys), stat_cap_of(n) / 4, pool, n, fl,
+                      policy == MP_BEST_FIT ? 1 : 0};
+    if (policy == MP_BEST_FIT) {
+        hipLaunchKernelGGL((t_place_kernel<kTBlock, kPlaceBest>), dim3(L.grid), dim3(kTBlock), 0,
+                           st, pa, wa);
+    } else {
+        if (!small) {
+            hipLaunchKernelGGL(t_rank_of_kernel, dim3(g), dim3(256), 0, st, pa.order,
+                               (const int32_t*)reach, n,
+                               reinterpret_cast<uint32_t*>(w + L.rank_of), fl);
+            hipLaunchKernelGGL((t_place_kernel<kChainBlock, kPlaceChain>), dim3(L.grid),
+                               dim3(kChainBlock), 0, st, pa, wa);
+        }
+        hipLaunchKernelGGL((t_place_kernel<kTBlock, kPlaceSelf>), dim3(L.grid), dim3(kTBlock), 0,
+                           st, pa, wa);
+    }
     hipLaunchKernelGGL(t_output_kernel, dim3(g), dim3(256), 0, st, (const uint32_t*)off,
                        (const uint32_t*)su, (const uint64_t*)off64, (const uint64_t*)su64,
                        (const uint32_t*)pid, n, offset_out, fl, peak_out);

@@ -203,3 +203,59 @@ def test_status_codes_and_empty():
     wide = tg.Trace(np.array([2 ** 31 + 1, 2 ** 31 + 1], np.int64), np.zeros(2, np.int32),
                     np.zeros(2, np.int32), 1)
     assert status(wide) == binding.MP_OK
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("n", [1, 2, 512, 513, 2048, 2049, 4095, 4096, 4097])
+def test_short_trace_paths(n, policy):
+    """Traces of up to 4,096 tensors go to the batched planner's kernel, at its
+    slot counts (512, 2048, 4096), and those it leaves (more than 12 pairs a
+    tensor, 64-bit unit counts, far-reaching tensors) to one workgroup's
+    preparation: both sides of each, in order and shuffled."""
+    binding = need_gpu()
+    rng = np.random.default_rng(310 + n)
+    cases = {"sparse": tg.random_trace(rng, n, n, max_len=4, sorted_first=True),
+             "shuffled, few sizes": tg.random_trace(rng, n, n, max_len=6, sizes=[64, 192, 448]),
+             "dense": tg.random_trace(rng, n, max(1, n // 4), max_len=max(1, n // 20)),
+             "dense, in order": tg.random_trace(rng, n, max(1, n // 25), max_len=12,
+                                                sorted_first=True, sizes=[256, 320, 384])}
+    wide = tg.random_trace(rng, n, n, max_len=3)
+    wide.size[:] = rng.integers(2 ** 31, 2 ** 35, n) | 1
+    cases["64-bit unit counts"] = wide
+    far = tg.random_trace(rng, n, n, max_len=2, sorted_first=True)
+    far.last[: min(n, 40)] = np.minimum(n - 1, far.first[: min(n, 40)] + 300)
+    cases["40 far-reaching"] = far
+    for name, t in cases.items():
+        print(f"case short trace of {n}, {name}, policy {policy}", flush=True)
+        off, peak = _plan(binding, t, policy=policy)
+        eo, ep = oracle.plan_trace(t.size, t.first, t.last, t.num_ops, policy)
+        assert np.array_equal(off, eo) and peak == ep
+
+
+@pytest.mark.parametrize("n", [4097, 20000])
+def test_one_workgroup_places(n):
+    """Traces deep and sparse enough for one placing workgroup (equal sizes
+    chaining in start order), with long-lived tensors that have most of the
+    window late, more than 64 gaps, and a preparation that places by itself
+    (more gaps than a hand-over holds)."""
+    binding = need_gpu()
+    rng = np.random.default_rng(330 + n)
+    ops = n // 25
+    first = np.sort(rng.integers(0, ops, n)).astype(np.int32)
+    last = np.minimum(ops - 1, first + rng.geometric(0.3, n) - 1).astype(np.int32)
+    last[rng.random(n) < 0.02] = ops - 1
+    size = 64 * rng.choice([1, 2, 3, 4, 5, 8, 20], n).astype(np.int64)
+    print(f"case chains of equal sizes, {n} tensors", flush=True)
+    _check(binding, tg.Trace(size, first, last, ops))
+    # alternate tensors of op 0 live on: as many one-unit gaps at op 1, met by
+    # chains of small tensors
+    k = n // 4
+    first = np.concatenate([np.zeros(2 * k), np.repeat(np.arange(1, 1 + (n - 2 * k) // 8 + 1), 8)[: n - 2 * k]])
+    first = first.astype(np.int32)
+    last = first.copy()
+    last[1:2 * k:2] = first.max()
+    last[2 * k:] = np.minimum(first.max(), first[2 * k:] + rng.integers(0, 3, n - 2 * k))
+    size = np.full(n, 64, np.int64)
+    size[2 * k::17] = 128
+    print(f"case {k} gaps, {n} tensors", flush=True)
+    _check(binding, tg.Trace(size, first, last, int(first.max()) + 1))
