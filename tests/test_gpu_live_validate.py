@@ -387,3 +387,28 @@ def test_validate_sorted_hint():
     binding.validate_plan(*_trace_dev(u), dev(np.zeros(u.n, np.int64), torch.int64),
                           capacity=1 << 16, assume_sorted=True, check=False, status=st)
     assert int(st.item()) == binding.MP_EINVAL  # promise broken
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 300_000])
+@pytest.mark.parametrize("ops", [4095, 4097, 50_000])
+def test_live_profile_windows(n, ops):
+    """Ops inside and outside the window a workgroup adds up before it writes
+    (4,096 ops from its first tensor's): in order, any order, all on one op,
+    long-lived, and down from the last op."""
+    binding = need_gpu()
+    rng = np.random.default_rng(n + ops)
+    f = rng.integers(0, ops, n).astype(np.int32)
+    size = rng.integers(1, 1 << 40, n).astype(np.int64) if n < 5000 else \
+        rng.integers(1, 1 << 20, n).astype(np.int64)
+    for name, first in (("in order", np.sort(f)), ("any order", f), ("one op", 0 * f + ops - 1),
+                        ("down", np.sort(f)[::-1].copy())):
+        for far in (False, True):
+            print(f"case live windows {n} tensors {ops} ops {name} {far}", flush=True)
+            last = np.minimum(ops - 1, first + rng.integers(0, ops if far else 3, n)).astype(np.int32)
+            live, mx = binding.live_bytes_profile(dev(size, torch.int64), dev(first, torch.int32),
+                                                  dev(last, torch.int32), ops)
+            d = np.zeros(ops + 1, np.int64)
+            np.add.at(d, first, size)
+            np.subtract.at(d, last + 1, size)
+            exp = np.cumsum(d)[:ops]
+            assert np.array_equal(host(live), exp) and int(mx.item()) == exp.max()
