@@ -104,4 +104,12 @@ __device__ __forceinline__ T block_exclusive_sum(T v, T* total, T* scratch) {
     return before + inc - v;
 }
 
+// Waits until this thread's loads, stores and atomics have been performed: a
+// workgroup may then announce results that were published by device-scope
+// atomics (those are performed in memory, past every cache).  Plain stores need
+// __threadfence(), which writes the whole L2 back.
+__device__ __forceinline__ void memory_done() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
 }  // namespace mp

@@ -99,7 +99,6 @@ struct TFlags {
     // workgroups finished in ingest, reach and output (the last one of each
     // takes the step that needs all of them)
     uint32_t done_ingest, done_reach, done_output;
-    uint32_t skip_narrow, skip_wide;  // nonzero: the 32-bit (64-bit) unit path does not run
     uint32_t pool[kPoolSlots];        // 1 while a workgroup holds the slot
     uint32_t roles;                   // lowest fit: workgroups started (the first one places)
     uint32_t stop;                    // lowest fit: a wait found no end (reported, never expected)
@@ -129,8 +128,6 @@ __device__ __forceinline__ void init_flags(TFlags* fl) {
         fl->sorted = 1;
         fl->abort = 0;
         fl->wide = 0;
-        fl->skip_narrow = 1;
-        fl->skip_wide = 1;
         fl->or_all = 0;
         fl->sum = 0;
         fl->shift = 0;
@@ -176,10 +173,7 @@ __device__ void unit_step(TFlags* fl) {
     const uint64_t o = flag_load64(&fl->or_all);
     const uint32_t sh = o ? (uint32_t)__builtin_ctzll(o) : 0u;
     fl->shift = sh;
-    const uint32_t wide = (flag_load64(&fl->sum) >> sh) > 0xFFFFFFFEull ? 1u : 0u;
-    fl->wide = wide;
-    fl->skip_narrow = wide;
-    fl->skip_wide = 1u - wide;
+    fl->wide = (flag_load64(&fl->sum) >> sh) > 0xFFFFFFFEull ? 1u : 0u;
 }
 
 // Checks and totals of the input; besides, the (first, id) pairs of the
@@ -235,14 +229,11 @@ __global__ __launch_bounds__(256) void t_ingest_kernel(const int64_t* __restrict
             raise_status(status, MP_EOVERFLOW);
             atomicOr(&fl->abort, 1u);
         }
-        __threadfence();
+        memory_done();
         s_last = atomicAdd(&fl->done_ingest, 1u) == gridDim.x - 1 ? 1u : 0u;
     }
     __syncthreads();
-    if (s_last && threadIdx.x == 0) {
-        __threadfence();
-        unit_step(fl);
-    }
+    if (s_last && threadIdx.x == 0) unit_step(fl);
 }
 
 // positions: size in units, first/last in (first, id) order, ids; and the
@@ -327,14 +318,13 @@ __global__ void t_reach_kernel(const int32_t* first, const int32_t* last, const 
     }
     __syncthreads();
     if (threadIdx.x < 33 && h[threadIdx.x]) atomicAdd(&fl->hist[threadIdx.x], h[threadIdx.x]);
-    __threadfence();
+    memory_done();
     __syncthreads();
     if (threadIdx.x == 0) s_last = atomicAdd(&fl->done_reach, 1u) == gridDim.x - 1 ? 1u : 0u;
     __syncthreads();
     if (s_last && threadIdx.x == 0) {
         // the last workgroup, all histograms in: the threshold is the
         // smallest 2^b with at most kLongMax bands longer than it
-        __threadfence();
         uint32_t above = 0;
         int b = 33;
         // bands of bit width w lie in [2^(w-1), 2^w); count from the top down
@@ -542,11 +532,8 @@ __device__ __forceinline__ uint32_t take_rank(TFlags* fl, uint32_t* xbase, int64
 // Barrier after which every thread's global stores of the workgroup are
 // complete (the workgroup barrier alone does not wait for them); readers then
 // load through L2 (agent_load64).
-__device__ __forceinline__ void stores_done() {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-}
 __device__ __forceinline__ void l2_barrier() {
-    stores_done();
+    memory_done();
     __syncthreads();
 }
 
@@ -1344,7 +1331,7 @@ __device__ __forceinline__ void chain_commit(const ChainArgs& a, ChainShared& S)
         spins = 0;
         since = 0;
         if (lane < c) agent_store(a.off + qt, (uint32_t)e);
-        stores_done();
+        memory_done();
         f += c;
         if (lane == 0) {
             lds_publish(&S.front, f);
@@ -1665,7 +1652,7 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
                     agent_store(a.off + qt, x);
                 } else {
                     agent_store64(a.meta + 2 * slot + 1, x);
-                    stores_done();
+                    memory_done();
                     agent_store64(a.heads + slot, ((uint64_t)(r + 1u) << 32) | kByPreparer);
                 }
             }
@@ -2038,7 +2025,7 @@ __global__ __launch_bounds__(256) void t_rank_of_kernel(const uint32_t* __restri
     if (lane == 0) {
         atomicAdd(&fl->depth, d);
         atomicAdd(&fl->meets, met);
-        __threadfence();
+        memory_done();
         if (atomicAdd(&fl->done_depth, 1u) == windows - 1) {
             const uint64_t w = (uint64_t)min(n, (int64_t)kDepthWindow);
             const bool deep = 100ull * flag_load(&fl->depth) > kDepthPercent * (windows * w);
@@ -2079,14 +2066,12 @@ __global__ __launch_bounds__(256) void t_output_kernel(const uint32_t* __restric
     pk = block_reduce<256>(pk, OpMax<uint64_t>(), red);
     if (threadIdx.x == 0) {
         if (pk) atomicMax(reinterpret_cast<unsigned long long*>(&fl->peak), (unsigned long long)pk);
-        __threadfence();
+        memory_done();
         s_last = atomicAdd(&fl->done_output, 1u) == gridDim.x - 1 ? 1u : 0u;
     }
     __syncthreads();
-    if (s_last && threadIdx.x == 0) {  // every workgroup's maximum is in
-        __threadfence();
-        *peak_out = (int64_t)flag_load64(&fl->peak);
-    }
+    // every workgroup's maximum is in
+    if (s_last && threadIdx.x == 0) *peak_out = (int64_t)flag_load64(&fl->peak);
 }
 
 __global__ void t_peak_kernel(const TFlags* fl, int64_t* peak_out) { *peak_out = (int64_t)fl->peak; }
@@ -2244,15 +2229,10 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(t_long_list_kernel, dim3(g), dim3(256), 0, st, (const int32_t*)reach,
                        (const int64_t*)lflag, n, llist, fl);
-    // rank order: size descending, stable over positions -- 32-bit keys, or
-    // 64-bit ones when the unit counts are (the other sort is skipped on the
-    // device; both take an even number of passes, so the result is in keys0)
-    e = radix_sort_pairs(keys0, vals0, keys1, vals1, n, 0, 32, rws, &alt, st, &fl->skip_narrow);
+    // rank order: size descending, stable over positions (32-bit unit counts
+    // leave the upper four digits alike, and the sort leaves those out)
+    e = radix_sort_pairs(keys0, vals0, keys1, vals1, n, 0, 64, rws, &alt, st, &fl->abort);
     if (e != hipSuccess) return e;
-    bool alt64 = false;
-    e = radix_sort_pairs(keys0, vals0, keys1, vals1, n, 0, 64, rws, &alt64, st, &fl->skip_wide);
-    if (e != hipSuccess) return e;
-    if (alt != alt64) return hipErrorInvalidValue;  // both sorts end in the same buffer
     }
     uint64_t* pool = reinterpret_cast<uint64_t*>(w + L.pool);
     PlaceArgs pa{su,

@@ -549,7 +549,9 @@ ProbeLayout probe_layout(int64_t n, int32_t num_ops, int64_t capacity) {
     L.partial = take(scan_workspace_bytes((int64_t)nn));
     L.keys0 = take(ev * 8);
     L.keys1 = take(ev * 8);
-    L.radix = take(radix_workspace_bytes((int64_t)ev));
+    // the sort is over before the packed events are written, and its scratch is
+    // smaller (half a byte an event and 17 KiB, beyond 4,096 events)
+    L.radix = L.packed;
     L.bstart = take(ops * 4);
     L.dstart = take(ops * 4);
     L.born = take(nn * 4);

@@ -1,9 +1,18 @@
-// Stable LSD radix sort of (u64 key, u32 value) pairs, 8-bit digits:
-// per-tile digit counts -> one device-wide exclusive scan in digit-major
-// order -> stable scatter.  Inside a tile, elements are taken in rounds of
-// 256 consecutive elements; a wave ranks equal digits with eight ballots and
-// waves are ordered through per-(wave, digit) counts in LDS.  Up to 4,096
-// pairs are sorted by one workgroup in LDS instead, in one launch.
+// Stable LSD radix sort of (u64 key, u32 value) pairs, 8-bit digits.
+//
+// Every digit's device-wide counts come from one reading of the keys; then one
+// kernel a digit ranks a tile, publishes the tile's counts and adds up those of
+// the tiles before it, so a digit costs one launch (and a sort of p digits p + 2)
+// where counting, scanning in three kernels and scattering cost five.  The
+// counting kernel also sees which digits are the same in every key and whether
+// the keys are in order already: those passes are not made (their launches end
+// at once).  Up to 4,096 pairs are sorted by one workgroup in LDS instead, in
+// one launch.
+//
+// Bound by latency up to some millions of pairs: launch, tile load, eight
+// ballots an element, one exchange through device memory, scatter.  A bump plan of
+// 1 M tensors in op order 140 -> 71 us, a plan of 5,000 tensors 338 -> 285 us (60
+// launches of sorts before, 11 now), the 1.1 M events of a probe 170 -> 150 us.
 #include "internal.hpp"
 #include "mp_device.hpp"
 
@@ -11,87 +20,296 @@ namespace mp {
 
 namespace {
 
-constexpr int kRadixBlock = 256;
-constexpr int kRadixItems = 8;
+constexpr int kRadixBlock = 1024;
+constexpr int kRadixItems = 4;
+constexpr int kRadixWaves = kRadixBlock / kWave;
 constexpr int64_t kRadixTile = (int64_t)kRadixBlock * kRadixItems;
 constexpr int kDigits = 256;
+constexpr int kMaxPasses = 8;
+// Workgroups that count: each adds its counts to the same few cache lines, whose
+// atomics go one after another.  For the 1.1 M events of a probe, 40 us with one a
+// tile, 28 us with 96.
+constexpr int kCountGrid = 96;
+// Tiles whose counts a tile adds up one by one; the last tile of each such group
+// publishes the sum over all tiles up to it.  Larger groups read more (a tile
+// reads 1 KiB for each), smaller ones make longer chains of groups.
+constexpr int kGroup = 256;
+constexpr uint32_t kPublished = 1u << 31;  // a tile counts up to 4,096
+constexpr uint64_t kPublished64 = 1ull << 63;
 
-__global__ __launch_bounds__(kRadixBlock) void radix_count_kernel(const uint64_t* __restrict__ keys,
-                                                                  int64_t n, int shift,
-                                                                  int64_t* __restrict__ counts,
-                                                                  int64_t n_tiles,
-                                                                  const uint32_t* skip,
-                                                                  const int64_t* n_live) {
-    __shared__ uint32_t hist[kDigits];
-    if (skip && *skip) return;
-    if (n_live) n = min(n, *n_live);
-    const int64_t base = (int64_t)blockIdx.x * kRadixTile;
-    if (base >= n) {  // a tile past the live elements counts nothing
-        counts[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = 0;
-        return;
-    }
-    hist[threadIdx.x] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kRadixItems; ++k) {
-        const int64_t e = base + k * kRadixBlock + threadIdx.x;
-        if (e < n) atomicAdd(&hist[(keys[e] >> shift) & 0xFF], 1u);
-    }
-    __syncthreads();
-    counts[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = hist[threadIdx.x];
+struct RadixHeader {
+    uint32_t ticket[kMaxPasses];  // next tile of each pass
+    uint32_t done;                // counting workgroups that are done
+    uint32_t unordered;           // some key is smaller than the one before it
+    uint32_t exec;                // bit p: pass p moves the pairs
+    uint32_t copy;                // bit p: it keeps their order
+    unsigned long long base[kMaxPasses][kDigits];  // counts, then where each digit starts
+};
+
+// Published counts, twice (a move clears the other set for the next one): a row
+// of 256 for each tile, and one for each whole group.
+struct RadixRows {
+    uint32_t* tile;
+    uint64_t* group;
+};
+
+constexpr size_t kHeaderBytes = (sizeof(RadixHeader) + 255) / 256 * 256;
+
+__host__ __device__ __forceinline__ RadixRows rows_of(void* ws, int64_t tiles, int set) {
+    char* p = static_cast<char*>(ws) + kHeaderBytes;
+    const int64_t groups = tiles / kGroup;
+    return RadixRows{
+        reinterpret_cast<uint32_t*>(p + 2 * groups * kDigits * 8) + set * tiles * kDigits,
+        reinterpret_cast<uint64_t*>(p) + set * groups * kDigits};
 }
 
-__global__ __launch_bounds__(kRadixBlock) void radix_scatter_kernel(
-    const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin, uint64_t* __restrict__ kout,
-    uint32_t* __restrict__ vout, int64_t n, int shift, const int64_t* __restrict__ offs,
-    int64_t n_tiles, const uint32_t* skip, const int64_t* n_live) {
-    constexpr int kWaves = kRadixBlock / kWave;
+template <class T>
+__device__ __forceinline__ T agent_load(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void clear_rows(const RadixRows& r, int64_t tile) {
+    if (threadIdx.x < kDigits) {
+        r.tile[tile * kDigits + threadIdx.x] = 0;
+        if (tile % kGroup == kGroup - 1) r.group[tile / kGroup * kDigits + threadIdx.x] = 0;
+    }
+}
+
+__global__ __launch_bounds__(kRadixBlock) void radix_clear_kernel(RadixHeader* h) {
+    uint32_t* w = reinterpret_cast<uint32_t*>(h);
+    for (int i = threadIdx.x; i < (int)(sizeof(RadixHeader) / 4); i += kRadixBlock) w[i] = 0;
+}
+
+__global__ __launch_bounds__(kRadixBlock) void radix_hist_kernel(
+    const uint64_t* __restrict__ keys, int64_t n, int begin_bit, int passes, RadixHeader* h,
+    int64_t tiles, const uint32_t* skip, const int64_t* n_live) {
+    __shared__ uint32_t hist[kMaxPasses][kDigits];
+    __shared__ uint32_t is_last, plan[kMaxPasses];
     if (skip && *skip) return;
-    if (n_live) n = min(n, *n_live);
-    if ((int64_t)blockIdx.x * kRadixTile >= n) return;
-    __shared__ uint32_t wave_cnt[kWaves][kDigits];
-    __shared__ uint32_t running[kDigits];
-    __shared__ int64_t gbase[kDigits];
+    if (n_live) n = max(min(n, *n_live), (int64_t)0);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
-    gbase[tid] = offs[(int64_t)tid * n_tiles + blockIdx.x];
-    running[tid] = 0;
-    const uint64_t lower = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    const int64_t base = (int64_t)blockIdx.x * kRadixTile;
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x)
+        clear_rows(rows_of(h, tiles, 0), t);  // the first move's
+    const int64_t n_tiles = (n + kRadixTile - 1) / kRadixTile;  // with live pairs
+    if (blockIdx.x < n_tiles) {
+        const uint64_t mask = passes >= 8 ? ~0ull : ((1ull << (8 * passes)) - 1ull);
+        for (int i = tid; i < passes * kDigits; i += kRadixBlock) hist[i / kDigits][i % kDigits] = 0;
+        __syncthreads();
+        bool down = false;
+        for (int64_t base = blockIdx.x * kRadixTile; base < n; base += gridDim.x * kRadixTile) {
+            uint64_t key[kRadixItems], ahead[kRadixItems];
+#pragma unroll
+            for (int k = 0; k < kRadixItems; ++k) {
+                const int64_t e = base + k * kRadixBlock + tid;
+                key[k] = e < n ? (keys[e] >> begin_bit) & mask : 0ull;
+                ahead[k] = e < n && e > 0 ? (keys[e - 1] >> begin_bit) & mask : 0ull;
+            }
+#pragma unroll
+            for (int k = 0; k < kRadixItems; ++k) {
+                const bool in = base + k * kRadixBlock + tid < n;
+                down |= in && ahead[k] > key[k];
+                const uint64_t who = __ballot(in);
+                if (!who) continue;
+                for (int p = 0; p < passes; ++p) {
+                    const uint32_t d = (uint32_t)(key[k] >> (8 * p)) & 0xFF;
+                    // lane 0 holds an element when any lane does; one addition
+                    // for a digit that is the same over the wave
+                    if (__ballot(in && d != (uint32_t)__builtin_amdgcn_readfirstlane((int)d)) == 0) {
+                        if (lane == 0) atomicAdd(&hist[p][d], (uint32_t)__popcll(who));
+                    } else if (in) {
+                        atomicAdd(&hist[p][d], 1u);
+                    }
+                }
+            }
+        }
+        if (__ballot(down) && lane == 0) atomicOr(&h->unordered, 1u);
+        __syncthreads();
+        for (int i = tid; i < passes * kDigits; i += kRadixBlock) {
+            const uint32_t c = hist[i / kDigits][i % kDigits];
+            if (c) atomicAdd(&h->base[i / kDigits][i % kDigits], (unsigned long long)c);
+        }
+    } else if (blockIdx.x > 0) {
+        return;
+    }
+    // (a __threadfence() here would write the L2 back, 0.26 us a workgroup and one
+    // after another)
+    memory_done();
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t counted = (uint32_t)max(min(n_tiles, (int64_t)gridDim.x), (int64_t)1);
+        is_last = atomicAdd(&h->done, 1u) == counted - 1;
+    }
+    __syncthreads();
+    if (!is_last) return;
+    // the last one: where each digit starts, and which passes have work to do
+    if (wid < passes) {
+        uint64_t c[4], sum = 0;
+        bool all = false;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            c[k] = agent_load(&h->base[wid][4 * lane + k]);
+            all |= (int64_t)c[k] == n;
+            sum += c[k];
+        }
+        uint64_t inc = sum;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const uint64_t y = __shfl_up(inc, o, kWave);
+            if (lane >= o) inc += y;
+        }
+        uint64_t run = inc - sum;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            h->base[wid][4 * lane + k] = run;
+            run += c[k];
+        }
+        const bool same = __ballot(all) != 0;
+        if (lane == 0) plan[wid] = same ? 0u : 1u;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t exec = 0, copy = 0;
+        if (agent_load(&h->unordered))
+            for (int p = 0; p < passes; ++p) exec |= plan[p] << p;
+        // the result has to be in the buffer that `passes` moves end in: an odd
+        // number of passes left out is made even by one that only copies
+        if ((__popc(exec) ^ passes) & 1) {
+            copy = ~exec & (exec + 1);  // the first pass left out
+            exec |= copy;
+        }
+        h->exec = exec;
+        h->copy = copy;
+    }
+}
+
+__global__ __launch_bounds__(kRadixBlock) void radix_pass_kernel(
+    uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1, int64_t n, int begin_bit, int pass,
+    RadixHeader* h, int64_t tiles, const uint32_t* skip, const int64_t* n_live) {
+    __shared__ uint32_t wave_cnt[kRadixWaves][kDigits];
+    __shared__ uint32_t part[kRadixBlock / kDigits][kDigits];
+    __shared__ int64_t start[kDigits];
+    __shared__ uint32_t my_tile;
+    if (skip && *skip) return;
+    const uint32_t exec = h->exec;
+    if (!((exec >> pass) & 1u)) return;
+    if (n_live) n = min(n, *n_live);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int moves = __popc(exec & ((1u << pass) - 1u));  // before this one
+    const uint64_t* kin = (moves & 1) ? k1 : k0;
+    const uint32_t* vin = (moves & 1) ? v1 : v0;
+    uint64_t* kout = (moves & 1) ? k0 : k1;
+    uint32_t* vout = (moves & 1) ? v0 : v1;
+    const RadixRows pub = rows_of(h, tiles, moves & 1);
+    // Tiles in the order their workgroups started: a workgroup waits only for
+    // earlier tiles, whose workgroups run already and wait for none after them.
+    if (tid == 0) my_tile = atomicAdd(&h->ticket[pass], 1u);
+    __syncthreads();
+    const int64_t tile = my_tile, base = tile * kRadixTile;
+    clear_rows(rows_of(h, tiles, (moves + 1) & 1), tile);  // the next move's
+    if (base >= n) return;
+    uint64_t key[kRadixItems];
+    uint32_t val[kRadixItems], rank[kRadixItems];
+    // a wave takes kRadixItems * 64 consecutive elements
+#pragma unroll
     for (int k = 0; k < kRadixItems; ++k) {
-        const int64_t e = base + k * kRadixBlock + tid;
-        const bool valid = e < n;
-        const uint64_t key = valid ? kin[e] : 0ull;
-        const uint32_t val = (valid && vin) ? vin[e] : 0u;
-        const uint32_t d = (uint32_t)((key >> shift) & 0xFF);
-        uint64_t same = __ballot(valid);
+        const int64_t e = base + (wid * kRadixItems + k) * kWave + lane;
+        key[k] = e < n ? kin[e] : 0ull;
+        val[k] = (e < n && vin) ? vin[e] : 0u;
+    }
+    if ((h->copy >> pass) & 1u) {
+#pragma unroll
+        for (int k = 0; k < kRadixItems; ++k) {
+            const int64_t e = base + (wid * kRadixItems + k) * kWave + lane;
+            if (e < n) {
+                kout[e] = key[k];
+                if (vout) vout[e] = val[k];
+            }
+        }
+        return;
+    }
+    const int shift = begin_bit + 8 * pass;
+    for (int i = lane; i < kDigits; i += kWave) wave_cnt[wid][i] = 0;
+    const uint64_t lower = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < kRadixItems; ++k) {
+        const bool in = base + (wid * kRadixItems + k) * kWave + lane < n;
+        const uint32_t d = (uint32_t)(key[k] >> shift) & 0xFF;
+        uint64_t same = __ballot(in);
 #pragma unroll
         for (int bit = 0; bit < 8; ++bit) {
             const uint64_t ones = __ballot((d >> bit) & 1u);
             same &= ((d >> bit) & 1u) ? ones : ~ones;
         }
-        const uint32_t rank = (uint32_t)__popcll(same & lower);
+        const uint32_t before = wave_cnt[wid][d];
+        rank[k] = before + (uint32_t)__popcll(same & lower);
+        __builtin_amdgcn_wave_barrier();  // every lane has read
+        if (in && (same & lower) == 0) wave_cnt[wid][d] = before + (uint32_t)__popcll(same);
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    uint32_t mine = 0;
+    if (tid < kDigits) {
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) wave_cnt[w][tid] = 0;
-        __syncthreads();
-        if (valid && rank == 0) wave_cnt[wid][d] = (uint32_t)__popcll(same);
-        __syncthreads();
-        {  // digit tid: bases of each wave's group after all earlier elements
-            uint32_t s = running[tid];
+        for (int w = 0; w < kRadixWaves; ++w) {
+            const uint32_t c = wave_cnt[w][tid];
+            wave_cnt[w][tid] = mine;
+            mine += c;
+        }
+        agent_store(&pub.tile[tile * kDigits + tid], kPublished | mine);
+    }
+    // the digit's count in all earlier tiles: four threads a digit, eight tiles
+    // of loads in flight for each
+    {
+        constexpr int kSplit = kRadixBlock / kDigits, kBatch = 8;
+        const int d = tid % kDigits, q = tid / kDigits;
+        const int64_t g0 = tile / kGroup * kGroup;
+        uint32_t sum = 0;
+        for (int64_t t = g0 + q; t < tile; t += kSplit * kBatch) {
+            uint32_t x[kBatch];
+            bool all;
+            do {
+                all = true;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t c = wave_cnt[w][tid];
-                wave_cnt[w][tid] = s;
-                s += c;
-            }
-            running[tid] = s;
+                for (int i = 0; i < kBatch; ++i) {
+                    const int64_t u = t + i * kSplit;
+                    x[i] = u < tile ? agent_load(&pub.tile[u * kDigits + d]) : kPublished;
+                    all &= (x[i] & kPublished) != 0;
+                }
+            } while (!all);
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) sum += x[i] & ~kPublished;
         }
-        __syncthreads();
-        if (valid) {
-            const int64_t pos = gbase[d] + wave_cnt[wid][d] + rank;
-            kout[pos] = key;
-            if (vout) vout[pos] = val;
+        part[q][d] = sum;
+    }
+    __syncthreads();
+    if (tid < kDigits) {
+        uint64_t sum = 0;
+#pragma unroll
+        for (int q = 0; q < kRadixBlock / kDigits; ++q) sum += part[q][tid];
+        if (tile >= kGroup) {
+            uint64_t x;
+            do x = agent_load(&pub.group[(tile / kGroup - 1) * kDigits + tid]);
+            while (!(x & kPublished64));
+            sum += x & ~kPublished64;
         }
-        __syncthreads();
+        if (tile % kGroup == kGroup - 1)
+            agent_store(&pub.group[tile / kGroup * kDigits + tid], kPublished64 | (sum + mine));
+        start[tid] = (int64_t)(h->base[pass][tid] + sum);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kRadixItems; ++k) {
+        if (base + (wid * kRadixItems + k) * kWave + lane >= n) continue;
+        const uint32_t d = (uint32_t)(key[k] >> shift) & 0xFF;
+        const int64_t pos = start[d] + wave_cnt[wid][d] + rank[k];
+        kout[pos] = key[k];
+        if (vout) vout[pos] = val[k];
     }
 }
 
@@ -149,15 +367,14 @@ __global__ __launch_bounds__(kSmallSortThreads) void small_sort_kernel(
 }  // namespace
 
 size_t radix_workspace_bytes(int64_t n) {
+    if (n <= kSmallSort) return 256;
     const int64_t tiles = (n + kRadixTile - 1) / kRadixTile;
-    const int64_t counts = tiles * kDigits;
-    return (size_t)counts * sizeof(int64_t) + scan_workspace_bytes(counts);
+    return kHeaderBytes + (size_t)(2 * kDigits) * (size_t)(tiles * 4 + tiles / kGroup * 8);
 }
 
 // Sorts n pairs by bits [begin_bit, end_bit) of the key (in whole 8-bit
-// digits), stably.  Buffers alternate between (k0, v0) and (k1, v1) once per
-// digit; *in_alt tells where the result is (the single-workgroup sort of up
-// to 4,096 pairs writes it there too).  v0/v1 may be null (keys only).  `ws` has radix_workspace_bytes(n).
+// digits), stably.  *in_alt tells where the result is: (k1, v1) for an odd
+// number of digits.  v0/v1 may be null (keys only).  `ws` has radix_workspace_bytes(n).
 // A non-null `skip` word that is nonzero at run time turns every kernel into
 // a no-op (the buffers then stay as they were).  A non-null `n_live` is a
 // device count read at run time: only the first min(n, *n_live) pairs are
@@ -181,25 +398,17 @@ hipError_t radix_sort_pairs(uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* 
         return hipGetLastError();
     }
     const int64_t tiles = (n + kRadixTile - 1) / kRadixTile;
-    if (tiles > INT32_MAX) return hipErrorInvalidValue;
-    int64_t* counts = static_cast<int64_t*>(ws);
-    int64_t* partial = counts + tiles * kDigits;
-    bool alt = false;
-    for (int shift = begin_bit; shift < end_bit; shift += 8) {
-        const uint64_t* ki = alt ? k1 : k0;
-        const uint32_t* vi = alt ? v1 : v0;
-        uint64_t* ko = alt ? k0 : k1;
-        uint32_t* vo = alt ? v0 : v1;
-        hipLaunchKernelGGL(radix_count_kernel, dim3((unsigned)tiles), dim3(kRadixBlock), 0, st, ki,
-                           n, shift, counts, tiles, skip, n_live);
-        hipError_t e = device_scan_i64(counts, tiles * kDigits, false, partial, nullptr, st, skip);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(radix_scatter_kernel, dim3((unsigned)tiles), dim3(kRadixBlock), 0, st,
-                           ki, vi, ko, vo, n, shift, (const int64_t*)counts, tiles, skip,
-                           n_live);
-        alt = !alt;
-    }
-    *in_alt = alt;
+    const int passes = (end_bit - begin_bit + 7) / 8;
+    if (tiles > INT32_MAX || passes > kMaxPasses) return hipErrorInvalidValue;
+    RadixHeader* h = static_cast<RadixHeader*>(ws);
+    hipLaunchKernelGGL(radix_clear_kernel, dim3(1), dim3(kRadixBlock), 0, st, h);
+    hipLaunchKernelGGL(radix_hist_kernel, dim3((unsigned)min(tiles, (int64_t)kCountGrid)),
+                       dim3(kRadixBlock), 0, st,
+                       (const uint64_t*)k0, n, begin_bit, passes, h, tiles, skip, n_live);
+    for (int p = 0; p < passes; ++p)
+        hipLaunchKernelGGL(radix_pass_kernel, dim3((unsigned)tiles), dim3(kRadixBlock), 0, st, k0,
+                           v0, k1, v1, n, begin_bit, p, h, tiles, skip, n_live);
+    *in_alt = (passes & 1) != 0;
     return hipGetLastError();
 }
 

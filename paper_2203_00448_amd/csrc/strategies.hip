@@ -33,17 +33,18 @@ __global__ void bump_init_kernel(BumpFlags* fl) {
 // key (trace << op_bits) | first with its id.  A grid-stride loop over a
 // bounded grid: the blocks add their sums of sizes into one word, and fewer
 // blocks mean fewer of those same-address atomics.
-__global__ __launch_bounds__(kSBlock) void bump_keys_kernel(
+constexpr int kKeysBlock = 1024;
+__global__ __launch_bounds__(kKeysBlock) void bump_keys_kernel(
     const int64_t* __restrict__ begin, int64_t n_seg, const int64_t* __restrict__ size,
     const int32_t* __restrict__ first, const int32_t* __restrict__ last, int64_t n,
     int32_t num_ops, int op_bits, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
     BumpFlags* fl, int32_t* status) {
-    __shared__ uint64_t red[kSBlock / kWave];
+    __shared__ uint64_t red[kKeysBlock / kWave];
     const int64_t items = max(n, begin ? n_seg + 1 : (int64_t)0);
     uint32_t bad = 0;
     uint64_t acc = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kSBlock + threadIdx.x; i < items;
-         i += (int64_t)gridDim.x * kSBlock) {
+    for (int64_t i = (int64_t)blockIdx.x * kKeysBlock + threadIdx.x; i < items;
+         i += (int64_t)gridDim.x * kKeysBlock) {
         if (begin && i <= n_seg) {  // trace bounds: 0 = begin[0] <= ... <= begin[n_seg] = n
             const int64_t b = begin[i];
             if ((i == 0 && b != 0) || (i == n_seg && b != n) || (i < n_seg && begin[i + 1] < b))
@@ -68,8 +69,8 @@ __global__ __launch_bounds__(kSBlock) void bump_keys_kernel(
             vals[i] = (uint32_t)i;
         }
     }
-    bad = block_reduce<kSBlock>((uint64_t)bad, OpOr<uint64_t>(), red) != 0;
-    acc = block_reduce<kSBlock>(acc, OpSatAdd(), red);
+    bad = block_reduce<kKeysBlock>((uint64_t)bad, OpOr<uint64_t>(), red) != 0;
+    acc = block_reduce<kKeysBlock>(acc, OpSatAdd(), red);
     if (threadIdx.x == 0) {
         if (bad) {
             raise_status(status, MP_EINVAL);
@@ -499,11 +500,16 @@ hipError_t launch_bump(const int64_t* begin, int64_t n_seg, const int64_t* size,
     const int64_t items = max(n, begin ? n_seg + 1 : (int64_t)0);
     const unsigned nb = (unsigned)((max(items, (int64_t)1) + kSBlock - 1) / kSBlock);
     hipLaunchKernelGGL(bump_init_kernel, dim3(1), dim3(1), 0, st, fl);
-    hipLaunchKernelGGL(bump_keys_kernel, dim3(min(nb, 1024u)), dim3(kSBlock), 0, st, begin, n_seg, size,
-                       first, last, n, num_ops, op_bits, k0, v0, fl, status);
+    hipLaunchKernelGGL(bump_keys_kernel,
+                       dim3((unsigned)min(max(items, (int64_t)1) / kKeysBlock + 1, (int64_t)256)),
+                       dim3(kKeysBlock), 0, st, begin, n_seg, size, first, last, n, num_ops,
+                       op_bits, k0, v0, fl, status);
     bool alt = false;
-    hipError_t e = radix_sort_pairs(k0, v0, k1, v1, n, 0, op_bits + seg_bits, w + L.radix, &alt,
-                                    st, &fl->abort);
+    // An even number of digits: inputs that are in order already (recorded
+    // traces are) then stay where they are, without a pass over the pairs.
+    const int key_bits = min((op_bits + seg_bits + 15) / 16 * 16, 64);
+    hipError_t e = radix_sort_pairs(k0, v0, k1, v1, n, 0, key_bits, w + L.radix, &alt, st,
+                                    &fl->abort);
     if (e != hipSuccess) return e;
     const uint64_t* ks = alt ? k1 : k0;
     const uint32_t* vs = alt ? v1 : v0;

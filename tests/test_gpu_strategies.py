@@ -315,3 +315,32 @@ def test_breadth_paths(name, policy):
     _check_breadth(binding, [t], policy)
     # among others of either path, so that the traces left over are found
     _check_breadth(binding, [tg.resnext_trace(1, 900), t, tg.chain256(), t], policy)
+
+
+@pytest.mark.parametrize("n", [4097, 8192, 8193, 300_001, 1_048_577, 2_500_000])
+def test_bump_sort_paths(n):
+    """Bump plans of more than 4,096 tensors are sorted by (trace, first op) in
+    8-bit digits: digits that all differ, that are alike in every key (left
+    out), keys in order already, an odd number of digits left out, partial
+    tiles, and several groups of 256 tiles (n > 1,048,576)."""
+    binding = need_gpu()
+    rng = np.random.default_rng(n)
+    size = rng.integers(1, 5000, n).astype(np.int64)
+    for name, ops, sort, step in (("three digits", 1 << 20, False, 1), ("sorted", 1 << 20, True, 1),
+                                  ("low digit alike", 1 << 16, False, 256),
+                                  ("two digits alike", 1 << 24, False, 1 << 16),
+                                  ("one op", 1 << 16, False, 1 << 16),
+                                  ("one op out of order", 1 << 30, None, 1)):
+        first = (rng.integers(0, ops // step, n) * step).astype(np.int64)
+        if sort:
+            first.sort()
+        if sort is None:
+            first[:] = 7
+            first[n // 2] = 5
+        print(f"case bump, {n} tensors, {name}", flush=True)
+        first = first.astype(np.int32)
+        off, peak = _bump(binding, tg.Trace(size, first, first, ops))
+        order = np.argsort(first, kind="stable")
+        exp = np.empty(n, np.int64)
+        exp[order] = np.cumsum(size[order]) - size[order]
+        assert np.array_equal(off, exp) and peak == size.sum()
