@@ -29,6 +29,10 @@ constexpr int kChunkRows = 64;                      // long rows per chunk (one 
 constexpr int kTileItems = 4;                       // candidates per thread per tile
 constexpr int64_t kTileJ = kVBlock * kTileItems;    // candidates per tile
 constexpr unsigned kTileGrid = 2048;                // workgroups of the count pass (tile ranges)
+constexpr int kWriteBlock = 1024;
+// Candidates up to which a wave writes a row alone (four rounds of its loads, no
+// exchange); more are split over the workgroup's 16 waves.
+constexpr int64_t kWaveRow = 2048;
 constexpr int kWriteUnroll = 8;                     // candidate loads in flight per lane (write pass)
 
 // Workspace words.
@@ -422,22 +426,24 @@ __global__ __launch_bounds__(kVBlock) void v_tile_kernel(
                             cnt);
 }
 
-// Write pass of the long rows that have pairs.  The workgroup checks 256 of
+// Write pass of the long rows that have pairs.  The workgroup checks 1,024 of
 // its long rows at once (rows b, b + G, b + 2G, ... for workgroup b of G, so
 // that neighbours in class order, often alike, land in different
-// workgroups) and lists those with pairs; then each listed row is
-// written by the whole workgroup: each wave takes a contiguous quarter of the
-// band, counts its hits, and after an exchange of the four counts writes them
-// in j order.  Rows write disjoint ranges, so the list order is free.
-__global__ __launch_bounds__(kVBlock) void v_long_write_kernel(
+// workgroups) and lists those with pairs.  Each listed row of up to kWaveRow
+// candidates is written by one wave; each longer one by the whole workgroup:
+// each wave takes a contiguous part of the band, counts its hits, and after an
+// exchange of the counts writes them in j order.  Rows write disjoint ranges,
+// so the list order is free.  Bound by the chain of loads over the longest band:
+// 100 rows of up to 100,000 candidates 99 us with four waves a row, 49 us with 16.
+__global__ __launch_bounds__(kWriteBlock) void v_long_write_kernel(
     const int32_t* first, const int32_t* last, const int64_t* off, const int64_t* size,
     const int32_t* pf, const int32_t* pl, const int64_t* po, const int64_t* ps,
     const uint32_t* pid, const int32_t* __restrict__ reach, const int64_t* __restrict__ cnt,
     const uint32_t* __restrict__ sorted, int64_t n, const VFlags* fl,
     int64_t* __restrict__ pairs, int64_t cap) {
-    constexpr int kWaves = kVBlock / kWave;
+    constexpr int kWaves = kWriteBlock / kWave;
     __shared__ uint32_t wcnt[2][kWaves];
-    __shared__ int32_t list[kVBlock];
+    __shared__ int32_t list[kWriteBlock];
     __shared__ uint32_t n_list;
     const VArrays a = pick_arrays(fl, first, last, off, size, pf, pl, po, ps, pid);
     const int64_t n_long = fl->n_long;
@@ -445,7 +451,7 @@ __global__ __launch_bounds__(kVBlock) void v_long_write_kernel(
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     int buf = 0;
     const int64_t G = gridDim.x;
-    for (int64_t base = blockIdx.x; base < n_long; base += G * kVBlock) {
+    for (int64_t base = blockIdx.x; base < n_long; base += G * kWriteBlock) {
         if (tid == 0) n_list = 0;
         __syncthreads();
         const int64_t k = base + tid * G;
@@ -456,10 +462,38 @@ __global__ __launch_bounds__(kVBlock) void v_long_write_kernel(
         }
         __syncthreads();
         const uint32_t listed = n_list;
+        // the pairs of row q among [s0, s1), from `pos` on, until `left` are found
+        auto write_row = [&](int64_t q, int64_t oq, int64_t sq, int64_t s0, int64_t s1, int64_t pos,
+                             int64_t left) {
+            for (int64_t j0 = s0; left > 0 && j0 < s1; j0 += kWave * kWriteUnroll) {
+                int64_t jo[kWriteUnroll], js[kWriteUnroll];
+#pragma unroll
+                for (int u = 0; u < kWriteUnroll; ++u) {
+                    const int64_t j = j0 + u * kWave + lane;
+                    jo[u] = j < s1 ? a.off[j] : 0;
+                    js[u] = j < s1 ? a.size[j] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < kWriteUnroll; ++u) {
+                    const int64_t j = j0 + u * kWave + lane;
+                    const bool h = j < s1 && bytes_meet(oq, sq, jo[u], js[u]);
+                    const uint64_t m = __ballot(h);
+                    if (h) put_pair(pairs, pos + lanes_below(m), cap, a, q, j);
+                    pos += __popcll(m);
+                    left -= __popcll(m);
+                }
+            }
+        };
+        for (uint32_t li = (uint32_t)wid; li < listed; li += kWaves) {
+            const int64_t q = list[li], r = reach[q];
+            if (r - q - 1 <= kWaveRow)
+                write_row(q, a.off[q], a.size[q], q + 1, r, cnt[q], cnt[q + 1] - cnt[q]);
+        }
         for (uint32_t li = 0; li < listed; ++li) {
             const int64_t q = list[li];
             const int64_t start = cnt[q];
             const int64_t r = reach[q];
+            if (r - q - 1 <= kWaveRow) continue;
             const int64_t oq = a.off[q], sq = a.size[q];
             const int64_t seg = ((r - q - 1 + kWaves * kWave - 1) / (kWaves * kWave)) * kWave;
             const int64_t s0 = q + 1 + wid * seg;
@@ -484,24 +518,7 @@ __global__ __launch_bounds__(kVBlock) void v_long_write_kernel(
             int64_t pos = start;
             for (int w = 0; w < wid; ++w) pos += wcnt[buf][w];
             buf ^= 1;  // the next row's exchange uses the other buffer
-            for (int64_t j0 = s0; mine > 0 && j0 < s1; j0 += kWave * kWriteUnroll) {
-                int64_t jo[kWriteUnroll], js[kWriteUnroll];
-#pragma unroll
-                for (int u = 0; u < kWriteUnroll; ++u) {
-                    const int64_t j = j0 + u * kWave + lane;
-                    jo[u] = j < s1 ? a.off[j] : 0;
-                    js[u] = j < s1 ? a.size[j] : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < kWriteUnroll; ++u) {
-                    const int64_t j = j0 + u * kWave + lane;
-                    const bool h = j < s1 && bytes_meet(oq, sq, jo[u], js[u]);
-                    const uint64_t m = __ballot(h);
-                    if (h) put_pair(pairs, pos + lanes_below(m), cap, a, q, j);
-                    pos += __popcll(m);
-                    mine -= (uint32_t)__popcll(m);
-                }
-            }
+            write_row(q, oq, sq, s0, s1, pos, mine);
         }
         __syncthreads();  // the list and n_list are rewritten for the next rows
     }
@@ -1138,7 +1155,7 @@ hipError_t launch_validate(const int64_t* begin, int64_t n_seg, const int64_t* s
                            (const int32_t*)pf, (const int32_t*)pl, (const int64_t*)po,
                            (const int64_t*)ps, (const uint32_t*)pid, (const int32_t*)segend, n,
                            reach, cnt, keys0, vals0, fl, 1, pairs, cap);
-        hipLaunchKernelGGL(v_long_write_kernel, dim3(kLongGrid), dim3(kVBlock), 0, st, first,
+        hipLaunchKernelGGL(v_long_write_kernel, dim3(kLongGrid), dim3(kWriteBlock), 0, st, first,
                            last, off, size, (const int32_t*)pf, (const int32_t*)pl,
                            (const int64_t*)po, (const int64_t*)ps, (const uint32_t*)pid,
                            (const int32_t*)reach, (const int64_t*)cnt, sorted, n,

@@ -412,3 +412,25 @@ def test_live_profile_windows(n, ops):
             np.subtract.at(d, last + 1, size)
             exp = np.cumsum(d)[:ops]
             assert np.array_equal(host(live), exp) and int(mx.item()) == exp.max()
+
+
+@pytest.mark.parametrize("band", [65, 2047, 2048, 2049, 16384, 16385, 20000])
+def test_validate_write_row_edges(band):
+    """Long rows on both sides of what one wave writes alone (2,048 candidates)
+    and of one round of a workgroup's loads (16 waves of 512), with pairs at the
+    ends of the band, in few and in many rows."""
+    binding = need_gpu()
+    n = band + 40
+    first = np.arange(n, dtype=np.int32)
+    for rows in (1, 40):
+        last = first.copy()
+        last[:rows] = np.minimum(n - 1, first[:rows] + band)
+        t = tg.Trace(np.full(n, 64, np.int64), first, last, n)
+        off = 64 * np.arange(n, dtype=np.int64)
+        for j in (rows, band // 2, band - 1, band, n - 1):
+            off[j] = 32
+        ep, ec = _oracle_pairs(t, off)
+        print(f"case rows of {band} candidates, {rows} of them ({ec} conflicts)", flush=True)
+        for cap in (ec, max(ec - 1, 1)):
+            gp, gc, st = _gpu_pairs(binding, t, off, capacity=cap)
+            assert gc == ec and np.array_equal(gp, ep[:cap])
