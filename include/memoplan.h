@@ -107,9 +107,13 @@ int32_t mp_plan_batch(const int64_t* begin, int64_t n_traces, const int32_t* num
 int64_t mp_batch_pair_capacity(int64_t max_trace_len);
 
 /* Greedy-by-size plan of one trace of any length, using the whole device
- * (a persistent kernel: workgroups take tensors in rank order, in blocks of
- * 32 consecutive ranks per XCD, and each fits its tensor once the
- * earlier-ranked tensors that meet it are placed).
+ * (a persistent kernel, in one of two forms chosen on the device: workgroups
+ * take tensors in rank order, in blocks of 32 consecutive ranks per XCD, and
+ * each fits its tensor once the earlier-ranked tensors that meet it are
+ * placed; or, lowest fit on deep and sparse traces, one workgroup places the
+ * tensors that the others prepare).  Traces of at most
+ * MP_BATCH_MAX_TRACE_LEN tensors are planned by mp_plan_batch's kernel when
+ * it can hold them.  The plan is the same in every form.
  *   size, first, last [n] (int64, int32, int32), 0 <= n < 2^30.
  *   offset_out[n] int64, peak_out: one device int64 (arena bytes).
  *   policy: MP_LOWEST_FIT or MP_BEST_FIT.

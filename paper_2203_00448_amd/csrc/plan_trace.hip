@@ -14,25 +14,31 @@
 //              chosen from a histogram of band lengths, so that the other
 //              tensors meeting t from behind lie in a short window before t
 //   rank       stable radix sort by size descending over positions
-//   place      persistent kernel.  Lowest fit: one workgroup places every
-//              tensor, the others prepare them in rank order ahead of it.  To
-//              prepare tensor t a workgroup walks t's candidates (forward
-//              band, backward window, long list), keeps those ranked before
-//              t, turns the already placed ones into one run of ranges by
-//              offset (their union through a coverage bitmap, or an LDS
-//              bitonic sort with prefix maxima of the ends) and hands over the
-//              run's gaps that hold t and the ranks still to be placed.  The
-//              placing workgroup's waves take the tensors in rank order and
-//              keep each one's lowest fit up to date while the late ranks
-//              arrive, in its own LDS.  A preparation waits for nothing but
-//              the placement to come within a window of ranks.
-//              BEST_FIT: every workgroup takes a rank, waits for its
-//              predecessors and fits it; ranks are taken in blocks of 32 per
-//              XCD, so that most links (usually rank r - 1 to rank r) stay
-//              inside one L2.  Either way a tensor only waits on lower ranks,
-//              each held by a running workgroup or taken once one finishes,
-//              so the schedule cannot deadlock.
+//   place      persistent kernel, in one of two forms.  To prepare tensor t a
+//              workgroup walks t's candidates (forward band, backward window,
+//              long list), keeps those ranked before t and turns the already
+//              placed ones into one run of ranges by offset (their union
+//              through a coverage bitmap, or an LDS bitonic sort with prefix
+//              maxima of the ends).
+//              Each its own (BEST_FIT, and lowest fit on wide or shallow
+//              traces): every workgroup takes a rank, prepares it, waits for
+//              its late predecessors and fits it; ranks are taken in blocks of
+//              32 per XCD, so that most links (usually rank r - 1 to rank r)
+//              stay inside one L2.
+//              Chain (lowest fit on deep, sparse traces): one workgroup places
+//              every tensor, the others prepare them in rank order ahead of it
+//              and hand over the run's gaps that hold t and the ranks still to
+//              be placed.  The placing workgroup's waves take the tensors in
+//              rank order and keep each one's lowest fit up to date while the
+//              late ranks arrive, in its own LDS.  A preparation waits for
+//              nothing but the placement to come within a window of ranks.
+//              Either way a tensor only waits on lower ranks, each held by a
+//              running workgroup or taken once one finishes, so the schedule
+//              cannot deadlock.
 //   output     offsets (scaled back to bytes) and the peak.
+//
+// Traces of up to 4,096 tensors go to the batched planner's kernel first, and
+// those it leaves are prepared by one workgroup in one launch.
 #include <type_traits>
 #ifdef MP_DEBUG_WAIT
 #include <stdlib.h>
@@ -46,12 +52,12 @@ namespace mp {
 
 namespace {
 
-constexpr int kTBlock = 512;      // BEST_FIT and the 64-bit path
-constexpr int kChainBlock = 1024; // lowest fit: 16 placing waves
+constexpr int kTBlock = 512;      // workgroups that place their own ranks
+constexpr int kChainBlock = 1024; // the chain form: 16 waves
 constexpr int kRunCap = 16384;    // ranges sorted at once in LDS
-// Predecessors still unplaced when t is examined (late).  Lowest fit: a
+// Predecessors still unplaced when t is examined (late).  Chain: a
 // preparation starts at most kAhead ranks ahead of the front (every rank below
-// the front is placed), so there are fewer than kAhead.  BEST_FIT: each is held
+// the front is placed), so there are fewer than kAhead.  Each its own: each is held
 // by another running workgroup (one rank at a time per workgroup) or is still
 // untaken in another XCD's current block (see kTicketBlock), so there are fewer
 // than the grid + kXcdGroups * (kTicketBlock - 1); the host keeps the grid at
