@@ -16,8 +16,11 @@ namespace mp {
 
 namespace {
 
-constexpr int kLiveBlock = 1024;
-constexpr int kLiveGrid = 256;      // workgroups add to one word: few, one a CU
+// Workgroups add to one word, so there are few, one a CU.  Up to a tensor for
+// each thread of 256 small ones there is no window: the few atomics go to memory
+// at once, where the window's two barriers cost 2 us.
+constexpr int kLiveGrid = 256;
+constexpr int kLiveSmall = 256, kLiveLarge = 1024;
 constexpr int kLiveWindow = 4096;   // ops
 
 __global__ void live_init_kernel(int64_t* __restrict__ live, int32_t num_ops,
@@ -31,23 +34,29 @@ __global__ void live_init_kernel(int64_t* __restrict__ live, int32_t num_ops,
     }
 }
 
-__global__ __launch_bounds__(kLiveBlock) void live_delta_kernel(
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void live_delta_kernel(
     const int64_t* __restrict__ size, const int32_t* __restrict__ first,
     const int32_t* __restrict__ last, int64_t n, int32_t num_ops, int64_t* __restrict__ live,
     uint64_t* __restrict__ sum, int32_t* __restrict__ status) {
-    __shared__ uint64_t red[kLiveBlock / kWave];
-    __shared__ unsigned long long win[kLiveWindow];
+    __shared__ uint64_t red[BLOCK / kWave];
+    constexpr bool kWindow = BLOCK == kLiveLarge;
+    __shared__ unsigned long long win[kWindow ? kLiveWindow : 1];
     const int64_t lo = n * blockIdx.x / gridDim.x, hi = n * (blockIdx.x + 1) / gridDim.x;
     uint32_t bad = 0;
     uint64_t acc = 0;
-    for (int w = threadIdx.x; w < kLiveWindow; w += kLiveBlock) win[w] = 0;
-    const int32_t base = lo < hi ? max(first[lo], 0) : 0;
-    __syncthreads();
+    int32_t base = 0, window = 0;
+    if constexpr (kWindow) {
+        base = lo < hi ? min(max(first[lo], 0), num_ops) : 0;
+        window = min(kLiveWindow, num_ops - base);
+        for (int w = threadIdx.x; w < window; w += BLOCK) win[w] = 0;
+        __syncthreads();
+    }
     auto add = [&](int32_t t, unsigned long long v) {
-        if (t >= base && t - base < kLiveWindow) atomicAdd(&win[t - base], v);
+        if (kWindow && t >= base && t - base < window) atomicAdd(&win[t - base], v);
         else atomicAdd(reinterpret_cast<unsigned long long*>(live + t), v);
     };
-    for (int64_t i = lo + threadIdx.x; i < hi; i += kLiveBlock) {
+    for (int64_t i = lo + threadIdx.x; i < hi; i += BLOCK) {
         const int64_t s = size[i];
         const int32_t f = first[i], l = last[i];
         if (s <= 0 || f < 0 || f > l || l >= num_ops) {
@@ -59,11 +68,11 @@ __global__ __launch_bounds__(kLiveBlock) void live_delta_kernel(
         add(f, (unsigned long long)s);
         if (l + 1 < num_ops) add(l + 1, (unsigned long long)(-s));
     }
-    __syncthreads();
-    for (int w = threadIdx.x; w < kLiveWindow; w += kLiveBlock)
+    if constexpr (kWindow) __syncthreads();
+    for (int w = threadIdx.x; w < window; w += BLOCK)
         if (win[w]) atomicAdd(reinterpret_cast<unsigned long long*>(live + base + w), win[w]);
-    bad = block_reduce<kLiveBlock>(bad, OpOr<uint32_t>(), reinterpret_cast<uint32_t*>(red));
-    acc = block_reduce<kLiveBlock>(acc, OpSatAdd(), red);
+    bad = block_reduce<BLOCK>(bad, OpOr<uint32_t>(), reinterpret_cast<uint32_t*>(red));
+    acc = block_reduce<BLOCK>(acc, OpSatAdd(), red);
     if (threadIdx.x == 0) {
         if (bad) raise_status(status, MP_EINVAL);
         // global saturating sum: once past INT64_MAX the overflow is reported
@@ -90,10 +99,13 @@ hipError_t launch_live_profile(const int64_t* size, const int32_t* first, const 
     hipLaunchKernelGGL(live_init_kernel, dim3(init_grid), dim3(256), 0, st, live_out, num_ops,
                        max_out, sum);
     if (n > 0) {
-        const int64_t g = (n + kLiveBlock - 1) / kLiveBlock;
-        const unsigned grid = (unsigned)(g < kLiveGrid ? g : kLiveGrid);
-        hipLaunchKernelGGL(live_delta_kernel, dim3(grid), dim3(kLiveBlock), 0, st, size, first,
-                           last, n, num_ops, live_out, sum, status);
+        const int64_t g = (n + kLiveSmall - 1) / kLiveSmall;
+        if (g <= kLiveGrid)
+            hipLaunchKernelGGL(live_delta_kernel<kLiveSmall>, dim3((unsigned)g), dim3(kLiveSmall), 0,
+                               st, size, first, last, n, num_ops, live_out, sum, status);
+        else
+            hipLaunchKernelGGL(live_delta_kernel<kLiveLarge>, dim3(kLiveGrid), dim3(kLiveLarge), 0,
+                               st, size, first, last, n, num_ops, live_out, sum, status);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

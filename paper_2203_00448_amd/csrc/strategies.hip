@@ -33,18 +33,19 @@ __global__ void bump_init_kernel(BumpFlags* fl) {
 // key (trace << op_bits) | first with its id.  A grid-stride loop over a
 // bounded grid: the blocks add their sums of sizes into one word, and fewer
 // blocks mean fewer of those same-address atomics.
-constexpr int kKeysBlock = 1024;
-__global__ __launch_bounds__(kKeysBlock) void bump_keys_kernel(
+constexpr unsigned kKeysGrid = 256;
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void bump_keys_kernel(
     const int64_t* __restrict__ begin, int64_t n_seg, const int64_t* __restrict__ size,
     const int32_t* __restrict__ first, const int32_t* __restrict__ last, int64_t n,
     int32_t num_ops, int op_bits, uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
     BumpFlags* fl, int32_t* status) {
-    __shared__ uint64_t red[kKeysBlock / kWave];
+    __shared__ uint64_t red[BLOCK / kWave];
     const int64_t items = max(n, begin ? n_seg + 1 : (int64_t)0);
     uint32_t bad = 0;
     uint64_t acc = 0;
-    for (int64_t i = (int64_t)blockIdx.x * kKeysBlock + threadIdx.x; i < items;
-         i += (int64_t)gridDim.x * kKeysBlock) {
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < items;
+         i += (int64_t)gridDim.x * BLOCK) {
         if (begin && i <= n_seg) {  // trace bounds: 0 = begin[0] <= ... <= begin[n_seg] = n
             const int64_t b = begin[i];
             if ((i == 0 && b != 0) || (i == n_seg && b != n) || (i < n_seg && begin[i + 1] < b))
@@ -69,8 +70,8 @@ __global__ __launch_bounds__(kKeysBlock) void bump_keys_kernel(
             vals[i] = (uint32_t)i;
         }
     }
-    bad = block_reduce<kKeysBlock>((uint64_t)bad, OpOr<uint64_t>(), red) != 0;
-    acc = block_reduce<kKeysBlock>(acc, OpSatAdd(), red);
+    bad = block_reduce<BLOCK>((uint64_t)bad, OpOr<uint64_t>(), red) != 0;
+    acc = block_reduce<BLOCK>(acc, OpSatAdd(), red);
     if (threadIdx.x == 0) {
         if (bad) {
             raise_status(status, MP_EINVAL);
@@ -500,10 +501,12 @@ hipError_t launch_bump(const int64_t* begin, int64_t n_seg, const int64_t* size,
     const int64_t items = max(n, begin ? n_seg + 1 : (int64_t)0);
     const unsigned nb = (unsigned)((max(items, (int64_t)1) + kSBlock - 1) / kSBlock);
     hipLaunchKernelGGL(bump_init_kernel, dim3(1), dim3(1), 0, st, fl);
-    hipLaunchKernelGGL(bump_keys_kernel,
-                       dim3((unsigned)min(max(items, (int64_t)1) / kKeysBlock + 1, (int64_t)256)),
-                       dim3(kKeysBlock), 0, st, begin, n_seg, size, first, last, n, num_ops,
-                       op_bits, k0, v0, fl, status);
+    if (nb <= kKeysGrid)
+        hipLaunchKernelGGL(bump_keys_kernel<kSBlock>, dim3(nb), dim3(kSBlock), 0, st, begin, n_seg,
+                           size, first, last, n, num_ops, op_bits, k0, v0, fl, status);
+    else
+        hipLaunchKernelGGL(bump_keys_kernel<1024>, dim3(kKeysGrid), dim3(1024), 0, st, begin, n_seg,
+                           size, first, last, n, num_ops, op_bits, k0, v0, fl, status);
     bool alt = false;
     // An even number of digits: inputs that are in order already (recorded
     // traces are) then stay where they are, without a pass over the pairs.

@@ -317,7 +317,7 @@ def test_breadth_paths(name, policy):
     _check_breadth(binding, [tg.resnext_trace(1, 900), t, tg.chain256(), t], policy)
 
 
-@pytest.mark.parametrize("n", [4097, 8192, 8193, 300_001, 1_048_577, 2_500_000])
+@pytest.mark.parametrize("n", [4097, 8192, 8193, 16_384, 16_385, 300_001, 1_048_577, 2_500_000])
 def test_bump_sort_paths(n):
     """Bump plans of more than 4,096 tensors are sorted by (trace, first op) in
     8-bit digits: digits that all differ, that are alike in every key (left
