@@ -113,7 +113,9 @@ int64_t mp_batch_pair_capacity(int64_t max_trace_len);
  * placed; or, lowest fit on deep and sparse traces, one workgroup places the
  * tensors that the others prepare).  Traces of at most
  * MP_BATCH_MAX_TRACE_LEN tensors are planned by mp_plan_batch's kernel when
- * it can hold them.  The plan is the same in every form.
+ * it can hold them.  The plan is the same in every form.  No form needs its
+ * workgroups on the device at once: the second is left for the first where
+ * only one of them gets to run.
  *   size, first, last [n] (int64, int32, int32), 0 <= n < 2^30.
  *   offset_out[n] int64, peak_out: one device int64 (arena bytes).
  *   policy: MP_LOWEST_FIT or MP_BEST_FIT.
@@ -131,8 +133,10 @@ int64_t mp_batch_pair_capacity(int64_t max_trace_len);
  * call reads the environment variable MEMOPLAN_DEBUG_WAIT on each call; "wide"
  * makes every wait for late predecessors take its widest form, "tight"
  * besides caps the late list at 8, so tensors with more wait during their
- * collection and the call reports MP_EDEVICE.  Offsets are exact either way;
- * both only exercise paths the schedule rarely reaches. */
+ * collection and the call reports MP_EDEVICE, "alone" starts the placing
+ * workgroup without any that prepares, so that it leaves the trace to the other
+ * form.  Offsets are exact in each; they only exercise paths the schedule
+ * rarely reaches. */
 int32_t mp_plan_trace(const int64_t* size, const int32_t* first, const int32_t* last, int64_t n,
                       int32_t num_ops, int32_t policy, int64_t* offset_out, int64_t* peak_out,
                       void* workspace, size_t workspace_bytes, int32_t* status_out,

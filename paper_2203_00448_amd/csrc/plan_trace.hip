@@ -106,7 +106,7 @@ struct TFlags {
     // takes the step that needs all of them)
     uint32_t done_ingest, done_reach, done_output;
     uint32_t pool[kPoolSlots];        // 1 while a workgroup holds the slot
-    uint32_t roles;                   // lowest fit: workgroups started (the first one places)
+    uint32_t roles;                   // lowest fit: workgroups started (the first one places), or kAlone
     uint32_t stop;                    // lowest fit: a wait found no end (reported, never expected)
     uint32_t chain;                   // lowest fit: one workgroup places (else each its own ranks)
     uint32_t depth, meets, done_depth;  // its measures, summed over the sampled windows
@@ -1587,6 +1587,32 @@ __device__ __noinline__ void chain_loop(ChainLds lds, MemU32 order, MemU32 off, 
 // its own ranks, at the lowest or the tightest gap.
 enum PlaceMode { kPlaceSelf, kPlaceBest, kPlaceChain };
 
+// The chain form needs a second workgroup on the device beside the placing one.
+// A workgroup that counts itself in `roles` is running and stays until every
+// rank is taken, so from the second on there is always one that prepares.  The
+// first one waits for it; where none starts (a stream masked to one CU, or every
+// other CU held by another kernel) it gives way after 2 ms -- a start takes
+// microseconds, and a trace takes 1.5 ms or more in this form -- and the
+// each-its-own kernel behind, which runs with any number of workgroups, places.
+// The exchange of `roles` settles it once: a workgroup that starts later leaves.
+constexpr uint32_t kAlone = 0x80000000u;
+constexpr int64_t kAloneTicks = 200'000;  // of the 100 MHz clock
+
+// The workgroup's place in the order of starts; kAlone or more: leave.
+__device__ __forceinline__ uint32_t chain_role(TFlags* fl) {
+    const uint32_t role = atomicAdd(&fl->roles, 1u);
+    if (role != 0) return role;
+    const int64_t t0 = (int64_t)wall_clock64();
+    while (agent_load(&fl->roles) == 1u) {
+        __builtin_amdgcn_s_sleep(4);
+        if ((int64_t)wall_clock64() - t0 > kAloneTicks && atomicCAS(&fl->roles, 1u, kAlone) == 1u) {
+            agent_store(&fl->chain, 0u);
+            return kAlone;
+        }
+    }
+    return 0u;
+}
+
 template <int BLOCK, PlaceMode MODE>
 __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wide) {
     constexpr bool BEST = MODE == kPlaceBest, CHAIN = MODE == kPlaceChain;
@@ -1614,10 +1640,11 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
     if (MODE != kPlaceBest && (a.fl->chain != 0) != CHAIN) return;  // the other kernel places
     const uint32_t lthr = a.fl->lthr, n_long = a.fl->n_long;
     if constexpr (CHAIN) {
-        if (threadIdx.x == 0) s_rank = atomicAdd(&a.fl->roles, 1u);
+        if (threadIdx.x == 0) s_rank = chain_role(a.fl);
         __syncthreads();
         const uint32_t role = uniform(s_rank);
         __syncthreads();
+        if (role >= kAlone) return;
         if (role == 0) {
             chain_loop((ChainLds)skeys, (MemU32)a.order, (MemU32)a.off, (MemU64)a.heads,
                        (MemU64)a.meta, (MemU64)a.gaps, (MemU64)a.late, (MemU32)a.fl,
@@ -2095,8 +2122,9 @@ struct TLayout {
 // has more late predecessors than wave 0 holds (the other workgroups' ranks
 // and the untaken ranks of the other XCDs' current blocks).  The launch
 // needs no co-residency -- a workgroup waits only on lower ranks, each held
-// by a running workgroup or taken once one on its XCD finishes -- so this
-// is a plain launch sized for throughput.
+// by a running workgroup or taken once one on its XCD finishes, and the chain
+// form, which needs two, is left for the other one where they do not run at
+// once (chain_role) -- so this is a plain launch sized for throughput.
 unsigned place_grid() {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -2265,10 +2293,16 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
     // predecessors a lane; =tight besides caps the late list at 8, so tensors
     // with more wait for the rest during the collection (and report
     // MP_EDEVICE, the condition that path exists for).  Offsets stay exact.
+    // =alone starts a single workgroup of the chain form, which then has none
+    // to prepare for it.
+    unsigned chain_grid = L.grid;
     if (const char* dbg = getenv("MEMOPLAN_DEBUG_WAIT")) {
         if (!strcmp(dbg, "wide")) pa.best |= 0x200;
         if (!strcmp(dbg, "tight")) pa.best |= 0x300;
+        if (!strcmp(dbg, "alone")) chain_grid = 1;
     }
+#else
+    const unsigned chain_grid = L.grid;
 #endif
     const WideArgs wa{su64, reach, pa.order, llist, off64,
                       reinterpret_cast<uint64_t*>(w + L.run_keys), stat_cap_of(n) / 4, pool, n, fl,
@@ -2281,7 +2315,7 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
             hipLaunchKernelGGL(t_rank_of_kernel, dim3(g), dim3(256), 0, st, pa.order,
                                (const int32_t*)reach, n,
                                reinterpret_cast<uint32_t*>(w + L.rank_of), fl);
-            hipLaunchKernelGGL((t_place_kernel<kChainBlock, kPlaceChain>), dim3(L.grid),
+            hipLaunchKernelGGL((t_place_kernel<kChainBlock, kPlaceChain>), dim3(chain_grid),
                                dim3(kChainBlock), 0, st, pa, wa);
         }
         hipLaunchKernelGGL((t_place_kernel<kTBlock, kPlaceSelf>), dim3(L.grid), dim3(kTBlock), 0,

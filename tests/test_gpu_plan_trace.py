@@ -145,7 +145,8 @@ def test_debug_wait_paths(monkeypatch):
     drives the late-predecessor paths the schedule rarely reaches: "wide"
     holds eight late predecessors a lane in every wait, "tight" caps the late
     list at 8 so that tensors with more wait for the rest during their
-    collection (reporting MP_EDEVICE).  Offsets stay exact either way."""
+    collection (reporting MP_EDEVICE), "alone" starts the placing workgroup
+    without any that prepares.  Offsets stay exact in each."""
     binding = need_gpu()
     saved = binding._lib
     binding._lib = None
@@ -159,6 +160,12 @@ def test_debug_wait_paths(monkeypatch):
 def _debug_wait_cases(binding, monkeypatch):
     t = tg.decode100k()
     exp = _expected("decode100k")
+    # the placing workgroup with none beside it (a stream masked to one CU):
+    # it gives way, and the call neither waits for good nor reports a failure
+    monkeypatch.setenv("MEMOPLAN_DEBUG_WAIT", "alone")
+    print("case decode100k, the placing workgroup alone", flush=True)
+    off, peak = _plan(binding, t)
+    assert peak == exp["peak"] and _sha(off) == exp["offsets_sha256"]
     monkeypatch.setenv("MEMOPLAN_DEBUG_WAIT", "wide")
     print("case decode100k, widest wait", flush=True)
     off, peak = _plan(binding, t)
