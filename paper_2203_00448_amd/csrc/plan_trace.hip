@@ -107,7 +107,6 @@ struct TFlags {
     uint32_t done_ingest, done_reach, done_output;
     uint32_t pool[kPoolSlots];        // 1 while a workgroup holds the slot
     uint32_t roles;                   // lowest fit: workgroups started (the first one places), or kAlone
-    uint32_t stop;                    // lowest fit: a wait found no end (reported, never expected)
     uint32_t chain;                   // lowest fit: one workgroup places (else each its own ranks)
     uint32_t depth, meets, done_depth;  // its measures, summed over the sampled windows
     alignas(64) uint32_t front;       // lowest fit: every rank below is placed and visible
@@ -145,7 +144,6 @@ __device__ __forceinline__ void init_flags(TFlags* fl) {
         fl->done_reach = 0;
         fl->done_output = 0;
         fl->roles = 0;
-        fl->stop = 0;
         fl->chain = 0;
         fl->depth = 0;
         fl->meets = 0;
@@ -1264,19 +1262,10 @@ __device__ __forceinline__ void place_wide(const WideArgs& a, uint64_t* lks, uin
 // Decode-like trace 49.4 -> 33.9 ms, ranking-like 712 -> 605 ms; a link is now
 // about 35 dependent instructions of one wave and two LDS round trips (0.4 us).
 
-// A wait that has found nothing for about 30 s (never expected): every
-// workgroup then leaves, and the call reports MP_EDEVICE.
-template <typename Args>
-__device__ __forceinline__ bool wait_over(uint32_t& spins, int64_t& since, const Args& a) {
-    if (++spins & 0xFFFFu) return false;
-    const int64_t now = (int64_t)wall_clock64();
-    if (since == 0) since = now;
-    if (now - since > 3000000000ll) {
-        raise_status(a.status, MP_EDEVICE);
-        agent_store(&a.fl->stop, 1u);
-    }
-    return agent_load(&a.fl->stop) != 0u;
-}
+// No wait here has a limit: each is for a lower rank's placement, its hand-over
+// or its commit, and those come in rank order from workgroups that run.  (A limit
+// would refuse traces whose single fits take long, and a workgroup that gave up
+// would leave the others waiting.)
 
 // Its 16 waves: wave 0 commits (stores the offsets of the placed prefix and
 // moves the front), waves 1-7 load hand-overs into LDS, each four ranks at a
@@ -1294,7 +1283,6 @@ struct ChainArgs {  // of PlaceArgs, what the placing workgroup reads and writes
     uint32_t* off;
     const uint64_t *heads, *meta, *gaps, *late;
     TFlags* fl;
-    int32_t* status;
     uint32_t n;
     int32_t best;
 };
@@ -1319,8 +1307,7 @@ __device__ __forceinline__ uint64_t lds_poll64(const uint64_t* p) {
 // Stores the offsets of ranks placed so far, in order, 64 at a time.
 __device__ __forceinline__ void chain_commit(const ChainArgs& a, ChainShared& S) {
     const uint32_t lane = threadIdx.x & (kWave - 1), n = a.n;
-    uint32_t f = 0, spins = 0;
-    int64_t since = 0;
+    uint32_t f = 0;
     while (f < n) {
         const uint32_t r = f + lane;
         const uint32_t qt = r < n ? a.order[r] : 0u;
@@ -1332,10 +1319,7 @@ __device__ __forceinline__ void chain_commit(const ChainArgs& a, ChainShared& S)
             c = ~ok ? (uint32_t)__builtin_ctzll(~ok) : (uint32_t)kWave;
             if (c) break;
             __builtin_amdgcn_s_sleep(2);
-            if (wait_over(spins, since, a)) return;
         }
-        spins = 0;
-        since = 0;
         if (lane < c) agent_store(a.off + qt, (uint32_t)e);
         memory_done();
         f += c;
@@ -1353,8 +1337,6 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
     LdsHand* mine = S.hand + loader * kLoadBlock;
     for (uint32_t base = loader * kLoadBlock; base < n; base += kLdsHands) {
         uint32_t todo = (1u << min(kLoadBlock, n - base)) - 1u;
-        uint32_t spins = 0;
-        int64_t since = 0;
         while (todo) {
             const uint32_t r = base + lane;
             const bool want = lane < kLoadBlock && ((todo >> lane) & 1u);
@@ -1364,7 +1346,6 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
             const uint32_t m = (uint32_t)__ballot(ok);
             if (!m) {
                 __builtin_amdgcn_s_sleep(2);
-                if (wait_over(spins, since, a)) return;
                 continue;
             }
             uint64_t gap[kLoadBlock], lt[kLoadBlock], me[kLoadBlock];
@@ -1413,11 +1394,10 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
     }
 }
 
-// Finds the offset of rank r from its hand-over, with up to K late predecessors
-// a lane; false when a wait was given up.
+// The offset of rank r from its hand-over, with up to K late predecessors a lane.
 template <int K>
-__device__ __forceinline__ bool chain_place(const ChainArgs& a, ChainShared& S, LdsHand& H,
-                                            uint32_t r, int ng, int nl, uint32_t* x_out) {
+__device__ __forceinline__ uint32_t chain_place(const ChainArgs& a, ChainShared& S, LdsHand& H,
+                                                uint32_t r, int ng, int nl) {
     const int lane = threadIdx.x & (kWave - 1);
     const size_t slot = r & (kHands - 1);
     const uint64_t* gaps = a.gaps + slot * kGapCap;
@@ -1482,8 +1462,6 @@ __device__ __forceinline__ bool chain_place(const ChainArgs& a, ChainShared& S, 
     // as they arrive: it moves (the walk resumes from it) only when a range
     // that arrived overlaps it.
     walk(0, 0u);
-    uint32_t spins = 0;
-    int64_t since = 0;
     uint64_t left = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) left |= pend[k];
@@ -1510,11 +1488,9 @@ __device__ __forceinline__ bool chain_place(const ChainArgs& a, ChainShared& S, 
         if (!any) {
             // ranks far from the one placed last look again later
             if ((int32_t)(r - uniform(last)) > 4) __builtin_amdgcn_s_sleep(2);
-            if (wait_over(spins, since, a)) return false;
         }
     }
-    *x_out = x;
-    return true;
+    return x;
 }
 
 // Draws ranks and places them.
@@ -1527,16 +1503,8 @@ __device__ __forceinline__ void chain_solve(const ChainArgs& a, ChainShared& S) 
         r = uniform(r);
         if (r >= n) break;
         LdsHand& H = S.hand[r % kLdsHands];
-        uint32_t spins = 0;
-        int64_t since = 0;
-        while (uniform(lds_poll(&H.rank)) != r) {
-            __builtin_amdgcn_s_sleep(1);
-            if (wait_over(spins, since, a)) return;
-        }
-        while (r - uniform(lds_poll(&S.front)) >= kRing - kAhead) {
-            __builtin_amdgcn_s_sleep(2);
-            if (wait_over(spins, since, a)) return;
-        }
+        while (uniform(lds_poll(&H.rank)) != r) __builtin_amdgcn_s_sleep(1);
+        while (r - uniform(lds_poll(&S.front)) >= kRing - kAhead) __builtin_amdgcn_s_sleep(2);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         const uint32_t hl = uniform(H.counts);
         uint32_t x;
@@ -1546,11 +1514,9 @@ __device__ __forceinline__ void chain_solve(const ChainArgs& a, ChainShared& S) 
             if (lane == 0) lds_publish(&H.rank, kSlotFree);
         } else {
             const int ng = (int)(hl & 0xFFFFu), nl = (int)(hl >> 16);
-            bool ok;
-            if (T_WIDEST_WAIT || nl > 4 * kWave) ok = chain_place<8>(a, S, H, r, ng, nl, &x);
-            else if (nl <= kWave) ok = chain_place<1>(a, S, H, r, ng, nl, &x);
-            else ok = chain_place<4>(a, S, H, r, ng, nl, &x);
-            if (!ok) return;
+            if (T_WIDEST_WAIT || nl > 4 * kWave) x = chain_place<8>(a, S, H, r, ng, nl);
+            else if (nl <= kWave) x = chain_place<1>(a, S, H, r, ng, nl);
+            else x = chain_place<4>(a, S, H, r, ng, nl);
         }
         if (lane == 0) {
             __hip_atomic_store(&S.ring[r & (kRing - 1)], ((uint64_t)r << 32) | x, __ATOMIC_RELAXED,
@@ -1565,12 +1531,11 @@ typedef __attribute__((address_space(3))) ChainShared* ChainLds;
 
 __device__ __noinline__ void chain_loop(ChainLds lds, MemU32 order, MemU32 off, MemU64 heads,
                                         MemU64 meta, MemU64 gaps, MemU64 late, MemU32 fl,
-                                        MemU32 status, uint32_t n, int32_t best) {
+                                        uint32_t n, int32_t best) {
     ChainShared& S = *(ChainShared*)lds;
     ChainArgs a{(const uint32_t*)order, (uint32_t*)off,  (const uint64_t*)heads,
                 (const uint64_t*)meta,  (const uint64_t*)gaps, (const uint64_t*)late,
-                (TFlags*)(uint32_t*)fl, (int32_t*)(uint32_t*)status, uniform(n),
-                (int32_t)uniform((uint32_t)best)};
+                (TFlags*)(uint32_t*)fl, uniform(n), (int32_t)uniform((uint32_t)best)};
     const uint32_t wid = uniform(threadIdx.x / kWave);
     for (uint32_t i = threadIdx.x; i < kRing; i += kChainBlock) S.ring[i] = ~0ull;
     if (threadIdx.x < kLdsHands) S.hand[threadIdx.x].rank = kSlotFree;
@@ -1648,7 +1613,7 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
         if (role == 0) {
             chain_loop((ChainLds)skeys, (MemU32)a.order, (MemU32)a.off, (MemU64)a.heads,
                        (MemU64)a.meta, (MemU64)a.gaps, (MemU64)a.late, (MemU32)a.fl,
-                       (MemU32)a.status, (uint32_t)a.n, a.best);
+                       (uint32_t)a.n, a.best);
             return;
         }
     }
@@ -1659,13 +1624,9 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
             if constexpr (!CHAIN) {
                 s_rank = take_rank(a.fl, a.xbase, a.xcap);
             } else {
-                uint32_t r = atomicAdd(&a.fl->ticket, 1u);
-                uint32_t spins = 0;
-                int64_t since = 0;
-                while (r < (uint32_t)a.n && r >= agent_load(&a.fl->front) + kAhead) {
+                const uint32_t r = atomicAdd(&a.fl->ticket, 1u);
+                while (r < (uint32_t)a.n && r >= agent_load(&a.fl->front) + kAhead)
                     __builtin_amdgcn_s_sleep(4);
-                    if (wait_over(spins, since, a)) r = (uint32_t)a.n;
-                }
                 s_rank = r;
             }
             s_nstat = 0;
@@ -1691,14 +1652,10 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
             }
             __syncthreads();
         };
-        // the offset of a lower rank, waited for (0 when the call is given up)
+        // the offset of a lower rank, waited for
         auto placed = [&](uint32_t p) {
-            uint32_t o, spins = 0;
-            int64_t since = 0;
-            while ((o = agent_load(a.off + p)) == kUnplacedT) {
-                __builtin_amdgcn_s_sleep(1);
-                if (wait_over(spins, since, a)) return 0u;
-            }
+            uint32_t o;
+            while ((o = agent_load(a.off + p)) == kUnplacedT) __builtin_amdgcn_s_sleep(1);
             return o;
         };
         // 1. collect: placed predecessors as keys, unplaced ones by position

@@ -157,3 +157,14 @@ def test_strategy_entry_points_host_checks(lib):
                                 None) == b.MP_EINVAL
     assert lib.mp_optimal_batch(dummy, 2, dummy, dummy, dummy, dummy, 4, dummy, dummy, None,
                                 None) == b.MP_EINVAL
+
+
+def test_placement_waits_have_no_limit():
+    """The single-trace placement waits for lower ranks as long as they take: no
+    wait is given up (a workgroup that left would leave others waiting, and a
+    trace whose single fits take long would be refused).  The one clock read is
+    before the choice of the form is final."""
+    text = open(os.path.join(ROOT, "paper_2203_00448_amd", "csrc", "plan_trace.hip")).read()
+    role = re.search(r"uint32_t chain_role\(.*?\n}\n", text, flags=re.S).group(0)
+    assert "clock64" in role
+    assert "clock64" not in text.replace(role, "")
