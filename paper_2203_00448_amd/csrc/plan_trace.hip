@@ -796,7 +796,7 @@ struct PlaceArgs {
     uint64_t* heads;  // (rank + 1) << 32 | kByPreparer | late << 16 | gaps; zero at the launch
     uint64_t* meta;   // 2 a slot: size << 32 | position; the run's top (or the offset)
     uint64_t* gaps;   // kGapCap a slot: end << 32 | start, in address order
-    uint64_t* late;   // kDynCap a slot: size << 32 | rank
+    uint64_t* late;   // kAhead a slot: size << 32 | rank
 };
 
 // Visit the positions ranked before t whose lifetimes meet t's: the forward
@@ -1243,10 +1243,10 @@ __device__ __forceinline__ void place_wide(const WideArgs& a, uint64_t* lks, uin
 #ifdef MP_DEBUG_WAIT
 // test build (MEMOPLAN_DEBUG_WAIT bits of a.best): 0x200 every wait takes its
 // widest form; 0x100 besides the late list holds 8
-#define T_DYN_CAP ((a.best & 0x100) ? 8u : (uint32_t)kDynCap)
+#define T_DYN_CAP ((a.best & 0x100) ? 8u : kLateCap)
 #define T_WIDEST_WAIT ((a.best & 0x200) != 0)
 #else
-#define T_DYN_CAP ((uint32_t)kDynCap)
+#define T_DYN_CAP kLateCap
 #define T_WIDEST_WAIT false
 #endif
 
@@ -1360,7 +1360,7 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
                              ? agent_load64(a.gaps + (size_t)slot * kGapCap + lane)
                              : 0ull;
                 lt[j] = open && lane < (hl[j] >> 16)
-                            ? agent_load64(a.late + (size_t)slot * kDynCap + lane)
+                            ? agent_load64(a.late + (size_t)slot * kAhead + lane)
                             : 0ull;
             }
 #pragma unroll
@@ -1371,7 +1371,7 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
                 H.late[lane] = lt[j];
                 const uint32_t nl = hl[j] >> 16;
                 if (!(hl[j] & kByPreparer) && nl > (uint32_t)kWave && nl <= kLdsLate) {
-                    const uint64_t* late = a.late + (size_t)((base + j) & (kHands - 1)) * kDynCap;
+                    const uint64_t* late = a.late + (size_t)((base + j) & (kHands - 1)) * kAhead;
                     uint64_t v[kLdsLate / kWave];
 #pragma unroll
                     for (uint32_t k = 1; k < kLdsLate / kWave; ++k)
@@ -1410,7 +1410,7 @@ __device__ __forceinline__ uint32_t chain_place(const ChainArgs& a, ChainShared&
         const int d = lane + kWave * k;
         uint64_t v = 0;
         if (K <= (int)kLdsLate / kWave) v = H.late[d];
-        else if (d < nl) v = agent_load64(a.late + slot * kDynCap + d);
+        else if (d < nl) v = agent_load64(a.late + slot * kAhead + d);
         want[k] = (uint32_t)v;
         sz[k] = (uint32_t)(v >> 32);
         pend[k] = __ballot(d < nl);
@@ -1581,9 +1581,10 @@ __device__ __forceinline__ uint32_t chain_role(TFlags* fl) {
 template <int BLOCK, PlaceMode MODE>
 __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wide) {
     constexpr bool BEST = MODE == kPlaceBest, CHAIN = MODE == kPlaceChain;
+    constexpr uint32_t kLateCap = CHAIN ? kAhead : (uint32_t)kDynCap;
     __shared__ uint64_t skeys[kRunCap];  // placed predecessors (one run); the placing workgroup's ring
-    __shared__ uint64_t dkeys[kDynCap];  // predecessors placed after t was examined
-    __shared__ uint32_t dpos[kDynCap];
+    __shared__ uint64_t dkeys[kLateCap];  // predecessors placed after t was examined
+    __shared__ uint32_t dpos[kLateCap];
     __shared__ uint32_t scratch[BLOCK / kWave];
     __shared__ uint64_t scratch64[BLOCK / kWave];
     __shared__ uint64_t gbits[kRunCap / 64];  // gaps of the placed run that hold t
@@ -1910,7 +1911,7 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
                     }
                     for (int d = threadIdx.x; d < ndyn; d += BLOCK) {
                         const uint32_t p = dpos[d];
-                        agent_store64(a.late + (size_t)slot * kDynCap + d,
+                        agent_store64(a.late + (size_t)slot * kAhead + d,
                                       ((uint64_t)a.su[p] << 32) | a.rank_of[p]);
                     }
                     if (threadIdx.x == 0) {
@@ -2137,11 +2138,13 @@ TLayout t_layout(int64_t n, unsigned grid) {
     // that ends it): blocks 0 .. (n + grid) / kTicketBlock
     L.xcap = (nn + (int64_t)grid) / kTicketBlock + 2;
     L.xbase = take((size_t)kXcdGroups * (size_t)L.xcap * 4);
-    L.rank_of = take(nn * 4);
-    L.heads = take((size_t)kHands * 8);
-    L.meta = take((size_t)kHands * 16);
-    L.gaps = take((size_t)kHands * kGapCap * 8);
-    L.late = take((size_t)kHands * kDynCap * 8);
+    if (nn > kSmallN) {  // the chain form's; a shorter trace never takes it
+        L.rank_of = take(nn * 4);
+        L.heads = take((size_t)kHands * 8);
+        L.meta = take((size_t)kHands * 16);
+        L.gaps = take((size_t)kHands * kGapCap * 8);
+        L.late = take((size_t)kHands * kAhead * 8);
+    }
     L.total = o;
     L.grid = grid;
     return L;

@@ -102,6 +102,17 @@ def test_workspace_bytes_query(lib):
         assert wb(*bad) == 0, bad
 
 
+def test_short_trace_workspace(lib):
+    """Traces of up to MP_BATCH_MAX_TRACE_LEN tensors are not planned in the form
+    whose hand-overs between workgroups take megabytes: 8 KiB a tensor (256
+    workgroups of 4 keys a tensor) and little else."""
+    from paper_2203_00448_amd import binding
+    need = lambda n: lib.mp_workspace_bytes(binding.OP_PLAN_TRACE, n, n, 1)
+    groups = 513 - 8 * 31  # the most a launch has
+    for n in (1, 256, 4096):
+        assert need(n) <= groups * 32 * n + 256 * n + (1 << 16), n
+
+
 def test_other_host_checks(lib):
     from paper_2203_00448_amd import binding as b
     d = ctypes.c_void_p(16)
