@@ -648,7 +648,7 @@ __device__ __forceinline__ uint64_t block_exclusive_max(uint64_t v, uint64_t* al
 // tensors): two copies of the list of placed tensors sorted by offset --
 // offsets (u64) at 0 and 8n, ids (u32) at 16n and 20n.  The live-bytes
 // difference array (n + 1 u64) uses the first copy before placement.  24n + 8
-// bytes in all; the LDS path keeps its position permutation (u16) at 0.
+// bytes in all.
 constexpr int64_t kWsPerTensor = 24;
 constexpr int64_t kWsPerTrace = 64;
 
@@ -762,10 +762,13 @@ __device__ void plan_general(const int64_t* __restrict__ size, const int32_t* __
         uint32_t* ni = (k & 1) ? sidx0 : sidx1;
         const int chunk = (k + BLOCK - 1) / BLOCK;  // k tensors are placed
         const int e0 = min(k, tid * chunk), e1 = min(k, e0 + chunk);
+        // A refused begin[] can give two traces the same lists: the call fails, and
+        // what is read there must still be an id of this trace.
+        auto id_at = [&](const uint32_t* p) { return min(l2_load32(p), (uint32_t)n - 1u); };
         auto meets = [&](uint32_t id) { return first[lo + id] <= lt && ft <= last[lo + id]; };
         uint64_t hi = 0;  // highest end among this thread's ranges that meet t
         for (int e = e0; e < e1; ++e) {
-            const uint32_t id = l2_load32(si + e);
+            const uint32_t id = id_at(si + e);
             if (meets(id)) {
                 const uint64_t en = l2_load64(so + e) + sz[id];
                 hi = hi > en ? hi : en;
@@ -775,7 +778,7 @@ __device__ void plan_general(const int64_t* __restrict__ size, const int32_t* __
         uint64_t run = block_exclusive_max<BLOCK>(hi, &top, red64);
         uint64_t cand = ~0ull, cgap = ~0ull;  // this thread's choice among its gaps
         for (int e = e0; e < e1; ++e) {
-            const uint32_t id = l2_load32(si + e);
+            const uint32_t id = id_at(si + e);
             if (!meets(id)) continue;
             const uint64_t o = l2_load64(so + e);
             if (o >= run && o - run >= st) {
@@ -862,6 +865,23 @@ __device__ __forceinline__ int item_index(int k) {
     return t + k * BLOCK;
 }
 
+// The tensor ids of a thread's positions (in a sorted trace the positions
+// themselves), two a register.  Not in memory of the call: workspace and offset_out
+// are the trace's alone only while begin[] is valid, and in a call with a refused
+// one two traces would read each other's ids.
+template <int BLOCK, int ITEMS>
+struct PositionIds {
+    uint32_t two[(ITEMS + 1) / 2];
+    bool unsorted;
+    __device__ __forceinline__ void set(int k, uint32_t id) {  // k in order
+        two[k / 2] = (k & 1) ? two[k / 2] | (id << 16) : id;
+    }
+    __device__ __forceinline__ int at(int k) const {
+        const uint32_t w = two[k / 2];
+        return unsorted ? (int)((k & 1) ? w >> 16 : w & 0xFFFFu) : item_index<BLOCK>(k);
+    }
+};
+
 // The Greedy by Breadth ranks of a trace in LDS (0 <= n <= 4096, its sizes
 // below 2^31 units in all): rk[k] = rank of position tid + k * BLOCK.  An op's
 // breadth (a tensor's size at its first op and, if different, at its last) is
@@ -873,22 +893,22 @@ __device__ __forceinline__ int item_index(int k) {
 // id.  Bound by the sort's barriers: 66 stages for 2048 tensors.
 template <int BLOCK, int ITEMS>
 __device__ __forceinline__ void breadth_ranks(
-    const int64_t* __restrict__ size, const int32_t* __restrict__ first,
-    const int32_t* __restrict__ last, int64_t lo, int n, int32_t n_ops, int sh,
-    const uint32_t (&su_r)[ITEMS], const uint16_t* perm, unsigned char* smem, uint32_t* ops,
-    uint16_t (&rk)[ITEMS]) {
+    const int32_t* __restrict__ first, const int32_t* __restrict__ last, int64_t lo, int n,
+    int32_t n_ops, const uint32_t (&su_r)[ITEMS], const PositionIds<BLOCK, ITEMS>& ids_r,
+    unsigned char* smem, uint32_t* ops, uint16_t (&rk)[ITEMS]) {
     const int tid = threadIdx.x;
     int m = 1;
     while (m < n) m <<= 1;
     uint64_t* keys = reinterpret_cast<uint64_t*>(smem);
     uint32_t* units = reinterpret_cast<uint32_t*>(smem + 8 * (size_t)m);  // by position
+    uint16_t* ids = reinterpret_cast<uint16_t*>(units + n);               // by position, if unsorted
     uint16_t* ranks = reinterpret_cast<uint16_t*>(smem);                  // over the dead keys
     for (int o = tid; o < n_ops; o += BLOCK) ops[o] = 0;
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
-        const int i = item_index<BLOCK>(k);
-        if (i < n) {
+        if (item_index<BLOCK>(k) < n) {
+            const int i = ids_r.at(k);
             const int32_t f = first[lo + i], l = last[lo + i];
             atomicAdd(&ops[f], su_r[k]);
             if (l != f) atomicAdd(&ops[l], su_r[k]);
@@ -896,20 +916,17 @@ __device__ __forceinline__ void breadth_ranks(
     }
     __syncthreads();
     uint64_t key[ITEMS];
-    uint32_t un[ITEMS];
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int q = item_index<BLOCK>(k);
         key[k] = ~0ull;
-        un[k] = su_r[k];
         if (q < n) {
-            const int i = perm ? (int)perm[q] : q;
+            const int i = ids_r.at(k);
             const int32_t f = first[lo + i], l = last[lo + i];
             const uint32_t bf = ops[f], bl = ops[l];
             const uint32_t br = bf >= bl ? bf : bl, op = (uint32_t)(bf >= bl ? f : l);
             // breadth below 2^31, op below 2^21 (n_ops words fit the LDS)
             key[k] = ((uint64_t)(0x7FFFFFFFu - br) << 33) | ((uint64_t)op << 12) | (uint32_t)q;
-            if (perm) un[k] = (uint32_t)((uint64_t)size[lo + i] >> sh);
         }
     }
     __syncthreads();
@@ -917,7 +934,8 @@ __device__ __forceinline__ void breadth_ranks(
     for (int k = 0; k < ITEMS; ++k) {
         const int q = item_index<BLOCK>(k);
         if (q < m) keys[q] = key[k];
-        if (q < n) units[q] = un[k];
+        if (q < n) units[q] = su_r[k];
+        if (q < n && ids_r.unsorted) ids[q] = (uint16_t)ids_r.at(k);
     }
     __syncthreads();
     bitonic_sort_u64<BLOCK>(keys, m);
@@ -932,7 +950,7 @@ __device__ __forceinline__ void breadth_ranks(
             auto before = [&](uint32_t o) {  // does position o rank before p? (one op)
                 const uint32_t v = units[o];
                 if (v != u) return v > u;
-                return perm ? perm[o] < perm[p] : o < p;
+                return ids_r.unsorted ? ids[o] < ids[p] : o < p;
             };
             int s = i;
             uint32_t cnt = 0;
@@ -961,10 +979,9 @@ __device__ __forceinline__ void breadth_ranks(
 // BREADTH: Greedy by Breadth (breadth.hip) on the same schedule.  A greedy in
 // any total order equals Kahn's rounds over the pairs that intersect, so only
 // the order of a pair differs: by the rank of (breadth of the tensor's op
-// desc, op, size desc, id), found once by breadth_ranks below.  The call has
-// no workspace: an unsorted trace's permutation sits in its own offset_out
-// until the outputs are written, and a trace that the LDS path cannot hold is
-// left to breadth_kernel, marked by a peak of -1.
+// desc, op, size desc, id), found once by breadth_ranks above.  The call has
+// no workspace: a trace that the LDS path cannot hold is left to
+// breadth_kernel, marked by a peak of -1.
 // ONE: a single trace of n_tensors tensors and one_ops ops (begin and num_ops
 // are null); *planned is 0 when the LDS path cannot hold it, else 1.
 // A trace of more than kOnePairs pairs a tensor is left too: its rounds are many
@@ -1033,9 +1050,6 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
         return;
     }
     const int n = (int)(hi - lo);
-    unsigned char* tws = BREADTH ? reinterpret_cast<unsigned char*>(offset_out + lo)
-                                 : trace_ws(ws, lo, b);
-    uint16_t* perm = reinterpret_cast<uint16_t*>(tws);  // ids by position (unsorted traces)
 
     // ---- ingest + checks (ids owned strided: i = tid + k * BLOCK).  The
     // sizes and last ops of a sorted trace stay in registers for the band
@@ -1116,12 +1130,14 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     }
     const int sh = __builtin_ctzll(or_all);  // common power-of-two unit of all sizes
     bool general = (total >> sh) > kFastMaxUnits;
-    // sizes in units (below 2^31 unless general), kept instead of the bytes
+    // sizes in units (below 2^31 unless general), kept instead of the bytes; by
+    // position from the position sort on
     uint32_t su_r[ITEMS];
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) su_r[k] = (uint32_t)((uint64_t)sz_r[k] >> sh);
     const bool unsorted = (flags & 2u) != 0;
-    auto id_of = [&](int q) { return unsorted ? (int)perm[q] : q; };  // position -> id
+    PositionIds<BLOCK, ITEMS> ids_r{};
+    ids_r.unsorted = unsorted;
 
     uint32_t live_max = 0, n_pairs = 0;
     uint16_t rk_r[ITEMS];  // BREADTH: ranks of this thread's positions
@@ -1137,22 +1153,23 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const int q = item_index<BLOCK>(k);
-                if (q < n) perm[q] = (uint16_t)(keys[q] & 0xFFFFu);
+                const uint32_t id = q < n ? (uint32_t)keys[q] : 0u;
+                ids_r.set(k, id);
+                if (q < n) su_r[k] = (uint32_t)((uint64_t)size[lo + id] >> sh);
             }
-            l2_barrier();  // the keys are dead: first[] goes back in position order
+            __syncthreads();  // the keys are dead: first[] goes back in position order
         }
         if constexpr (BREADTH) {
             general = (size_t)n_ops * 4 > R.total - R.e;  // the ops' breadths do not fit
             if (!general)
-                breadth_ranks<BLOCK, ITEMS>(size, first, last, lo, n, n_ops, sh, su_r,
-                                            unsorted ? perm : nullptr, smem,
+                breadth_ranks<BLOCK, ITEMS>(first, last, lo, n, n_ops, su_r, ids_r, smem,
                                             reinterpret_cast<uint32_t*>(smem + R.e), rk_r);
         }
         if (unsorted || BREADTH) {
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const int q = item_index<BLOCK>(k);
-                if (q < n) fst[q] = first[lo + id_of(q)];
+                if (q < n) fst[q] = first[lo + ids_r.at(k)];
             }
         }
         for (int i = tid; i <= n; i += BLOCK) live[i] = 0;
@@ -1187,7 +1204,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
             const int q = item_index<BLOCK>(k);
             rch[k] = q + 1;
             if (q < n) {
-                const int32_t l = last[lo + (unsorted ? (int)perm[q] : q)];
+                const int32_t l = last[lo + ids_r.at(k)];
                 if (by_table) {
                     rch[k] = ptab[l];
                 } else {
@@ -1203,9 +1220,8 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
         for (int k = 0; k < ITEMS; ++k) {
             const int q = item_index<BLOCK>(k);
             if (q < n) {
-                const int32_t l = last[lo + (unsorted ? (int)perm[q] : q)];
-                const uint32_t sq =
-                    unsorted ? (uint32_t)((uint64_t)size[lo + perm[q]] >> sh) : su_r[k];
+                const int32_t l = last[lo + ids_r.at(k)];
+                const uint32_t sq = su_r[k];
                 int a = rch[k];
                 if (!by_table && a == q + 5) {  // first[q + 4] <= l: gallop on
                     int known = q + 4, step = 8, probe = q + 8;  // first[known] <= l
@@ -1330,8 +1346,8 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
     if (general) {
         __syncthreads();
         uint64_t pk = 0, bound = 0;
-        plan_general<BLOCK>(size, first, last, lo, n, best, smem, tws, red, offset_out, &pk,
-                            &bound);
+        plan_general<BLOCK>(size, first, last, lo, n, best, smem, trace_ws(ws, lo, b), red,
+                            offset_out, &pk, &bound);
         if (tid == 0) {
             peak_out[b] = (int64_t)pk;
             if (lb_out) lb_out[b] = (int64_t)bound;
@@ -1349,7 +1365,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
         if (BREADTH) {
             if (q < n) rank16[q] = rk_r[k];
         } else if (q < n) {
-            su[q] = unsorted ? (uint32_t)((uint64_t)size[lo + perm[q]] >> sh) : su_r[k];
+            su[q] = su_r[k];
         }
     }
     __syncthreads();
@@ -1412,11 +1428,7 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
             const uint32_t K = (uint32_t)lbeg[q + 1] - lbeg[q] + rlen[q];
             const uint32_t c = ready_class(K, best);
             const uint32_t pc = packed_get(pend, (uint32_t)q);
-            uint32_t units;
-            if constexpr (BREADTH)
-                units = unsorted ? (uint32_t)((uint64_t)size[lo + perm[q]] >> sh) : su_r[k];
-            else
-                units = su[q];
+            const uint32_t units = BREADTH ? su_r[k] : su[q];
             w_r[k] = ((uint64_t)(kUnplacedBit | class_bits(c) | pc) << 32) | units;
             cls_r[k] = pc == 0 ? c + 8 : c;  // +8: a seed
             const uint32_t f = 1u << (10u * (c < 3u ? c : c - 3u));
@@ -1672,22 +1684,12 @@ __global__ __launch_bounds__(BLOCK, BEST ? 4 : (ITEMS <= 4 ? 6 : 4)) void plan_b
 
     // ---- outputs
     uint32_t pk = 0;
-    if constexpr (BREADTH) {
-        // the permutation lies in offset_out: every thread has read its part
-        // before any offset is written
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            const int q = item_index<BLOCK>(k);
-            rk_r[k] = (uint16_t)(q < n ? id_of(q) : 0);
-        }
-        __syncthreads();
-    }
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int q = item_index<BLOCK>(k);
         if (q < n) {
             const uint64_t w = ofsz[q];
-            offset_out[lo + (BREADTH ? (int)rk_r[k] : id_of(q))] = (int64_t)((uint64_t)word_off(w) << sh);
+            offset_out[lo + ids_r.at(k)] = (int64_t)((uint64_t)word_off(w) << sh);
             const uint32_t e = word_end(w);
             pk = pk > e ? pk : e;
         }

@@ -173,3 +173,41 @@ def test_odd_bounds(bound):
         eo, ep = oracle.plan_batch(batch.begin, batch.num_ops, batch.size, batch.first,
                                    batch.last, policy)
         assert np.array_equal(host(off), eo) and np.array_equal(host(peak), ep)
+
+
+@pytest.mark.parametrize("call", ["lowest", "best", "breadth", "dense"])
+def test_refused_begin_with_shared_tensors(call):
+    """A begin[] that goes back gives several traces the same tensors.  The call
+    is refused, and until then each of those traces keeps to its own memory: its
+    working data lies in no array that another one of them writes, so the ids it
+    reads are ids of its tensors and the plan (the same for all of them, in any
+    order) is the oracle's.  "dense" takes the general path, whose lists the
+    traces share: there the call only has to end in MP_EINVAL."""
+    binding = need_gpu()
+    rng = np.random.default_rng(170)
+    n, copies = 1500, 300
+    if call == "dense":
+        t = tg.random_trace(rng, n, 40, max_len=30)
+    else:
+        t = tg.random_trace(rng, n, n, max_len=6)  # in any order
+    assert np.any(np.diff(t.first) < 0)
+    begin = np.array(([0, n] * copies)[: 2 * copies], np.int64)
+    ops = np.full(begin.size - 1, t.num_ops, np.int32)
+    args = (dev(begin, torch.int64), dev(ops, torch.int32), dev(t.size, torch.int64),
+            dev(t.first, torch.int32), dev(t.last, torch.int32))
+    st = binding.new_status()
+    peak = torch.full((ops.size,), -7, dtype=torch.int64, device="cuda")
+    off = torch.full((n,), -7, dtype=torch.int64, device="cuda")
+    print(f"case refused begin, {call}", flush=True)
+    if call == "breadth":
+        binding.plan_breadth_batch(*args, check=False, status=st, out=(off, peak))
+        eo, ep = oracle.plan_breadth(t.size, t.first, t.last, t.num_ops, 0)
+    else:
+        policy = int(call == "best")
+        binding.plan_batch(*args, max_trace_len=n, policy=policy, check=False, status=st,
+                           out=(off, peak, None))
+        eo, ep = oracle.plan_trace(t.size, t.first, t.last, t.num_ops, policy)
+    assert int(st.item()) == binding.MP_EINVAL
+    if call != "dense":
+        assert np.array_equal(host(off), eo)
+        assert np.all(host(peak)[::2] == ep) and np.all(host(peak)[1::2] == -7)
