@@ -74,8 +74,10 @@ static_assert(kAhead <= (uint32_t)kDynCap && kDynCap <= 8 * kWave,
 // than kAhead below its tensor's) is never overwritten while it is waited for.
 constexpr uint32_t kRing = 2048;
 constexpr uint32_t kHands = kAhead;  // hand-overs in flight, slot rank % kHands
-constexpr uint32_t kGapCap = 4096;   // gaps a hand-over holds (512: 28,000 of the 10^6 ranking-like
-                                     // tensors had more and were left to their preparers, 905 ms)
+// (A hand-over holds every gap of a run, up to kRunCap: a tensor left to its
+// preparer waits rank by rank through memory.  With room for 512 gaps, 28,000 of
+// the 10^6 ranking-like tensors had more, 905 ms; with 4,096, a trace of 48,000
+// with 6,000 gaps for most of them took 354 ms, 69 ms so.)
 constexpr uint32_t kByPreparer = 0x80000000u;  // hand-over: the preparer placed the tensor
 static_assert((kRing & (kRing - 1)) == 0 && (kHands & (kHands - 1)) == 0 && kRing >= 2 * kAhead,
               "rings indexed by the rank's low bits");
@@ -795,7 +797,8 @@ struct PlaceArgs {
     const uint32_t* rank_of;
     uint64_t* heads;  // (rank + 1) << 32 | kByPreparer | late << 16 | gaps; zero at the launch
     uint64_t* meta;   // 2 a slot: size << 32 | position; the run's top (or the offset)
-    uint64_t* gaps;   // kGapCap a slot: end << 32 | start, in address order
+    uint64_t* gaps;   // gap_cap a slot: end << 32 | start, in address order
+    uint32_t gap_cap;  // the most gaps a run of n - 1 ranges or fewer has
     uint64_t* late;   // kAhead a slot: size << 32 | rank
 };
 
@@ -1283,7 +1286,7 @@ struct ChainArgs {  // of PlaceArgs, what the placing workgroup reads and writes
     uint32_t* off;
     const uint64_t *heads, *meta, *gaps, *late;
     TFlags* fl;
-    uint32_t n;
+    uint32_t n, gap_cap;
     int32_t best;
 };
 
@@ -1357,7 +1360,7 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
                 const bool on = (m >> j) & 1u, open = on && !(hl[j] & kByPreparer);
                 me[j] = on && lane < 2 ? agent_load64(a.meta + 2 * slot + lane) : 0ull;
                 gap[j] = open && lane < (hl[j] & 0xFFFFu)
-                             ? agent_load64(a.gaps + (size_t)slot * kGapCap + lane)
+                             ? agent_load64(a.gaps + (size_t)slot * a.gap_cap + lane)
                              : 0ull;
                 lt[j] = open && lane < (hl[j] >> 16)
                             ? agent_load64(a.late + (size_t)slot * kAhead + lane)
@@ -1400,7 +1403,7 @@ __device__ __forceinline__ uint32_t chain_place(const ChainArgs& a, ChainShared&
                                                 uint32_t r, int ng, int nl) {
     const int lane = threadIdx.x & (kWave - 1);
     const size_t slot = r & (kHands - 1);
-    const uint64_t* gaps = a.gaps + slot * kGapCap;
+    const uint64_t* gaps = a.gaps + slot * a.gap_cap;
     const uint32_t st = uniform(H.st), top = uniform(H.top);
     uint64_t gap = H.gaps[lane];
     uint32_t want[K], sz[K];  // late ranks and their sizes (late predecessor lane + 64 k in slot k)
@@ -1531,11 +1534,11 @@ typedef __attribute__((address_space(3))) ChainShared* ChainLds;
 
 __device__ __noinline__ void chain_loop(ChainLds lds, MemU32 order, MemU32 off, MemU64 heads,
                                         MemU64 meta, MemU64 gaps, MemU64 late, MemU32 fl,
-                                        uint32_t n, int32_t best) {
+                                        uint32_t n, uint32_t gap_cap, int32_t best) {
     ChainShared& S = *(ChainShared*)lds;
     ChainArgs a{(const uint32_t*)order, (uint32_t*)off,  (const uint64_t*)heads,
                 (const uint64_t*)meta,  (const uint64_t*)gaps, (const uint64_t*)late,
-                (TFlags*)(uint32_t*)fl, uniform(n), (int32_t)uniform((uint32_t)best)};
+                (TFlags*)(uint32_t*)fl, uniform(n), uniform(gap_cap), (int32_t)uniform((uint32_t)best)};
     const uint32_t wid = uniform(threadIdx.x / kWave);
     for (uint32_t i = threadIdx.x; i < kRing; i += kChainBlock) S.ring[i] = ~0ull;
     if (threadIdx.x < kLdsHands) S.hand[threadIdx.x].rank = kSlotFree;
@@ -1614,7 +1617,7 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
         if (role == 0) {
             chain_loop((ChainLds)skeys, (MemU32)a.order, (MemU32)a.off, (MemU64)a.heads,
                        (MemU64)a.meta, (MemU64)a.gaps, (MemU64)a.late, (MemU32)a.fl,
-                       (uint32_t)a.n, a.best);
+                       (uint32_t)a.n, a.gap_cap, a.best);
             return;
         }
     }
@@ -1903,32 +1906,30 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
                 uint32_t ng;
                 uint32_t at = block_exclusive_sum<BLOCK>((uint32_t)__popcll(bits), &ng, scratch);
                 ng = uniform(ng);
-                if (ng <= kGapCap) {
-                    for (; bits; bits &= bits - 1, ++at) {
-                        const int i = 64 * (int)threadIdx.x + __builtin_ctzll(bits);
-                        const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
-                        agent_store64(a.gaps + (size_t)slot * kGapCap + at, ((uint64_t)g1 << 32) | g0);
-                    }
-                    for (int d = threadIdx.x; d < ndyn; d += BLOCK) {
-                        const uint32_t p = dpos[d];
-                        agent_store64(a.late + (size_t)slot * kAhead + d,
-                                      ((uint64_t)a.su[p] << 32) | a.rank_of[p]);
-                    }
-                    if (threadIdx.x == 0) {
-                        agent_store64(a.meta + 2 * slot, ((uint64_t)st << 32) | (uint32_t)qt);
-                        agent_store64(a.meta + 2 * slot + 1, m ? run_pmax(skeys[m - 1]) : 0u);
-                    }
-                    l2_barrier();  // the hand-over is in memory before its head
-                    if (threadIdx.x == 0)
-                        agent_store64(a.heads + slot, ((uint64_t)(r + 1u) << 32) |
-                                                          ((uint64_t)(uint32_t)ndyn << 16) | ng);
-                    // Without a barrier here the compiler joins this test of
-                    // thread 0 with the one at the loop's top: the first
-                    // wave's other lanes then go round the loop, barriers
-                    // included, before lane 0 has drawn the next rank.
-                    __syncthreads();
-                    continue;
+                for (; bits; bits &= bits - 1, ++at) {
+                    const int i = 64 * (int)threadIdx.x + __builtin_ctzll(bits);
+                    const uint32_t g0 = i ? run_pmax(skeys[i - 1]) : 0u, g1 = run_start(skeys[i]);
+                    agent_store64(a.gaps + (size_t)slot * a.gap_cap + at, ((uint64_t)g1 << 32) | g0);
                 }
+                for (int d = threadIdx.x; d < ndyn; d += BLOCK) {
+                    const uint32_t p = dpos[d];
+                    agent_store64(a.late + (size_t)slot * kAhead + d,
+                                  ((uint64_t)a.su[p] << 32) | a.rank_of[p]);
+                }
+                if (threadIdx.x == 0) {
+                    agent_store64(a.meta + 2 * slot, ((uint64_t)st << 32) | (uint32_t)qt);
+                    agent_store64(a.meta + 2 * slot + 1, m ? run_pmax(skeys[m - 1]) : 0u);
+                }
+                l2_barrier();  // the hand-over is in memory before its head
+                if (threadIdx.x == 0)
+                    agent_store64(a.heads + slot, ((uint64_t)(r + 1u) << 32) |
+                                                      ((uint64_t)(uint32_t)ndyn << 16) | ng);
+                // Without a barrier here the compiler joins this test of
+                // thread 0 with the one at the loop's top: the first
+                // wave's other lanes then go round the loop, barriers
+                // included, before lane 0 has drawn the next rank.
+                __syncthreads();
+                continue;
             }
         }
         // 3. wait for the predecessors that were not placed yet; their ranges
@@ -2106,6 +2107,9 @@ int64_t stat_cap_of(int64_t n) {
     return 4 * n < cap ? 4 * n : cap;
 }
 
+// Gaps of one sorted run: at most one below each of its ranges.
+uint32_t gap_cap_of(int64_t n) { return (uint32_t)(n < kRunCap ? n : kRunCap); }
+
 TLayout t_layout(int64_t n, unsigned grid) {
     TLayout L{};
     size_t o = 0;
@@ -2142,7 +2146,7 @@ TLayout t_layout(int64_t n, unsigned grid) {
         L.rank_of = take(nn * 4);
         L.heads = take((size_t)kHands * 8);
         L.meta = take((size_t)kHands * 16);
-        L.gaps = take((size_t)kHands * kGapCap * 8);
+        L.gaps = take((size_t)kHands * gap_cap_of(nn) * 8);
         L.late = take((size_t)kHands * kAhead * 8);
     }
     L.total = o;
@@ -2247,6 +2251,7 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
                  reinterpret_cast<uint64_t*>(w + L.heads),
                  reinterpret_cast<uint64_t*>(w + L.meta),
                  reinterpret_cast<uint64_t*>(w + L.gaps),
+                 gap_cap_of(n),
                  reinterpret_cast<uint64_t*>(w + L.late)};
 #ifdef MP_DEBUG_WAIT
     // test build: MEMOPLAN_DEBUG_WAIT=wide makes every wait hold eight late

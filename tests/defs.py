@@ -166,3 +166,68 @@ def packed_wide_trace(n):
     size[0] = 64
     off = np.append(4096 * (n - 1), 4096 * np.arange(n - 1, dtype=np.int64))
     return size, np.zeros(n, np.int32), np.ones(n, np.int32), 2, off, 4096 * (n - 1) + 64
+
+
+def _planner_constant(name):
+    """A constexpr number of the single-trace planner's source."""
+    import os
+    import re
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2203_00448_amd",
+                        "csrc", "plan_trace.hip")
+    return int(re.search(r"\b%s = (\d+)" % name, open(path).read()).group(1))
+
+
+def one_workgroup_places(t):
+    """The single-trace planner's choice of its lowest fit's form for a trace of
+    32-bit unit counts: True where one workgroup places what the others prepare.
+    Up to 64 windows of 128 consecutive ranks, their dependency depth and the
+    pairs that meet."""
+    if t.n <= 4096:
+        return False
+    order = np.lexsort((np.arange(t.n), t.first, -t.size))
+    windows = min(min(4096, -(-t.n // 256)), _planner_constant("kDepthWindows"))
+    depth = met = 0
+    for b in range(windows):
+        ids = order[(t.n - 128) * b // (windows - 1):][:128]
+        f, l = t.first[ids], t.last[ids]
+        m = np.tril((f[:, None] <= l[None, :]) & (f[None, :] <= l[:, None]), -1)
+        level = np.ones(128, int)
+        for i in range(1, 128):
+            level[i] = 1 + (level[:i] * m[i, :i]).max()
+        depth += int(level.max())
+        met += int(m.sum())
+    return (100 * depth > _planner_constant("kDepthPercent") * windows * 128 and
+            100 * met < _planner_constant("kMeetPercent") * windows * (128 * 127 // 2))
+
+
+def gap_trace(k, m, crowd, tiny, births=8, seed=0):
+    """k long tensors with a gap of their size below each: 2k tensors of op 0, all
+    of one size, of which every second lives to the end.  Into the gaps go m of the
+    same size with short lives, `births` an op and `crowd` more at one op, which then
+    fill as many gaps at once; with `tiny` one of a single byte that meets all the
+    others is ranked last.  Returns (trace, offsets, peak): without the long ones the
+    short ones' plan is theirs by slots, which the caller's oracle makes for them
+    alone (`plan`), and slot s is gap s while there are gaps."""
+    from paper_2203_00448_amd import tracegen as tg
+    import oracle
+    rng = np.random.default_rng(seed)
+    unit = 128
+    first = 1 + np.arange(m) // births
+    last = np.minimum(first.max(), first + rng.integers(0, 3, m))
+    at = m // 2
+    first[at:at + crowd] = first[at]
+    last[at:at + crowd] = first[at]
+    ops = int(first.max()) + 1
+    alone, peak = oracle.plan_trace(np.full(m, unit, np.int64), first.astype(np.int32),
+                                    last.astype(np.int32), ops)
+    slot = alone // unit
+    off = np.where(slot < k, 2 * slot, k + slot) * unit
+    long_last = np.where(np.arange(2 * k) % 2 == 1, ops - 1, 0)
+    size = np.full(2 * k + m, unit, np.int64)
+    first, last = np.concatenate([np.zeros(2 * k, int), first]), np.concatenate([long_last, last])
+    off = np.concatenate([np.arange(2 * k) * unit, off])
+    top = max(2 * k * unit, int(off.max()) + unit)
+    if tiny:  # the lowest byte that nothing ever covers: all of op 0's are covered
+        size, first, last = np.append(size, 1), np.append(first, 0), np.append(last, ops - 1)
+        off, top = np.append(off, top), top + 1
+    return tg.Trace(size, first.astype(np.int32), last.astype(np.int32), ops), off, top

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import oracle
-from defs import interleaved_trace, packed_wide_trace
+from defs import gap_trace, interleaved_trace, one_workgroup_places, packed_wide_trace
 from gpu_util import dev, host, need_gpu, torch
 from paper_2203_00448_amd import tracegen as tg
 
@@ -243,8 +243,7 @@ def test_short_trace_paths(n, policy):
 def test_one_workgroup_places(n):
     """Traces deep and sparse enough for one placing workgroup (equal sizes
     chaining in start order), with long-lived tensors that have most of the
-    window late, more than 64 gaps, and a preparation that places by itself
-    (more gaps than a hand-over holds)."""
+    window late."""
     binding = need_gpu()
     rng = np.random.default_rng(330 + n)
     ops = n // 25
@@ -252,17 +251,30 @@ def test_one_workgroup_places(n):
     last = np.minimum(ops - 1, first + rng.geometric(0.3, n) - 1).astype(np.int32)
     last[rng.random(n) < 0.02] = ops - 1
     size = 64 * rng.choice([1, 2, 3, 4, 5, 8, 20], n).astype(np.int64)
+    t = tg.Trace(size, first, last, ops)
+    assert one_workgroup_places(t)
     print(f"case chains of equal sizes, {n} tensors", flush=True)
-    _check(binding, tg.Trace(size, first, last, ops))
-    # alternate tensors of op 0 live on: as many one-unit gaps at op 1, met by
-    # chains of small tensors
-    k = n // 4
-    first = np.concatenate([np.zeros(2 * k), np.repeat(np.arange(1, 1 + (n - 2 * k) // 8 + 1), 8)[: n - 2 * k]])
-    first = first.astype(np.int32)
-    last = first.copy()
-    last[1:2 * k:2] = first.max()
-    last[2 * k:] = np.minimum(first.max(), first[2 * k:] + rng.integers(0, 3, n - 2 * k))
-    size = np.full(n, 64, np.int64)
-    size[2 * k::17] = 128
-    print(f"case {k} gaps, {n} tensors", flush=True)
-    _check(binding, tg.Trace(size, first, last, int(first.max()) + 1))
+    _check(binding, t)
+
+
+@pytest.mark.parametrize("name, k, m, crowd, tiny", [
+    # 4,200 gaps for most tensors, 300 tensors at once that fill as many: the walk
+    # over the gaps goes on from the first 64 to later ones
+    ("4,200 gaps", 4200, 70_000, 300, False),
+    # besides a last tensor that meets all others: several runs of ranges (a byte is
+    # the unit, and the ranges reach past the coverage bitmap), placed by its preparer
+    ("4,200 gaps, several runs", 4200, 70_000, 300, True),
+    # more ranges than a workgroup's buffer holds: a shared one
+    ("140,000 ranges", 1, 140_000, 300, True),
+])
+def test_one_workgroup_places_gaps(name, k, m, crowd, tiny):
+    """Hand-overs of more gaps than the placing workgroup loads at once, and tensors
+    that their preparers place, where one workgroup places the rest."""
+    binding = need_gpu()
+    t, eo, ep = gap_trace(k, m, crowd, tiny)
+    assert one_workgroup_places(t)
+    print(f"case {name}", flush=True)
+    off, peak = _plan(binding, t)
+    bad = np.nonzero(off != eo)[0]
+    assert bad.size == 0, f"{bad.size} offsets differ, first at {bad[:5]}"
+    assert peak == ep

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import oracle
-from defs import (interleaved_trace, packed_wide_trace, best_fit_candidates, brute_force_opt, conflict, greedy_definitional,
+from defs import (gap_trace, interleaved_trace, packed_wide_trace, best_fit_candidates, brute_force_opt, conflict, greedy_definitional,
                   intersecting_pairs_band, live_profile_bruteforce, lowest_fit_candidates,
                   rank_order)
 from paper_2203_00448_amd import tracegen as tg
@@ -542,3 +542,11 @@ def test_dag_depth_hand_and_bruteforce():
         level, depth = oracle.dag_depth(t.size, t.first, t.last, t.num_ops)
         blevel, bdepth = _longest_chain_bruteforce(t.size, t.first, t.last)
         assert level.tolist() == blevel and depth == bdepth
+
+
+def test_gap_trace():
+    """The generator of a trace with many gaps gives the oracle's plan of it."""
+    for k, m, crowd, tiny in [(20, 300, 50, True), (5, 200, 30, True), (40, 900, 10, False)]:
+        t, off, peak = gap_trace(k, m, crowd, tiny)
+        eo, ep = oracle.plan_trace(t.size, t.first, t.last, t.num_ops)
+        assert np.array_equal(off, eo) and peak == ep
