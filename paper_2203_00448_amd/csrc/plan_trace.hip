@@ -110,10 +110,11 @@ struct TFlags {
     uint32_t pool[kPoolSlots];        // 1 while a workgroup holds the slot
     uint32_t roles;                   // lowest fit: workgroups started (the first one places), or kAlone
     uint32_t chain;                   // lowest fit: one workgroup places (else each its own ranks)
-    uint32_t depth, meets, done_depth;  // its measures, summed over the sampled windows
+    uint32_t depth, chain_ns, done_depth;  // its measures, summed over the sampled windows
     alignas(64) uint32_t front;       // lowest fit: every rank below is placed and visible
     uint32_t hist[64];      // band lengths by bit width
     uint64_t peak;
+    uint64_t pairs;         // that meet, of the whole trace
     int64_t long_prefix_tiles;
 };
 
@@ -148,10 +149,11 @@ __device__ __forceinline__ void init_flags(TFlags* fl) {
         fl->roles = 0;
         fl->chain = 0;
         fl->depth = 0;
-        fl->meets = 0;
+        fl->chain_ns = 0;
         fl->done_depth = 0;
         fl->front = 0;
         fl->peak = 0;
+        fl->pairs = 0;
         fl->planned = 0;
     }
 }
@@ -303,27 +305,32 @@ __device__ __forceinline__ int32_t gallop_reach(const int32_t* f, int32_t q, int
     return (int32_t)a;
 }
 
-__global__ void t_reach_kernel(const int32_t* first, const int32_t* last, const int32_t* pf,
+__global__ __launch_bounds__(256) void t_reach_kernel(const int32_t* first, const int32_t* last, const int32_t* pf,
                                const int32_t* pl, const uint32_t* pid, int64_t n,
                                int32_t* __restrict__ reach, TFlags* fl) {
-    // band-length histogram by bit width: per workgroup in LDS, then one
-    // device atomic per nonzero bin (one per position would serialize on the
-    // few bins most bands fall in)
+    // band-length histogram by bit width, and the bands' sum: per workgroup in
+    // LDS, then one device atomic per nonzero bin (one per position would
+    // serialize on the few bins most bands fall in)
     __shared__ uint32_t h[33];
     __shared__ uint32_t s_last;
+    __shared__ uint64_t red[256 / kWave];
     if (fl->abort) return;
     if (threadIdx.x < 33) h[threadIdx.x] = 0u;
     __syncthreads();
     const TView v = view(fl, first, last, pf, pl, pid);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    uint64_t pairs = 0;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += stride) {
         const int32_t r = gallop_reach(v.first, (int32_t)q, (int32_t)n, v.last[q]);
         reach[q] = r;
         const uint32_t band = (uint32_t)(r - q - 1);
+        pairs += band;
         atomicAdd(&h[band ? 32 - __builtin_clz(band) : 0], 1u);
     }
-    __syncthreads();
+    pairs = block_reduce<256>(pairs, OpAdd<uint64_t>(), red);  // (the histogram is in, too)
     if (threadIdx.x < 33 && h[threadIdx.x]) atomicAdd(&fl->hist[threadIdx.x], h[threadIdx.x]);
+    if (threadIdx.x == 0 && pairs)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&fl->pairs), (unsigned long long)pairs);
     memory_done();
     __syncthreads();
     if (threadIdx.x == 0) s_last = atomicAdd(&fl->done_reach, 1u) == gridDim.x - 1 ? 1u : 0u;
@@ -1960,19 +1967,33 @@ __global__ __launch_bounds__(BLOCK) void t_place_kernel(PlaceArgs a, WideArgs wi
 }
 
 // Rank by position (the inverse of the rank order), for the hand-overs, and the
-// choice of the lowest fit's kernel from up to kDepthWindows windows of 128
-// consecutive ranks, one a workgroup: their dependency depth (level of a
-// tensor: one more than the highest among the window's earlier ranks it meets)
-// and the share of their pairs that meet.  256 workgroups placing their own
-// ranks take about 0.75 us a level, one workgroup about 0.33 us a rank whatever
-// the depth, and more where a tensor's late predecessors are many (each is held
-// in a lane and walked past).  Measured (depth and pairs met as shares of a
-// window's most), each its own / one workgroup: ResNeXt-like 30,000 tensors (2%,
-// 0%) 1.2 / 10 ms; decode-like 40,000 (63%, 15%) 19.1 / 13.5 ms; ranking-like
-// 300,000 (76%, 41.3%) 209 / 180 ms, 70,000 (73%, 43.7%) 43.2 / 42.6 ms, 40,000
-// (70%, 48%) 24.4 / 29.2 ms, 20,000 (71%, 56%) 15.2 / 23.0 ms.
+// choice of the lowest fit's kernel, from up to kDepthWindows windows of
+// kDepthWindow consecutive ranks, one a workgroup: their dependency depth (level of
+// a tensor: one more than the highest among the window's earlier ranks it meets)
+// and the share of their pairs that meet.
+// 256 workgroups placing their own ranks take kSelfNs a level.  One workgroup takes
+// kChainNs a rank and, as late predecessors become many (each is held in a lane and
+// walked past), kMeetNs times the share that meets; where nearly all of them do, the
+// late ones stack up and each is one step of the walk: kAllMeetNs times the share's
+// 32nd power.  That part counts by windows, not by their mean: ranks that all meet
+// can cost more than the others save.  (Fitted to the following; depth and share of
+// each, each its own / one workgroup in ms.)  ResNeXt-like 30,000 tensors (1.5%, 0%)
+// 1.2 / 2.5; decode-like 40,000 (63%, 15%) 19.1 / 11.1; equal sizes 36,000 (98%, 47%)
+// 30.6 / 18.2; ranking-like 150,000 (76%, 42%) 99.6 / 81.6, 70,000 (74%, 44.5%) 47.2
+// / 41.4, 40,000 (71%, 48%) 23.7 / 26.6, 20,000 (72%, 57%) 13.8 / 21.0; 12,000 that
+// all meet 13.4 / 50.6, and they before 36,000 of equal sizes in chains (90%, 36%)
+// 43.7 / 69.2.
+// Nor does one workgroup place where tensors have more predecessors than one run
+// holds: those are placed by their preparers, which wait rank by rank through
+// memory.  The last rank's are estimated by the mean number a tensor meets, and that
+// the coverage bitmap does not hold their union by the mean live units.  Ranking-like
+// ones in units of 4 bytes, 18,900 met by each of 100,000: 969 / 1216 ms; 14,700 by
+// each of 60,000: 256 / 243.
 constexpr uint32_t kDepthWindow = 128, kDepthWindows = 64;
-constexpr uint64_t kDepthPercent = 45, kMeetPercent = 43;
+constexpr uint32_t kWindowPairs = kDepthWindow * (kDepthWindow - 1) / 2;
+constexpr uint64_t kDepthPercent = 45;  // measured down to here; below, each its own
+constexpr uint64_t kSelfNs = 870;
+constexpr uint32_t kChainNs = 170, kMeetNs = 710, kAllMeetNs = 3700;
 __global__ __launch_bounds__(256) void t_rank_of_kernel(const uint32_t* __restrict__ order,
                                                         const int32_t* __restrict__ reach,
                                                         int64_t n, uint32_t* __restrict__ rank_of,
@@ -2015,15 +2036,22 @@ __global__ __launch_bounds__(256) void t_rank_of_kernel(const uint32_t* __restri
     const uint32_t d = wave_reduce(max(lv[0], lv[1]), OpMax<uint32_t>());
     met = wave_reduce(met, OpAdd<uint32_t>());
     if (lane == 0) {
+        const float share = (float)met / (float)kWindowPairs;
+        float power = share;  // 32nd
+        for (int k = 0; k < 5; ++k) power *= power;
         atomicAdd(&fl->depth, d);
-        atomicAdd(&fl->meets, met);
+        atomicAdd(&fl->chain_ns,
+                  (uint32_t)((float)kChainNs + (float)kMeetNs * share + (float)kAllMeetNs * power));
         memory_done();
         if (atomicAdd(&fl->done_depth, 1u) == windows - 1) {
-            const uint64_t w = (uint64_t)min(n, (int64_t)kDepthWindow);
-            const bool deep = 100ull * flag_load(&fl->depth) > kDepthPercent * (windows * w);
-            const bool sparse =
-                100ull * flag_load(&fl->meets) < kMeetPercent * (windows * (w * (w - 1) / 2));
-            fl->chain = deep && sparse ? 1u : 0u;
+            const uint64_t levels = flag_load(&fl->depth);  // of windows * kDepthWindow ranks
+            const bool deep = 100 * levels > kDepthPercent * windows * kDepthWindow;
+            const bool faster = (uint64_t)flag_load(&fl->chain_ns) * kDepthWindow < kSelfNs * levels;
+            const double mean = (double)fl->pairs / (double)n;  // half of what a tensor meets
+            const bool several =
+                2.0 * mean > (double)kRunCap &&
+                (double)(fl->sum >> fl->shift) * mean / (double)n > 64.0 * (double)kRunCap;
+            fl->chain = deep && faster && !several ? 1u : 0u;
         }
     }
 }

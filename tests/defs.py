@@ -181,12 +181,13 @@ def one_workgroup_places(t):
     """The single-trace planner's choice of its lowest fit's form for a trace of
     32-bit unit counts: True where one workgroup places what the others prepare.
     Up to 64 windows of 128 consecutive ranks, their dependency depth and the
-    pairs that meet."""
+    pairs that meet give the cost of either form; besides, the mean number of
+    tensors one meets and of units alive at once."""
     if t.n <= 4096:
         return False
     order = np.lexsort((np.arange(t.n), t.first, -t.size))
     windows = min(min(4096, -(-t.n // 256)), _planner_constant("kDepthWindows"))
-    depth = met = 0
+    levels, chain_ns = 0, 0
     for b in range(windows):
         ids = order[(t.n - 128) * b // (windows - 1):][:128]
         f, l = t.first[ids], t.last[ids]
@@ -194,10 +195,21 @@ def one_workgroup_places(t):
         level = np.ones(128, int)
         for i in range(1, 128):
             level[i] = 1 + (level[:i] * m[i, :i]).max()
-        depth += int(level.max())
-        met += int(m.sum())
-    return (100 * depth > _planner_constant("kDepthPercent") * windows * 128 and
-            100 * met < _planner_constant("kMeetPercent") * windows * (128 * 127 // 2))
+        levels += int(level.max())
+        share = m.sum() / (128 * 127 // 2)
+        chain_ns += (_planner_constant("kChainNs") + _planner_constant("kMeetNs") * share +
+                     _planner_constant("kAllMeetNs") * share ** 32)
+    by_first = np.sort(t.first)
+    mean = float((np.searchsorted(by_first, t.last, "right") - np.searchsorted(
+        by_first, t.first, "left")).sum() - t.n)  # pairs, those of one op's births twice
+    _, births = np.unique(t.first, return_counts=True)
+    mean = (mean - (births * (births - 1) // 2).sum()) / t.n
+    unit = np.bitwise_or.reduce(t.size)
+    unit = int(unit & -unit)
+    run = _planner_constant("kRunCap")
+    several = 2 * mean > run and t.size.sum() // unit * mean / t.n > 64 * run
+    return bool(100 * levels > _planner_constant("kDepthPercent") * windows * 128 and
+                chain_ns * 128 < _planner_constant("kSelfNs") * levels and not several)
 
 
 def gap_trace(k, m, crowd, tiny, births=8, seed=0):

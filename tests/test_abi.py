@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -179,3 +180,28 @@ def test_placement_waits_have_no_limit():
     role = re.search(r"uint32_t chain_role\(.*?\n}\n", text, flags=re.S).group(0)
     assert "clock64" in role
     assert "clock64" not in text.replace(role, "")
+
+
+def test_placement_form():
+    """The form of the single-trace placement, by the rule's own constants: one
+    workgroup places deep traces few of whose ranks meet, not those where many ranks
+    all meet beside many that do not, nor those whose tensors have more predecessors
+    than one run holds (of no union that the coverage bitmap could draw)."""
+    from defs import gap_trace, one_workgroup_places
+    from paper_2203_00448_amd import tracegen as tg
+
+    def ranking(n, births, unit):
+        rng = np.random.default_rng(5)
+        first = np.arange(n) // births
+        last = np.minimum(first.max(), first + rng.integers(1, 1001, n))
+        size = np.floor(2.0 ** (6 + 10 * rng.random(n))).astype(np.int64)
+        size = (size + unit - 1) // unit * unit
+        size[0] = unit
+        return tg.Trace(size, first.astype(np.int32), last.astype(np.int32), int(first.max()) + 1)
+
+    assert one_workgroup_places(tg.decode100k())
+    assert one_workgroup_places(ranking(150_000, 10, 64))
+    assert one_workgroup_places(ranking(60_000, 16, 4))       # 14,700 met by each
+    assert not one_workgroup_places(ranking(60_000, 20, 4))   # 18,000
+    assert one_workgroup_places(gap_trace(50, 36_000, 0, False)[0])
+    assert not one_workgroup_places(gap_trace(6000, 36_000, 0, False)[0])  # a quarter all meet

@@ -260,10 +260,10 @@ def test_one_workgroup_places(n):
 @pytest.mark.parametrize("name, k, m, crowd, tiny", [
     # 4,200 gaps for most tensors, 300 tensors at once that fill as many: the walk
     # over the gaps goes on from the first 64 to later ones
-    ("4,200 gaps", 4200, 70_000, 300, False),
+    ("4,200 gaps", 4200, 110_000, 300, False),
     # besides a last tensor that meets all others: several runs of ranges (a byte is
     # the unit, and the ranges reach past the coverage bitmap), placed by its preparer
-    ("4,200 gaps, several runs", 4200, 70_000, 300, True),
+    ("4,200 gaps, several runs", 4200, 110_000, 300, True),
     # more ranges than a workgroup's buffer holds: a shared one
     ("140,000 ranges", 1, 140_000, 300, True),
 ])
