@@ -550,7 +550,8 @@ ProbeLayout probe_layout(int64_t n, int32_t num_ops, int64_t capacity) {
     L.keys0 = take(ev * 8);
     L.keys1 = take(ev * 8);
     // the sort is over before the packed events are written, and its scratch is
-    // smaller (half a byte an event and 17 KiB, beyond 4,096 events)
+    // smaller (beyond 4,096 events 17 KiB and half a byte an event, beyond 16,384
+    // two bytes an event more)
     L.radix = L.packed;
     L.bstart = take(ops * 4);
     L.dstart = take(ops * 4);

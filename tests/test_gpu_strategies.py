@@ -317,12 +317,14 @@ def test_breadth_paths(name, policy):
     _check_breadth(binding, [tg.resnext_trace(1, 900), t, tg.chain256(), t], policy)
 
 
-@pytest.mark.parametrize("n", [4097, 8192, 8193, 16_384, 16_385, 300_001, 1_048_577, 2_500_000])
+@pytest.mark.parametrize("n", [4097, 8192, 8193, 16_384, 16_385, 262_144, 262_145, 1_048_577,
+                               2_500_000])
 def test_bump_sort_paths(n):
     """Bump plans of more than 4,096 tensors are sorted by (trace, first op) in
     8-bit digits: digits that all differ, that are alike in every key (left
     out), keys in order already, an odd number of digits left out, partial
-    tiles, and several groups of 256 tiles (n > 1,048,576)."""
+    tiles, more tiles than counting workgroups (n > 1,048,576), and one and
+    several groups of 64 tiles (262,144 pairs)."""
     binding = need_gpu()
     rng = np.random.default_rng(n)
     size = rng.integers(1, 5000, n).astype(np.int64)
@@ -344,3 +346,18 @@ def test_bump_sort_paths(n):
         exp = np.empty(n, np.int64)
         exp[order] = np.cumsum(size[order]) - size[order]
         assert np.array_equal(off, exp) and peak == size.sum()
+
+
+def test_bump_sort_second_block():
+    """A sort beyond one block of 64 groups of tiles (2^24 pairs)."""
+    binding = need_gpu()
+    n, ops = (1 << 24) + 300_000, 1 << 12
+    rng = np.random.default_rng(98)
+    size = rng.integers(1, 5000, n).astype(np.int64)
+    first = rng.integers(0, ops, n).astype(np.int16)
+    print(f"case bump, {n} tensors in any order", flush=True)
+    off, peak = _bump(binding, tg.Trace(size, first.astype(np.int32), first.astype(np.int32), ops))
+    order = np.argsort(first, kind="stable")  # 16-bit keys: a radix sort
+    exp = np.empty(n, np.int64)
+    exp[order] = np.cumsum(size[order]) - size[order]
+    assert np.array_equal(off, exp) and peak == size.sum()
