@@ -30,8 +30,8 @@ constexpr int kTileItems = 4;                       // candidates per thread per
 constexpr int64_t kTileJ = kVBlock * kTileItems;    // candidates per tile
 constexpr unsigned kTileGrid = 2048;                // workgroups of the count pass (tile ranges)
 constexpr int kWriteBlock = 1024;
-// Candidates up to which a wave writes a row alone (four rounds of its loads, no
-// exchange); more are split over the workgroup's 16 waves.
+// Candidates up to which a wave always writes a row alone (four rounds of its loads,
+// no exchange).
 constexpr int64_t kWaveRow = 2048;
 constexpr int kWriteUnroll = 8;                     // candidate loads in flight per lane (write pass)
 
@@ -430,11 +430,12 @@ __global__ __launch_bounds__(kVBlock) void v_tile_kernel(
 // its long rows at once (rows b, b + G, b + 2G, ... for workgroup b of G, so
 // that neighbours in class order, often alike, land in different
 // workgroups) and lists those with pairs.  Each listed row of up to kWaveRow
-// candidates is written by one wave; each longer one by the whole workgroup:
-// each wave takes a contiguous part of the band, counts its hits, and after an
-// exchange of the counts writes them in j order.  Rows write disjoint ranges,
-// so the list order is free.  Bound by the chain of loads over the longest band:
-// 100 rows of up to 100,000 candidates 99 us with four waves a row, 49 us with 16.
+// candidates is written by one wave; a longer one by the whole workgroup, unless
+// there are enough of them alike to keep every wave at one of its own: each wave
+// takes a contiguous part of the band, counts its hits, and after an exchange of
+// the counts writes them in j order.  Rows write disjoint ranges, so the list order
+// is free.  Bound by the chain of loads over the longest band: 100 rows of up to
+// 100,000 candidates 99 us with four waves a row, 49 us with 16.
 __global__ __launch_bounds__(kWriteBlock) void v_long_write_kernel(
     const int32_t* first, const int32_t* last, const int64_t* off, const int64_t* size,
     const int32_t* pf, const int32_t* pl, const int64_t* po, const int64_t* ps,
@@ -445,6 +446,7 @@ __global__ __launch_bounds__(kWriteBlock) void v_long_write_kernel(
     __shared__ uint32_t wcnt[2][kWaves];
     __shared__ int32_t list[kWriteBlock];
     __shared__ uint32_t n_list;
+    __shared__ unsigned long long wide, widest;  // candidates of the rows beyond kWaveRow
     const VArrays a = pick_arrays(fl, first, last, off, size, pf, pl, po, ps, pid);
     const int64_t n_long = fl->n_long;
     const uint32_t* long_rows = long_rows_of(sorted, n, fl);
@@ -452,16 +454,31 @@ __global__ __launch_bounds__(kWriteBlock) void v_long_write_kernel(
     int buf = 0;
     const int64_t G = gridDim.x;
     for (int64_t base = blockIdx.x; base < n_long; base += G * kWriteBlock) {
-        if (tid == 0) n_list = 0;
+        if (tid == 0) {
+            n_list = 0;
+            wide = widest = 0;
+        }
         __syncthreads();
         const int64_t k = base + tid * G;
         if (k < n_long) {
             const int32_t q = (int32_t)long_rows[k];
             const int64_t start = cnt[q];
-            if (start != cnt[q + 1] && start < cap) list[atomicAdd(&n_list, 1u)] = q;
+            if (start != cnt[q + 1] && start < cap) {
+                list[atomicAdd(&n_list, 1u)] = q;
+                const int64_t len = reach[q] - q - 1;
+                if (len > kWaveRow) {
+                    atomicAdd(&wide, (unsigned long long)len);
+                    atomicMax(&widest, (unsigned long long)len);
+                }
+            }
         }
         __syncthreads();
         const uint32_t listed = n_list;
+        // Shared, a row is read twice by 16 waves; alone, once by one: a wave each
+        // when no row is more than an eighth of them all.  The whole validation of
+        // 20,000 and 40,000 tensors most of which meet, all rows with pairs: 690 and
+        // 1194 us with every row shared, 598 and 784 so.
+        const bool share = widest * (kWaves / 2) > wide;
         // the pairs of row q among [s0, s1), from `pos` on, until `left` are found
         auto write_row = [&](int64_t q, int64_t oq, int64_t sq, int64_t s0, int64_t s1, int64_t pos,
                              int64_t left) {
@@ -486,10 +503,10 @@ __global__ __launch_bounds__(kWriteBlock) void v_long_write_kernel(
         };
         for (uint32_t li = (uint32_t)wid; li < listed; li += kWaves) {
             const int64_t q = list[li], r = reach[q];
-            if (r - q - 1 <= kWaveRow)
+            if (!share || r - q - 1 <= kWaveRow)
                 write_row(q, a.off[q], a.size[q], q + 1, r, cnt[q], cnt[q + 1] - cnt[q]);
         }
-        for (uint32_t li = 0; li < listed; ++li) {
+        for (uint32_t li = 0; share && li < listed; ++li) {
             const int64_t q = list[li];
             const int64_t start = cnt[q];
             const int64_t r = reach[q];

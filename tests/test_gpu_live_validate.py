@@ -434,3 +434,21 @@ def test_validate_write_row_edges(band):
         for cap in (ec, max(ec - 1, 1)):
             gp, gc, st = _gpu_pairs(binding, t, off, capacity=cap)
             assert gc == ec and np.array_equal(gp, ep[:cap])
+
+
+def test_validate_write_rows_alone_and_shared():
+    """Many long rows a workgroup: a wave each while no row is longer than an eighth
+    of them all, and the workgroups that hold a much longer one share theirs."""
+    binding = need_gpu()
+    n, band = 14_000, 3000
+    first = np.arange(n, dtype=np.int32)
+    last = np.minimum(n - 1, first + band).astype(np.int32)
+    last[[5, 700, 1024 + 9]] = n - 1
+    t = tg.Trace(np.full(n, 64, np.int64), first, last, n)
+    off = 64 * (np.arange(n, dtype=np.int64) % (band - 100))  # one pair a row, near its end
+    off[50::701] = 32
+    ep, ec = _oracle_pairs(t, off)
+    print(f"case {n} rows of {band} candidates ({ec} conflicts)", flush=True)
+    for cap in (ec, ec // 2):
+        gp, gc, st = _gpu_pairs(binding, t, off, capacity=cap)
+        assert gc == ec and np.array_equal(gp, ep[:cap])
