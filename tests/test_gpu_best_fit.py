@@ -143,12 +143,36 @@ def test_decode100k_single_trace():
     assert int(p.item()) == ep
 
 
+def _wide_neighbourhood(K, rng, shuffle):
+    """A smallest tensor t that meets K others, in whose offsets there are gaps: short
+    ones, four an op, below a floor; above it six that t meets, with gaps where
+    tensors that live only after t lie between them, from wide to narrow in address
+    order, and the two narrowest that hold t equal."""
+    T = -(-(K - 6) // 4)
+    first, last, size = [0], [T - 1], [50]                    # t
+    for i in range(K - 6):
+        first.append(i // 4), last.append(i // 4), size.append(int(rng.integers(1300, 5000)))
+    first.append(T), last.append(T + 1), size.append(20_000)  # the floor
+    for met, above in ((1000, (900,)), (800, (600,)), (500, (300, 300)), (250, (120,)),
+                       (110, (60, 60)), (55, ())):
+        first.append(int(rng.integers(T // 4, T)))  # (so that none meets more than K)
+        last.append(T + 1), size.append(met)
+        for b in above:
+            first.append(T), last.append(T + 1), size.append(b)
+    first, last = np.array(first, np.int32), np.array(last, np.int32)
+    n = first.size
+    meets = ((first[:, None] <= last) & (last[:, None] >= first)).sum(axis=1) - 1
+    assert meets[0] == K == meets.max()
+    p = rng.permutation(n) if shuffle else np.argsort(first, kind="stable")
+    return tg.Trace(64 * np.array(size, np.int64)[p], first[p], last[p], T + 2)
+
+
 @pytest.mark.parametrize("K", [7, 8, 9, 15, 16, 17, 31, 32, 63, 64, 65, 255, 256])
 def test_batch_neighbour_counts(K):
     """Traces whose tensors meet K others (and, at the ends, fewer), around the
     counts at which the batched planner changes the lanes a tensor is fitted
     by; sizes of few values (equal gaps and equal ends) and of many, in order
-    and shuffled."""
+    and shuffled.  The two fits have to differ, so that a gap is chosen."""
     binding = need_gpu()
     rng = np.random.default_rng(700 + K)
     traces = []
@@ -160,10 +184,13 @@ def test_batch_neighbour_counts(K):
             last = np.minimum(first + left + (first % 2) * (K % 2), n - 1).astype(np.int32)
             size = (np.asarray(sizes, np.int64)[rng.integers(0, 4, n)] if sizes
                     else 64 * rng.integers(1, 400, n))
-            if K > 32:  # one tensor meeting exactly K others, among a few short ones
-                last = first.copy()
-                last[0] = K
+            if K > 32:
+                traces += [_wide_neighbourhood(K, rng, shuffle) for _ in range(3)]
+                continue
             p = rng.permutation(n) if shuffle else np.arange(n)
             traces.append(tg.Trace(size[p], first[p], last[p], n))
+    differ = [not np.array_equal(*(oracle.plan_trace(t.size, t.first, t.last, t.num_ops, policy)[0]
+                                   for policy in (0, BEST))) for t in traces]
+    assert any(differ) and (K <= 32 or all(differ))
     print(f"case BEST_FIT, {K} neighbours", flush=True)
     _check_batch(binding, tg.concat(traces), max_trace_len=600)
