@@ -162,7 +162,7 @@ def _wide_neighbourhood(K, rng, shuffle):
     first, last = np.array(first, np.int32), np.array(last, np.int32)
     n = first.size
     meets = ((first[:, None] <= last) & (last[:, None] >= first)).sum(axis=1) - 1
-    assert meets[0] == K == meets.max()
+    assert meets[0] == K and meets.max() <= max(K, 24)
     p = rng.permutation(n) if shuffle else np.argsort(first, kind="stable")
     return tg.Trace(64 * np.array(size, np.int64)[p], first[p], last[p], T + 2)
 
@@ -172,10 +172,11 @@ def test_batch_neighbour_counts(K):
     """Traces whose tensors meet K others (and, at the ends, fewer), around the
     counts at which the batched planner changes the lanes a tensor is fitted
     by; sizes of few values (equal gaps and equal ends) and of many, in order
-    and shuffled.  The two fits have to differ, so that a gap is chosen."""
+    and shuffled; and one tensor whose K neighbours leave gaps to choose from, so
+    that the two fits differ."""
     binding = need_gpu()
     rng = np.random.default_rng(700 + K)
-    traces = []
+    traces, chosen = [], []
     for sizes in ([64, 128, 192, 320], None):
         for shuffle in (False, True):
             n = 2 * K + 40
@@ -184,13 +185,14 @@ def test_batch_neighbour_counts(K):
             last = np.minimum(first + left + (first % 2) * (K % 2), n - 1).astype(np.int32)
             size = (np.asarray(sizes, np.int64)[rng.integers(0, 4, n)] if sizes
                     else 64 * rng.integers(1, 400, n))
-            if K > 32:
-                traces += [_wide_neighbourhood(K, rng, shuffle) for _ in range(3)]
+            chosen += [_wide_neighbourhood(K, rng, shuffle) for _ in range(2)]
+            if K > 32:  # more pairs than the lists hold
                 continue
             p = rng.permutation(n) if shuffle else np.arange(n)
             traces.append(tg.Trace(size[p], first[p], last[p], n))
-    differ = [not np.array_equal(*(oracle.plan_trace(t.size, t.first, t.last, t.num_ops, policy)[0]
-                                   for policy in (0, BEST))) for t in traces]
-    assert any(differ) and (K <= 32 or all(differ))
+    for t in chosen:
+        lowest, best = (oracle.plan_trace(t.size, t.first, t.last, t.num_ops, policy)[0]
+                        for policy in (0, BEST))
+        assert not np.array_equal(lowest, best)
     print(f"case BEST_FIT, {K} neighbours", flush=True)
-    _check_batch(binding, tg.concat(traces), max_trace_len=600)
+    _check_batch(binding, tg.concat(traces + chosen), max_trace_len=600)
