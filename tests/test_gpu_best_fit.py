@@ -162,7 +162,7 @@ def _wide_neighbourhood(K, rng, shuffle):
     first, last = np.array(first, np.int32), np.array(last, np.int32)
     n = first.size
     meets = ((first[:, None] <= last) & (last[:, None] >= first)).sum(axis=1) - 1
-    assert meets[0] == K and meets.max() <= max(K, 24)
+    assert meets[0] == K and meets.max() <= max(K, 48)
     p = rng.permutation(n) if shuffle else np.argsort(first, kind="stable")
     return tg.Trace(64 * np.array(size, np.int64)[p], first[p], last[p], T + 2)
 
