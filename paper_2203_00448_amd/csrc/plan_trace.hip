@@ -1285,7 +1285,8 @@ __device__ __forceinline__ void place_wide(const WideArgs& a, uint64_t* lks, uin
 // the commit and the loads touch memory, so a placing wave never waits for it.
 constexpr uint32_t kLoaders = 7, kLoadBlock = 4, kPlacers = 8;
 constexpr uint32_t kLdsHands = kLoaders * kLoadBlock;
-constexpr uint32_t kLdsLate = 256;        // late predecessors a slot holds (more: read from memory)
+constexpr uint32_t kLdsLate = 256;        // late predecessors a slot holds
+static_assert(kAhead <= kLdsLate, "a slot holds every late predecessor of a hand-over");
 constexpr uint32_t kSlotFree = 0xFFFFFFFFu;
 
 struct ChainArgs {  // of PlaceArgs, what the placing workgroup reads and writes
@@ -1380,7 +1381,7 @@ __device__ __forceinline__ void chain_load(const ChainArgs& a, ChainShared& S, u
                 H.gaps[lane] = gap[j];
                 H.late[lane] = lt[j];
                 const uint32_t nl = hl[j] >> 16;
-                if (!(hl[j] & kByPreparer) && nl > (uint32_t)kWave && nl <= kLdsLate) {
+                if (!(hl[j] & kByPreparer) && nl > (uint32_t)kWave) {
                     const uint64_t* late = a.late + (size_t)((base + j) & (kHands - 1)) * kAhead;
                     uint64_t v[kLdsLate / kWave];
 #pragma unroll
@@ -1418,9 +1419,7 @@ __device__ __forceinline__ uint32_t chain_place(const ChainArgs& a, ChainShared&
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int d = lane + kWave * k;
-        uint64_t v = 0;
-        if (K <= (int)kLdsLate / kWave) v = H.late[d];
-        else if (d < nl) v = agent_load64(a.late + slot * kAhead + d);
+        const uint64_t v = k < (int)kLdsLate / kWave ? H.late[d] : 0ull;
         want[k] = (uint32_t)v;
         sz[k] = (uint32_t)(v >> 32);
         pend[k] = __ballot(d < nl);
@@ -1524,9 +1523,8 @@ __device__ __forceinline__ void chain_solve(const ChainArgs& a, ChainShared& S) 
             if (lane == 0) lds_publish(&H.rank, kSlotFree);
         } else {
             const int ng = (int)(hl & 0xFFFFu), nl = (int)(hl >> 16);
-            if (T_WIDEST_WAIT || nl > 4 * kWave) x = chain_place<8>(a, S, H, r, ng, nl);
-            else if (nl <= kWave) x = chain_place<1>(a, S, H, r, ng, nl);
-            else x = chain_place<4>(a, S, H, r, ng, nl);
+            if (T_WIDEST_WAIT || nl > kWave) x = chain_place<kLdsLate / kWave>(a, S, H, r, ng, nl);
+            else x = chain_place<1>(a, S, H, r, ng, nl);
         }
         if (lane == 0) {
             __hip_atomic_store(&S.ring[r & (kRing - 1)], ((uint64_t)r << 32) | x, __ATOMIC_RELAXED,
@@ -2282,7 +2280,7 @@ hipError_t launch_plan_trace(const int64_t* size, const int32_t* first, const in
                  gap_cap_of(n),
                  reinterpret_cast<uint64_t*>(w + L.late)};
 #ifdef MP_DEBUG_WAIT
-    // test build: MEMOPLAN_DEBUG_WAIT=wide makes every wait hold eight late
+    // test build: MEMOPLAN_DEBUG_WAIT=wide makes every wait hold the most late
     // predecessors a lane; =tight besides caps the late list at 8, so tensors
     // with more wait for the rest during the collection (and report
     // MP_EDEVICE, the condition that path exists for).  Offsets stay exact.

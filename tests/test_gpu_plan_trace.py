@@ -143,7 +143,7 @@ def test_ranking1m():
 def test_debug_wait_paths(monkeypatch):
     """The test build of the library (MP_DEBUG_WAIT) with MEMOPLAN_DEBUG_WAIT
     drives the late-predecessor paths the schedule rarely reaches: "wide"
-    holds eight late predecessors a lane in every wait, "tight" caps the late
+    holds the most late predecessors a lane in every wait, "tight" caps the late
     list at 8 so that tensors with more wait for the rest during their
     collection (reporting MP_EDEVICE), "alone" starts the placing workgroup
     without any that prepares.  Offsets stay exact in each."""
