@@ -276,7 +276,7 @@ def strategies_leg(binding, tg, np, torch, medium, n_traces: int = 2048, n: int 
         return {"mean": float(r.mean()), "max": float(r.max()),
                 "at_optimum": float((x == opt).mean())}
     return {"workload": f"tiny_batch: {n_traces} ResNeXt-like traces x {n} tensors "
-                        "(seeds [6,b]), exact optimum by exhaustive search",
+                        "(seeds [6,b]), exact optimum by branch and bound",
             "optimal_ms": opt_ms, "calls": reps,
             "greedy_lowest_over_opt": ratio(low), "greedy_best_over_opt": ratio(best),
             "breadth_over_opt": ratio(breadth), "bump_over_opt": ratio(bump),

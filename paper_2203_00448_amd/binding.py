@@ -403,7 +403,7 @@ def bump_plan(size, first, last, num_ops: int, *, begin=None, check: bool = True
 def optimal_batch(begin, num_ops, size, first, last, *, check: bool = True, out=None,
                   status=None, stream=None):
     """The optimum of Eq. 2.1 for tiny traces (at most OPT_MAX_N tensors each)
-    by exhaustive search (mp_optimal_batch).  Returns (offset int64[N] of one
+    by branch and bound (mp_optimal_batch).  Returns (offset int64[N] of one
     optimal plan per trace, peak int64[B] = the optimum)."""
     L = load_library()
     begin = _dev(begin, torch.int64, "begin")

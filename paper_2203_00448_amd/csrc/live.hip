@@ -6,7 +6,9 @@
 // in a recorded trace use consecutive ops: it adds up a window of ops in LDS and
 // sends one device atomic for each op of it; ops outside go to memory directly.
 // 1 M tensors: 84 us with an atomic for each end (2 M of them), 11 us so; bound by
-// the reading then.
+// the reading then.  A workgroup's tensors are a 256th of all: with one birth an op
+// those beyond 1 M in all leave the window (the whole call for 2 M 145 -> 121 us,
+// 4 M 250 -> 228); in any order, where hardly any are in it, it is even (148, 142).
 #include <mutex>
 
 #include "internal.hpp"

@@ -34,7 +34,9 @@
 //              nothing but the placement to come within a window of ranks.
 //              Either way a tensor only waits on lower ranks, each held by a
 //              running workgroup or taken once one finishes, so the schedule
-//              cannot deadlock.
+//              cannot deadlock.  (The chain form begins once a second workgroup
+//              runs beside the placing one; where none does, the other form
+//              takes the trace, see chain_role.)
 //   output     offsets (scaled back to bytes) and the peak.
 //
 // Traces of up to 4,096 tensors go to the batched planner's kernel first, and
@@ -63,9 +65,10 @@ constexpr int kRunCap = 16384;    // ranges sorted at once in LDS
 // than the grid + kXcdGroups * (kTicketBlock - 1); the host keeps the grid at
 // most 513 - kXcdGroups * (kTicketBlock - 1).
 constexpr int kDynCap = 512;
-// (kAhead 64 / 128 / 256 / 512 with the decode-like and the ranking-like trace:
-// 62.9 / 42.1 / 33.9 / 33.3 and 664 / 535 / 605 / 765 ms: too near a front
-// leaves the long preparations late, too far makes the lists of late ranks long.)
+// (kAhead 64 / 128 / 256 / 512 with the decode-like and the ranking-like trace,
+// while the waits still had a limit: 62.9 / 42.1 / 33.9 / 33.3 and 664 / 535 / 605 /
+// 765 ms: too near a front leaves the long preparations late, too far makes the
+// lists of late ranks long.)
 constexpr uint32_t kAhead = 256;
 static_assert(kAhead <= (uint32_t)kDynCap && kDynCap <= 8 * kWave,
               "a wave holds every late predecessor, 8 a lane at most");
@@ -1269,8 +1272,10 @@ __device__ __forceinline__ void place_wide(const WideArgs& a, uint64_t* lks, uin
 // places the ranks it draws from an LDS counter, a tensor's late predecessors
 // are read from an LDS ring of (rank, offset) words that the other placing
 // waves write, and only the finished offset goes to memory, for the preparers.
-// Decode-like trace 49.4 -> 33.9 ms, ranking-like 712 -> 605 ms; a link is now
-// about 35 dependent instructions of one wave and two LDS round trips (0.4 us).
+// Decode-like trace 49.4 -> 28.4 ms, ranking-like 712 -> 530 ms; a link is now
+// about 35 dependent instructions of one wave and two LDS round trips (0.35 us).
+// Of the placing waves' time 88 and 94% goes into late ranks and the walk past them
+// (14 and 66 late a rank), 7 and 3% into waiting for a hand-over.
 
 // No wait here has a limit: each is for a lower rank's placement, its hand-over
 // or its commit, and those come in rank order from workgroups that run.  (A limit
@@ -1279,10 +1284,10 @@ __device__ __forceinline__ void place_wide(const WideArgs& a, uint64_t* lks, uin
 
 // Its 16 waves: wave 0 commits (stores the offsets of the placed prefix and
 // moves the front), waves 1-7 load hand-overs into LDS, each four ranks at a
-// time, and waves 8-15, two a SIMD and at raised priority (38.5 ms without),
-// place: more polling waves a SIMD made every link wait for their instructions
-// (16 placing waves 50 ms, 10: 35.2, 4: 45).  Only
-// the commit and the loads touch memory, so a placing wave never waits for it.
+// time, and waves 8-15, two a SIMD and at raised priority (38.5 ms without it where
+// it was 33.9), place: more polling waves a SIMD made every link wait for their
+// instructions (16 placing waves 50 ms, 10: 35.2, 4: 45).  Only the commit and the
+// loads touch memory, so a placing wave waits for it only past the first 64 gaps.
 constexpr uint32_t kLoaders = 7, kLoadBlock = 4, kPlacers = 8;
 constexpr uint32_t kLdsHands = kLoaders * kLoadBlock;
 constexpr uint32_t kLdsLate = 256;        // late predecessors a slot holds
