@@ -156,14 +156,14 @@ int bit_width64(uint64_t x) { return x ? 64 - __builtin_clzll(x) : 0; }
 // one op stacked from the last offset on, cannot end below the best peak; the
 // search stops at the live-bytes lower bound.  The best starts at the greedy by
 // size plan, which reaches the bound for nine in ten of the tiny ResNeXt-like
-// traces.
+// traces, or else at the best of 128 other greedy plans.
 //
 // One wave per trace.  Tensors are numbered by size descending, so the masks
 // below are the same for every lane and sit in scalar registers; a lane holds
 // its tensors' ends in registers and searches depth first below prefixes of the
 // order (the first kOptPrefix levels, dealt to the lanes as they become free).
 // Each turn of the loop evaluates the lane's node and either places a tensor or
-// backs up, without memory accesses: bound by instruction issue (about 500
+// backs up, without memory accesses: bound by instruction issue (several hundred
 // vector instructions a turn) and by the longest search of the batch.  All
 // lanes share the best peak through ballots, so the plan found does not depend
 // on timing.  2048 traces of 10 tensors: 6.80 ms for the search over all n!
@@ -178,6 +178,7 @@ struct OptShared {
     int32_t id[kOptMaxN];
     uint32_t meets[kOptMaxN];  // bit j: lifetimes of i and j meet (j != i)
     uint32_t alive[kOptMaxN];  // bit j: j is alive at i's first op
+    int32_t by_area[kOptMaxN]; // numbers by size times lifetime descending
 };
 
 __device__ __forceinline__ uint32_t opt_uniform(uint32_t v) {
@@ -191,30 +192,29 @@ __device__ __forceinline__ T opt_wave_min(T v) {
     return wave_reduce(v, OpMin<T>());
 }
 
-// The search over T counts of the trace's unit.  `ends`: this lane's best plan
-// (the greedy one in every lane to start with), `best` its peak; returns the
-// least peak found, `mine` the peak of the lane's `ends`.
-template <typename T>
-__device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb, T best, T (&ends)[kOptMaxN],
-                        T* mine_out) {
+// The search over T counts of the trace's unit.  `ends`: this lane's best plan so
+// far, `mine` its peak, `best` the least of them; returns the least peak found.
+template <typename T, int N>
+__device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb, T best, T (&ends)[N],
+                                        T& mine) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint64_t below = (1ull << lane) - 1ull;
     const uint32_t all = (1u << n) - 1u;
-    T sz[kOptMaxN];
-    uint32_t meets[kOptMaxN], alive[kOptMaxN];
-    T left0[kOptMaxN];  // sizes alive at i's first op, all unplaced
+    T sz[N];
+    uint32_t meets[N], alive[N];
+    T left0[N];  // sizes alive at i's first op, all unplaced
 #pragma unroll
-    for (int i = 0; i < kOptMaxN; ++i) {
+    for (int i = 0; i < N; ++i) {
         const int c = i < n ? i : 0;
         sz[i] = i < n ? opt_uniform((T)((uint64_t)S.sz[c] >> sh)) : T(0);
         meets[i] = i < n ? opt_uniform(S.meets[c]) : 0u;
         alive[i] = i < n ? opt_uniform(S.alive[c]) : 0u;
     }
 #pragma unroll
-    for (int i = 0; i < kOptMaxN; ++i) {
+    for (int i = 0; i < N; ++i) {
         left0[i] = 0;
 #pragma unroll
-        for (int j = 0; j < kOptMaxN; ++j) left0[i] += ((alive[i] >> j) & 1u) ? sz[j] : T(0);
+        for (int j = 0; j < N; ++j) left0[i] += ((alive[i] >> j) & 1u) ? sz[j] : T(0);
     }
     // prefixes of two tensors (at most 132 for 64 lanes), or of three from 11
     // tensors on, where single subtrees get long enough to idle the others
@@ -223,9 +223,8 @@ __device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb,
     for (int k = 0; k < d; ++k) n_pre *= (uint32_t)(n - k);
     uint32_t next_pre = 0;  // uniform
 
-    T end[kOptMaxN];   // ends of the placed tensors, 0 while unplaced
-    T left[kOptMaxN];  // sizes of the unplaced tensors alive at i's first op
-    T mine = best;
+    T end[N];   // ends of the placed tensors, 0 while unplaced
+    T left[N];  // sizes of the unplaced tensors alive at i's first op
     uint64_t order = 0;  // 4 bits a level
     uint32_t placed = 0, from = 0, forced = 0;
     int level = 0;
@@ -253,7 +252,7 @@ __device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb,
                     order = 0;
                     level = 0;
 #pragma unroll
-                    for (int i = 0; i < kOptMaxN; ++i) {
+                    for (int i = 0; i < N; ++i) {
                         end[i] = 0;
                         left[i] = left0[i];
                     }
@@ -268,31 +267,35 @@ __device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb,
         const int prev = level ? (int)((order >> (4 * (level - 1))) & 15u) : -1;
         T last = 0, limit = ~T(0), need = 0;
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i) last = i == prev ? end[i] - sz[i] : last;
-        T base[kOptMaxN];
+        for (int i = 0; i < N; ++i) last = i == prev ? end[i] - sz[i] : last;
+        T base[N];
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i) {
+        for (int i = 0; i < N; ++i) {
             T b = 0;
-            // the mask goes through an empty asm each turn: hoisted out of the
-            // loop, its bits became 132 lane masks and were spilled
-            uint32_t mi = meets[i];
-            asm volatile("" : "+s"(mi));
+            T top = 0;  // highest end at i's first op
+            // the masks go through an empty asm each turn: hoisted out of the
+            // loop, their bits became 132 lane masks and were spilled
+            uint32_t mi = meets[i], ai = alive[i];
+            asm volatile("" : "+s"(mi), "+s"(ai));
 #pragma unroll
-            for (int j = 0; j < kOptMaxN; ++j) {
+            for (int j = 0; j < N; ++j) {
                 const T e = end[j] & (T)(int64_t)((int32_t)(mi << (31 - j)) >> 31);
+                const T a = end[j] & (T)(int64_t)((int32_t)(ai << (31 - j)) >> 31);
                 b = e > b ? e : b;
+                top = a > top ? a : top;
             }
             base[i] = b;
             const bool un = i < n && !((placed >> i) & 1u);
             const T e = b + sz[i], h = (b > last ? b : last) + sz[i];
             limit = un && e < limit ? e : limit;
             need = un && h > need ? h : need;
-            const T l = last + left[i];  // the tensors left at i's first op, stacked
+            // the tensors left at i's first op, stacked on those placed there
+            const T l = (top > last ? top : last) + left[i];
             need = i < n && left[i] && l > need ? l : need;
         }
         uint32_t cand = 0;
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i) {
+        for (int i = 0; i < N; ++i) {
             const bool ok = base[i] < limit && (base[i] > last || (base[i] == last && i > prev));
             cand |= ok ? 1u << i : 0u;
         }
@@ -309,14 +312,14 @@ __device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb,
         uint32_t at = 0;
         T s = 0;
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i) {
+        for (int i = 0; i < N; ++i) {
             s = i == c ? sz[i] : s;
             const T e = place ? base[i] + sz[i] : T(0);
             end[i] = moves && i == c ? e : end[i];
             at |= ((alive[i] >> (c & 31)) & 1u) << i;  // the first ops at which c is alive
         }
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i) {
+        for (int i = 0; i < N; ++i) {
             const T v = moves && ((at >> i) & 1u) ? s : T(0);
             left[i] = place ? left[i] - v : left[i] + v;
         }
@@ -337,11 +340,11 @@ __device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb,
             if (busy && level == n) {
                 pk = 0;
 #pragma unroll
-                for (int i = 0; i < kOptMaxN; ++i) pk = end[i] > pk ? end[i] : pk;
+                for (int i = 0; i < N; ++i) pk = end[i] > pk ? end[i] : pk;
                 if (pk < mine) {
                     mine = pk;
 #pragma unroll
-                    for (int i = 0; i < kOptMaxN; ++i) ends[i] = end[i];
+                    for (int i = 0; i < N; ++i) ends[i] = end[i];
                 }
                 if (n == d) busy = false;  // the prefix was the whole order
             }
@@ -350,19 +353,80 @@ __device__ __forceinline__ T opt_search(const OptShared& S, int n, int sh, T lb,
             if (best <= lb) break;
         }
     }
-    *mine_out = mine;
     return best;
+}
+
+// Before the search: 64 greedy plans at once, lane l's with two tensors put first
+// (the l-th pair) and the rest by size or by area.  Nine in ten of the tiny
+// ResNeXt-like traces that greedy by size leaves above the live-bytes bound reach it
+// so, whose searches made up most of the time: three sets of 400 traces of 8
+// tensors, launch and all, 66, 130 and 83 us without and 61, 30 and 30 with them, of
+// 9 tensors 80, 84 and 92 and 35, 35 and 44 (a workgroup a trace over all orders: 51,
+// 52, 52 and 56, 698, 60).
+template <typename T, int N>
+__device__ __forceinline__ T opt_variants(const OptShared& S, int n, int sh, bool area, T best,
+                                          T (&ends)[N], T& mine) {
+    const uint32_t pair = threadIdx.x % (uint32_t)(n * (n - 1));
+    const uint32_t p0 = pair % (uint32_t)n, q = pair / (uint32_t)n, p1 = q + (q >= p0 ? 1u : 0u);
+    T off[N], end[N], pk = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) off[i] = end[i] = 0;
+    uint32_t left = (1u << n) - 1u;  // positions of the order
+    for (int t = 0; t < n; ++t) {
+        const uint32_t pos = t == 0 ? p0 : (t == 1 ? p1 : (uint32_t)__builtin_ctz(left));
+        left &= ~(1u << pos);
+        const uint32_t c = area ? (uint32_t)S.by_area[pos] : pos;
+        const T w = (T)((uint64_t)S.sz[c] >> sh);
+        const uint32_t nb = S.meets[c];
+        T hi[N];  // ends of the placed neighbours, 0 of the others
+#pragma unroll
+        for (int j = 0; j < N; ++j) hi[j] = (nb >> j) & 1u ? end[j] : T(0);
+        T x = 0;
+        while (true) {  // past the highest end among the ranges that overlap, until none does
+            T up = 0;
+#pragma unroll
+            for (int j = 0; j < N; ++j) up = off[j] < x + w && x < hi[j] && hi[j] > up ? hi[j] : up;
+            if (!__ballot(up != 0)) break;
+            x = up ? up : x;
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            off[j] = (uint32_t)j == c ? x : off[j];
+            end[j] = (uint32_t)j == c ? x + w : end[j];
+        }
+        pk = x + w > pk ? x + w : pk;
+    }
+    if (pk < mine) {
+        mine = pk;
+#pragma unroll
+        for (int i = 0; i < N; ++i) ends[i] = end[i];
+    }
+    const T low = opt_wave_min(mine);
+    return low < best ? low : best;
+}
+
+// Numbers by area, for the second set of greedy plans.
+__device__ __forceinline__ void opt_areas(OptShared& S, int n) {
+    const int lane = threadIdx.x & (kWave - 1);
+    auto area = [&](int i) { return (double)S.sz[i] * (double)(S.last[i] - S.first[i] + 1); };
+    if (lane < n) {
+        const double a = area(lane);
+        int r = 0;
+        for (int j = 0; j < n; ++j) r += area(j) > a || (area(j) == a && j < lane) ? 1 : 0;
+        S.by_area[r] = lane;
+    }
+    __syncthreads();
 }
 
 // Greedy by size over T units (tensors in rank order, each at the lowest
 // offset that fits), by one wave: lane a tries the end of tensor a, lane n
 // offset 0.  Returns the peak; ends[] the same in every lane.
-template <typename T>
-__device__ __forceinline__ T opt_greedy(const OptShared& S, int n, int sh, T (&ends)[kOptMaxN]) {
+template <typename T, int N>
+__device__ __forceinline__ T opt_greedy(const OptShared& S, int n, int sh, T (&ends)[N]) {
     const int lane = threadIdx.x & (kWave - 1);
     T pk = 0;
 #pragma unroll
-    for (int i = 0; i < kOptMaxN; ++i) ends[i] = 0;
+    for (int i = 0; i < N; ++i) ends[i] = 0;
     T my_end = 0;  // of the tensor this lane holds
     for (int t = 0; t < n; ++t) {
         const T s = (T)((uint64_t)S.sz[t] >> sh);
@@ -378,27 +442,42 @@ __device__ __forceinline__ T opt_greedy(const OptShared& S, int n, int sh, T (&e
         if (lane == t) my_end = at + s;
         pk = at + s > pk ? at + s : pk;
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i) ends[i] = i == t ? at + s : ends[i];
+        for (int i = 0; i < N; ++i) ends[i] = i == t ? at + s : ends[i];
     }
     return pk;
 }
 
-template <typename T>
-__device__ __forceinline__ void opt_plan(const OptShared& S, int n, int sh, uint64_t lb_bytes, int64_t b0,
+template <typename T, int N>
+__device__ __forceinline__ void opt_plan(OptShared& S, int n, int sh, uint64_t lb_bytes, int64_t b0,
                          int64_t* __restrict__ offset_out, int64_t* __restrict__ peak) {
     const int lane = threadIdx.x & (kWave - 1);
     const T lb = (T)(lb_bytes >> sh);
-    T ends[kOptMaxN], mine;
-    T best = opt_greedy<T>(S, n, sh, ends);
+    T ends[N], mine;
+    T best = opt_greedy<T, N>(S, n, sh, ends);
     mine = best;
-    if (best > lb) best = opt_search<T>(S, n, sh, lb, best, ends, &mine);
+    if (best > lb) best = opt_variants<T, N>(S, n, sh, false, best, ends, mine);
+    if (best > lb) {
+        opt_areas(S, n);
+        best = opt_variants<T, N>(S, n, sh, true, best, ends, mine);
+    }
+    if (best > lb) best = opt_search<T, N>(S, n, sh, lb, best, ends, mine);
     const uint64_t win = __ballot(mine == best);
     if (lane == (int)__builtin_ctzll(win)) {
 #pragma unroll
-        for (int i = 0; i < kOptMaxN; ++i)
+        for (int i = 0; i < N; ++i)
             if (i < n) offset_out[b0 + S.id[i]] = (int64_t)((uint64_t)ends[i] << sh) - S.sz[i];
         *peak = (int64_t)((uint64_t)best << sh);
     }
+}
+
+// A turn goes over all pairs of the N tensors it is written out for.
+template <typename T>
+__device__ __forceinline__ void opt_plan_n(OptShared& S, int n, int sh, uint64_t lb, int64_t b0,
+                                           int64_t* __restrict__ offset_out,
+                                           int64_t* __restrict__ peak) {
+    if (n <= 8) opt_plan<T, 8>(S, n, sh, lb, b0, offset_out, peak);
+    else if (n <= 10) opt_plan<T, 10>(S, n, sh, lb, b0, offset_out, peak);
+    else opt_plan<T, kOptMaxN>(S, n, sh, lb, b0, offset_out, peak);
 }
 
 __global__ __launch_bounds__(kWave) void optimal_kernel(
@@ -471,9 +550,9 @@ __global__ __launch_bounds__(kWave) void optimal_kernel(
     const int sh = __builtin_ctzll(orv);
     // 32-bit counts of the common unit while two sums of the sizes fit them
     if ((total >> sh) < (1ull << 31))
-        opt_plan<uint32_t>(S, n, sh, lb, b0, offset_out, peak_out + blockIdx.x);
+        opt_plan_n<uint32_t>(S, n, sh, lb, b0, offset_out, peak_out + blockIdx.x);
     else
-        opt_plan<uint64_t>(S, n, sh, lb, b0, offset_out, peak_out + blockIdx.x);
+        opt_plan_n<uint64_t>(S, n, sh, lb, b0, offset_out, peak_out + blockIdx.x);
 }
 
 }  // namespace

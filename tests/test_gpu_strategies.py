@@ -361,3 +361,29 @@ def test_bump_sort_second_block():
     exp = np.empty(n, np.int64)
     exp[order] = np.cumsum(size[order]) - size[order]
     assert np.array_equal(off, exp) and peak == size.sum()
+
+
+@pytest.mark.parametrize("n, count", [(5, 20), (7, 40), (8, 40), (9, 20), (10, 3)])
+def test_optimal_where_greedy_is_not(n, count):
+    """Traces whose greedy plans stay above the live-bytes bound, at the sizes that
+    the search is written out for (8, 10 and 12 tensors): those that another order
+    brings to the bound, and those that are searched; in order and shuffled, 32-bit
+    counts and (a byte more than 2^31 times the unit) 64-bit ones."""
+    binding = need_gpu()
+    rng = np.random.default_rng(180 + n)
+    traces = []
+    while len(traces) < count:
+        t = _tiny(rng, n, T=max(3, n), span=max(2, n // 2), unit=4, kinds=60)
+        lb = oracle.live_bytes_profile(t.size, t.first, t.last, t.num_ops)[1]
+        if oracle.plan_trace(t.size, t.first, t.last, t.num_ops)[1] > lb:
+            traces.append(t)
+    for t in traces[::2]:
+        p = rng.permutation(n)
+        t.size, t.first, t.last = t.size[p], t.first[p], t.last[p]
+    wide = [tg.Trace((t.size << 32) + 1, t.first, t.last, t.num_ops) for t in traces[::5]]
+    traces += wide
+    expected = [oracle.optimal_plan(t.size, t.first, t.last, t.num_ops)[1] for t in traces]
+    print(f"case optimum of {len(traces)} traces of {n} that greedy leaves above the bound", flush=True)
+    b, o, p = _optimal(binding, traces)
+    _check_optimal(b, o, p, traces, expected)
+    assert np.array_equal(o, _optimal(binding, traces)[1])  # the same plan every time
