@@ -455,10 +455,10 @@ __device__ __forceinline__ void opt_plan(OptShared& S, int n, int sh, uint64_t l
     T ends[N], mine;
     T best = opt_greedy<T, N>(S, n, sh, ends);
     mine = best;
-    if (best > lb) best = opt_variants<T, N>(S, n, sh, false, best, ends, mine);
-    if (best > lb) {
-        opt_areas(S, n);
-        best = opt_variants<T, N>(S, n, sh, true, best, ends, mine);
+#pragma unroll 1  // one copy of the code, fetched once
+    for (int area = 0; area < 2 && best > lb; ++area) {
+        if (area) opt_areas(S, n);
+        best = opt_variants<T, N>(S, n, sh, area != 0, best, ends, mine);
     }
     if (best > lb) best = opt_search<T, N>(S, n, sh, lb, best, ends, mine);
     const uint64_t win = __ballot(mine == best);
